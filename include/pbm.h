@@ -177,13 +177,11 @@ typedef struct {
     int32_t far_symmetric;    /* FP32 matrix-free far field, screened or not (Numerical
                                  discretization; the kernels are symmetric in x, y): every
                                  unordered triangle pair evaluated once for both directions or
-                                 every ordered pair.  0 (default): once per unordered pair on
-                                 meshes of 3584 triangles and more, per ordered pair below (where
-                                 one mesh leaves most of the device idle); 1: once per unordered
-                                 pair at every size (faster for many small meshes solved together
-                                 by pb_solve_batch); -1: per ordered pair.  Single and batched
-                                 solves of a handle use the same choice, so their results stay
-                                 bitwise equal; the two choices agree to FP32 rounding. */
+                                 every ordered pair.  0 (default, automatic): once per unordered
+                                 pair (faster at every size); 1: once per unordered pair; -1: per
+                                 ordered pair.  Single and batched solves of a handle use the same
+                                 choice, so their results stay bitwise equal; the two choices
+                                 agree to FP32 rounding. */
 } pb_options;
 
 typedef struct {

@@ -38,6 +38,16 @@ struct FarCoef {
     R cKL, cKY, cVL, cVY, cTL, cTY, cDL, cDY;
 };
 
+// Coefficients of the symmetric FP32 kernel (k_far_sym.hip), set by sym_coef
+struct SymCoef {
+    float s;                   // coordinate scale (kappa log2 e; 1 for kappa = 0)
+    float kap;                 // kappa / s
+    float cK, cV, cT, cD;      // factors of the four sums (FORM 0: kL, vL, kY, vY)
+    float kD;                  // 2 kappa^2 times the Yukawa coefficient of D
+    float aK, aV, aT, aD;      // FORM 4: Laplace coefficients inside the values
+    float bK, bV, bT, bD;      // FORM 1: Yukawa over Laplace; FORM 4: Yukawa coefficients
+};
+
 // one request of the batched far field: its mesh data, partial-sum buffer and
 // coefficients
 template <typename R>
@@ -50,6 +60,8 @@ struct FarReq {
     FarCoef<R> cf;
     int T, chunk;
     int rt, nr;        // symmetric split (k_far_sym.hip): tiles per range, ranges; 0 if unused
+    SymCoef sc;        // and its coefficients, FP64 records and tile bounds
+    const double *stat64, *tiles;
 };
 
 // One source triangle against the six points of a target triangle: the
@@ -250,28 +262,45 @@ inline int far_coef(const DevMesh &d, FarCoef<R> &cf)
 
 // Coefficients of the symmetric kernel (k_far_sym.hip), whose coordinates are
 // scaled by s = kappa log2(e) (kappa > 0): with x' = s x, 1/r = s / r', the
-// normal-derivative factors (d.n)/r^2 = s (d'.n)/r'^2 and exp(-kappa r) =
-// exp2(-r'), so the K- and T-type coefficients take s^2, the V-type ones, the
-// kappa-weighted FORM 0 one and D's s, and kappa becomes kappa / s; kexp
-// carries s.  For kappa = 0, s = 1 (coordinates and coefficients as they are,
-// kappa 0).  Returns the kernel FORM.
-inline int far_coef_sym(const DevMesh &d, FarCoef<float> &cf)
+// normal-derivative factors (d.n)/r^3 = s^2 (d'.n)/r'^3 and exp(-kappa r) =
+// exp2(-r'), so the K- and T-type coefficients take s^2, the V- and D-type ones
+// s, and kappa becomes kappa / s.  For kappa = 0, s = 1 (coordinates and
+// coefficients as they are, kappa 0).  Returns the kernel FORM: 0 (direct), 1
+// (every operator has a Laplace term: its coefficient is taken out), 3 (none
+// has), 4 (some have: a combined field with one zero constant).
+inline int sym_coef(const DevMesh &d, SymCoef &sc)
 {
     FarCoef<double> c;
-    const int form = far_coef(d, c);
-    // unscreened meshes keep their coordinates (the kernel skips the exponential)
+    int form = far_coef(d, c);
     const double s = d.prm.kappa > 0.0 ? d.prm.kappa * 1.4426950408889634 : 1.0, s2 = s * s;
-    cf = FarCoef<float>{};
-    cf.kappa = (float)(d.prm.kappa / s);
-    cf.kexp = (float)s;
-    cf.k2 = (float)c.k2;
-    cf.kL = (float)(c.kL * s2); cf.vL = (float)(c.vL * s);
-    cf.kY = (float)(c.kY * s2); cf.vY = (float)(c.vY * s); cf.kYk = (float)(c.kYk * s);
-    cf.cKL = (float)(c.cKL * s2); cf.cKY = (float)(c.cKY * s2);
-    cf.cVL = (float)(c.cVL * s); cf.cVY = (float)(c.cVY * s);
-    cf.cTL = (float)(c.cTL * s2); cf.cTY = (float)(c.cTY * s2);
-    cf.cDL = (float)(c.cDL * s); cf.cDY = (float)(c.cDY * s);
+    sc = SymCoef{};
+    sc.s = (float)s;
+    sc.kap = (float)(d.prm.kappa / s);
+    sc.kD = (float)(2.0 * c.k2 * c.cDY * s);
+    if (form == 0) {
+        sc.cK = (float)(c.kL * s2); sc.cV = (float)(c.vL * s);
+        sc.cT = (float)(c.kY * s2); sc.cD = (float)(c.vY * s);
+        return 0;
+    }
+    if (form == 1 && !(c.cKL != 0.0 && c.cVL != 0.0 && c.cTL != 0.0 && c.cDL != 0.0)) form = 4;
+    if (form == 1) {
+        sc.cK = (float)(c.cKL * s2); sc.cV = (float)(c.cVL * s);
+        sc.cT = (float)(c.cTL * s2); sc.cD = (float)(c.cDL * s);
+        sc.bK = (float)(c.cKY / c.cKL); sc.bV = (float)(c.cVY / c.cVL);
+        sc.bT = (float)(c.cTY / c.cTL); sc.bD = (float)(c.cDY / c.cDL);
+    } else if (form == 3) {
+        sc.cK = (float)(c.cKY * s2); sc.cV = (float)(c.cVY * s);
+        sc.cT = (float)(c.cTY * s2); sc.cD = (float)(c.cDY * s);
+    } else {
+        sc.cK = sc.cT = (float)s2;
+        sc.cV = sc.cD = (float)s;
+        sc.aK = (float)c.cKL; sc.aV = (float)c.cVL; sc.aT = (float)c.cTL; sc.aD = (float)c.cDL;
+        sc.bK = (float)c.cKY; sc.bV = (float)c.cVY; sc.bT = (float)c.cTY; sc.bD = (float)c.cDY;
+    }
     return form;
 }
+constexpr int kSymForms = 4;
+constexpr int kSymFormOf[kSymForms] = {0, 1, 3, 4};
+inline int sym_form_index(int form) { return form == 0 ? 0 : form == 1 ? 1 : form == 3 ? 2 : 3; }
 
 }  // namespace pbm

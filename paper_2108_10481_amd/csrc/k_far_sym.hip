@@ -5,29 +5,41 @@
 //
 // Work: tiles of 64 Morton-consecutive triangles, tile ranges of `rt` tiles;
 // an item (a, b), a <= b, is the pairs of triangles of range a x range b
-// (I <= J when a == b) and is done by one wavefront.  For a tile pair (I, J)
-// lane l holds target t = 64 I + l; in step k = 0..63 it meets source
-// s = 64 J + ((l + k) mod 64) (on a diagonal tile I == J only the steps and
-// lanes that meet each unordered pair once: 1 <= k <= 31, and k = 32 on the
-// lower half of the lanes).  Its target's sums (a1, a2, W) stay in the lane;
-// the sums of the source side -- the transposed pair -- are held by the lane
-// that meets that source and move one lane down after every step, so after
-// 64 steps each source's sums are back in lane (s mod 64): no cross-lane
-// reduction is needed.  Tile J's source records are staged once per wavefront
-// in LDS (one array per field, so the lanes' rotated reads hit distinct
-// banks).
+// (I <= J when a == b) and is done by one block of four wavefronts.  For a tile
+// pair (I, J) wavefront w holds the 16 target triangles 64 I + 16 w + r and
+// walks the 64 sources of J in four groups of 16 columns: lane l has the column
+// l mod 16 and the rows 4 (l / 16) + v, v = 0..3, the result layout of
+// v_mfma_f32_16x16x4, for every one of the 36 point pairs.
+//
+// The squared distances of a 16 x 16 block of point pairs are one matrix
+// instruction: r^2 = |X|^2 - 2 X.Y + |Y|^2 is (X, 1).(-2Y, |Y|^2) with |X|^2 as
+// the accumulator's start, which takes the six vector instructions of the
+// subtracted form off the VALU, the unit that bounds this kernel; so are the
+// normal components d.n_s = X.n_s - O_s and d.n_t = O_t - Y.n_t (O: a
+// triangle's plane offset; the points of a flat triangle lie in its plane).
+// The points enter relative to the centre of tile J, subtracted in FP64 and then
+// rounded: |Y| is at most the tile's radius, the terms that cancel against |X|^2
+// are small, and r^2 keeps the accuracy of the subtracted form as long as the
+// tiles are apart (kSymApart).  Tile pairs that are not apart take the
+// subtracted form (NEAR), and only they can hold pairs that share a vertex.
 //
 // Coordinates (points and the plane offsets) are used scaled by s = kappa
-// log2(e), with the coefficients of far_coef_sym: then exp(-kappa r) =
-// exp2(-r') with r' = r2' / sqrt(r2') and no multiply for the argument.
-// Unscreened meshes (kappa = 0, K0) keep their coordinates and skip the
-// exponential: e = 1, so the Yukawa kernels are the Laplace ones.
+// log2(e), with the coefficients of sym_coef: then exp(-kappa r) = exp2(-r')
+// with r' = r2' / sqrt(r2') and no multiply for the argument.  Unscreened
+// meshes (kappa = 0, K0) keep their coordinates and skip the exponential:
+// e = 1, so the Yukawa kernels are the Laplace ones.
 //
-// The quadrature points of a flat triangle lie in its plane, so the normal
-// components of d = x_p - y_q factor: d . n_s = x_p . n_s - o_s depends on the
-// target point only and d . n_t = o_t - y_q . n_t on the source point only
-// (o = the triangle's plane offset, y . n for any of its points).  Both are
-// formed once per triangle pair, not per point pair.
+// Bound: VALU issue.  A point pair of the direct form costs 6 instructions for
+// the kernel values, two transcendentals and 8 fused multiply-adds into the sums
+// (16.0 executed with everything outside, by counters), the issue slots are 91%
+// taken.  Measured per product, before (a lane per target triangle, the source
+// sums rotating through the wavefront, r^2 subtracted on the VALU) and now:
+// 81920 triangles direct 80.4 -> 69.5 ms, Juffer 108 -> 86 ms; 20480 triangles
+// Juffer 6.97 -> 5.98 ms; against the FP64 operator at 20480 triangles the error
+// went from 1.2e-8 / 5.5e-8 (direct / Juffer) to 0.6e-8 / 0.7e-8, the input
+// rounding of global coordinates being gone.  Three wavefronts per SIMD (168
+// registers, spilling) gained 3% on the direct form at 81920 triangles, lost 2%
+// at 20480 and 10% on Juffer.
 //
 // Output: per triangle, one 16-value partial (6 + 6 point sums, 3 curl sums)
 // per target-side item (slot b, the source range) and one per source-side
@@ -40,288 +52,461 @@
 
 namespace pbm {
 
-constexpr int kSymWaves = 2;   // independent wavefronts (items) per block
-// staged source record, one LDS array per field: 0..17 points, 18..20 normal,
-// 21 plane offset o_s, then per source point
-//   FORM 0: 22..27 kL b1, 28..33 vL b2, 34..39 kY b1, 40..45 vY b2 (the
-//           source-point constants of the direct form's target-side sums);
-//   else:   22..27 b1, 28..33 b2, 34..36 C.
-template <int FORM> struct SymLds {
-    static constexpr int NF = FORM == 0 ? 46 : 37;
-    float f[NF][64];
-    int id[3][64];
+constexpr int kSymWaves = 4;   // wavefronts per block, 16 rows of the target tile each
+// Tiles I, J are apart when their centres are at least kSymApart times the sum
+// of their radii apart: then r >= (kSymApart - 1)(rad_I + rad_J) and the terms of
+// r^2 that cancel, 2 |X| |Y|, are a small multiple of r^2
+constexpr double kSymApart = 1.25;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS of one block: the columns (sources of tile J) and per wavefront the rows
+// (its 16 targets), relative to tile J's centre
+struct SymCols {
+    f32x4 bq[6][64];      // (-2 Y_q, |Y_q|^2)
+    f32x4 bn[64];         // (n_s, -O_s)
+    f32x4 w[6][64];       // the source point's four weights (sym_cols)
+    f32x4 curl[64];       // C_s
+    int id[3][64];        // vertex ids (NEAR)
+};
+struct SymRows {
+    float x2[6][16];      // |X_p|^2
+    float x[6][3][16];    // X_p (NEAR)
+    float o[16];          // O_t
+    float d[16][16];      // the dynamic record: b1 6, b2 6, C 3
+};
+struct SymLds {
+    SymCols c;
+    SymRows r[kSymWaves];
+    f32x4 out[kSymWaves][64][4];   // source-side sums of each wavefront's rows
+    int item;
 };
 
-// one step: the 36 point pairs of target t (lane registers) and source j
-// (LDS column j); adds t's sums to a1, a2, W and the source's sums to acc
-template <int FORM, bool K0>
-__device__ __forceinline__ void sym_pair(const FarCoef<float> &cf, const SymLds<FORM> &L, int j, const float (&tx)[6],
-                                         const float (&ty)[6], const float (&tz)[6], float ot, float ntx,
-                                         float nty, float ntz, const float (&cs)[9][6], const float (&Ct)[3],
-                                         float (&a1)[6], float (&a2)[6], float (&W)[3], float (&acc)[15])
+// Sum of 16 values per lane over the four 16-lane rows of the wavefront: v_m of
+// all rows end as w_(m mod 4) of row m / 4 (v_permlane32_swap and
+// v_permlane16_swap exchange half-wavefronts and rows of two registers)
+__device__ __forceinline__ f32x4 rows_sum16(const float (&v)[16])
 {
-    const float nsx = L.f[18][j], nsy = L.f[19][j], nsz = L.f[20][j], os = L.f[21][j];
-    // dns[p] = (x_p - y) . n_s, dnt[q] = (x - y_q) . n_t
-    float dns[6], dnt[6];
+    float u[8];
 #pragma unroll
-    for (int p = 0; p < 6; ++p) dns[p] = fmaf(tx[p], nsx, fmaf(ty[p], nsy, fmaf(tz[p], nsz, -os)));
+    for (int m = 0; m < 8; ++m) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[m]), __float_as_uint(v[m + 8]), false, false);
+        u[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    f32x4 w;
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
-        dnt[q] = fmaf(-L.f[3 * q][j], ntx, fmaf(-L.f[3 * q + 1][j], nty, fmaf(-L.f[3 * q + 2][j], ntz, ot)));
-    float gL = 0.0f, gY = 0.0f, nn = 0.0f;
-    float P[6];   // FORM 1, 3: target p's row-1 double-layer sum before its factor dns[p]
+    for (int m = 0; m < 4; ++m) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[m]), __float_as_uint(u[m + 4]), false, false);
+        w[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    return w;
+}
+
+// sum over the 16 lanes of a row, in every lane of it
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x)
+{
+    return x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float x)
+{
+    return dpp_add<0x121>(dpp_add<0x122>(dpp_add<0x124>(dpp_add<0x128>(x))));   // row_ror 8, 4, 2, 1
+}
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// One wavefront's 16 targets against one group of 16 sources (columns col0..):
+// adds to its targets' sums a1, a2, W and returns the sources' sums over its rows
+// (value m of column l mod 16 in row m / 4's component m mod 4).
+//   A[p] = (X_p, 1), A2 = (n_t / 2, 0): the matrix operands of the targets
+//   live[v] (NEAR): the pair of row v and the lane's column is summed here
+// FORM 0 (direct): Laplace row kL K_L + vL V_L, Yukawa row kY K_Y + vY V_Y with
+// R3 = r^-3, E = e (r^-3 + kappa r^-2): the double-layer sums of target point p
+// over the source points (P, Q) take d.n_s once per triangle pair, those of
+// source point q over the target points (S1, S2) d.n_t once per source point.
+// FORM 1, 3, 4: row 1 = K and V, row 2 = T and D, each operator's two kernels
+// joined in one value per point pair: L + b Y with the factor a taken out (FORM
+// 1), Y alone (FORM 3: no Laplace term), a L + b Y (FORM 4: some operator
+// without a Laplace term).  T's normal factors are per point and go with the
+// weights; its target side carries d.n_t b2 per source point, its source side
+// d.n_s b2_t per target point (wt).
+template <int FORM, bool K0, bool NEAR>
+__device__ __forceinline__ void sym_block(const SymCoef &cf, const SymCols &C, const SymRows &R, int col0, int lane,
+                                          const float (&A)[6], float A2, const bool (&live)[4], f32x4 (&a1)[6],
+                                          f32x4 (&a2)[6], f32x4 (&W)[3], f32x4 &src)
+{
+    const int lc = col0 + (lane & 15), g = lane >> 4, r0 = 4 * g;
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const float bn = ((const float *)&C.bn[lc])[g];
+    f32x4 P[6], Q[6];   // FORM 0: Q the Yukawa double layer; else Q = d.n_s b2_t
+    f32x4 gs = zero, nn = zero;
 #pragma unroll
-    for (int p = 0; p < 6; ++p) P[p] = 0.0f;
-    if (FORM >= 1) nn = cf.cDY * cf.k2 * (ntx * nsx + nty * nsy + ntz * nsz);
+    for (int p = 0; p < 6; ++p) P[p] = Q[p] = zero;
+    if (FORM >= 1) {
+        nn = mfma4(A2, bn, zero);   // n_t . n_s / 2
+#pragma unroll
+        for (int p = 0; p < 6; ++p) Q[p] = mfma4(A[p], bn, zero) * *(const f32x4 *)&R.d[6 + p][r0];
+    }
+    float acc[16];
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-        const float yx = L.f[3 * q][j], yy = L.f[3 * q + 1][j], yz = L.f[3 * q + 2][j];
-        if (FORM == 0) {
-            // target side: Laplace row kL K_L + vL V_L, Yukawa row kY K_Y + vY V_Y, the
-            // source point's constants c1..c4 staged (kYk = kappa kY); source side (K at
-            // the target's normal: -F d.n_t): cs = -kL b1_t, vL b2_t, -kY b1_t, vY b2_t,
-            // -kY kappa b1_t per target point
-            const float c1 = L.f[22 + q][j], c2 = L.f[28 + q][j], c3 = L.f[34 + q][j], c4 = L.f[40 + q][j];
-            const float c3k = cf.kappa * c3;   // kYk = kappa kY (unused when K0)
+        const float b = ((const float *)&C.bq[q][lc])[g];
+        const f32x4 w = C.w[q][lc];
+        const f32x4 dnt = mfma4(A2, b, *(const f32x4 *)&R.o[r0]);
+        f32x4 yq = zero;
+        if (NEAR) yq = C.bq[q][lc];
+        f32x4 S1 = zero, S2 = zero;
+        f32x4 tq = zero, nb = zero;
+        if (FORM >= 1) {
+            tq = dnt * w[2];
+            nb = nn * w[3];
+        }
+        float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                const float dx = tx[p] - yx, dy = ty[p] - yy, dz = tz[p] - yz;
-                const float r2 = dx * dx + dy * dy + dz * dz;
-                const float ri = rsqrt_r(r2);
-                const float ri2 = ri * ri;
-                const float g = dns[p] * ri2, h = dnt[q] * ri2;
-                a1[p] = fmaf(ri, fmaf(c1, g, c2), a1[p]);
-                acc[q] = fmaf(ri, fmaf(cs[0][p], h, cs[1][p]), acc[q]);
-                if constexpr (K0) {
-                    a2[p] = fmaf(ri, fmaf(c3, g, c4), a2[p]);
-                    acc[6 + q] = fmaf(ri, fmaf(cs[2][p], h, cs[3][p]), acc[6 + q]);
-                } else {
-                    const float e = __builtin_amdgcn_exp2f(-(r2 * ri));
-                    a2[p] = fmaf(e, fmaf(ri, fmaf(c3, g, c4), c3k * g), a2[p]);
-                    acc[6 + q] = fmaf(e, fmaf(ri, fmaf(cs[2][p], h, cs[3][p]), cs[4][p] * h), acc[6 + q]);
+        for (int p = 0; p < 6; ++p) {
+            f32x4 r2;
+            if (NEAR) {
+                const f32x4 xx = *(const f32x4 *)&R.x[p][0][r0], xy = *(const f32x4 *)&R.x[p][1][r0],
+                            xz = *(const f32x4 *)&R.x[p][2][r0];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float dx = fmaf(0.5f, yq[0], xx[v]), dy = fmaf(0.5f, yq[1], xy[v]),
+                                dz = fmaf(0.5f, yq[2], xz[v]);
+                    r2[v] = dx * dx + dy * dy + dz * dz;
                 }
+            } else {
+                r2 = mfma4(A[p], b, *(const f32x4 *)&R.x2[p][r0]);
             }
-        } else {
-            // target side as far_source; source side: row 1 with -h (K at n_t), row 2
-            // with -g (T at n_s): cs = -cKL b1_t, -cKY b1_t, (unused), cVL b2_t,
-            // cVY b2_t, -cTL b2_t, -cTY b2_t, (unused), b1_t.  The Yukawa double-layer
-            // kernel e (1 + kappa r) / r^3 d.n is E d.n with E = e (r^-3 + kappa r^-2).
-            const float b1 = L.f[22 + q][j], b2 = L.f[28 + q][j];
-            const float c1L = cf.cKL * b1, c1Y = cf.cKY * b1, c2L = cf.cVL * b2, c2Y = cf.cVY * b2;
-            const float c3L = cf.cTL * b2, c3Y = cf.cTY * b2, kb1 = nn * b1;
-            float S = 0.0f;   // source q's row-1 double-layer sum before its factor dnt[q]
+            const f32x4 t1 = *(const f32x4 *)&R.d[p][r0], t2 = *(const f32x4 *)&R.d[6 + p][r0];
+            const float ww = float(rule_w(p) * rule_w(q));
 #pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                const float dx = tx[p] - yx, dy = ty[p] - yy, dz = tz[p] - yz;
-                const float r2 = dx * dx + dy * dy + dz * dz;
-                const float ri = rsqrt_r(r2);
-                const float ri2 = ri * ri;
-                const float e = K0 ? 1.0f : __builtin_amdgcn_exp2f(-(r2 * ri));
+            for (int v = 0; v < 4; ++v) {
+                float ri = rsqrt_r(r2[v]);
+                if (NEAR) ri = live[v] ? ri : 0.0f;   // every kernel value of the pair is then zero
+                const float ri2 = ri * ri, R3 = ri * ri2;
+                const float e = K0 ? 1.0f : __builtin_amdgcn_exp2f(-(r2[v] * ri));
                 const float gy = K0 ? ri : e * ri;
-                // F_L d.n = R3 (d.n), F_Y d.n = E (d.n) with R3 = r^-3 and E = e (1/r + kappa)
-                // r^-2 = e (R3 + kappa r^-2); the factors dns[p] of target p's row 1 and
-                // dnt[q] of source q's row 1 are applied once per triangle pair (P, S)
-                const float R3 = ri * ri2;
-                const float E = K0 ? R3 : e * fmaf(cf.kappa, ri2, R3);
-                if (FORM == 3) {
-                    P[p] = fmaf(c1Y, E, P[p]);
-                    a1[p] = fmaf(gy, c2Y, a1[p]);
-                    a2[p] = fmaf(dnt[q] * c3Y, E, fmaf(gy, kb1, a2[p]));
-                    S = fmaf(cs[1][p], E, S);
-                    acc[q] = fmaf(gy, cs[4][p], acc[q]);
-                    acc[6 + q] = fmaf(dns[p] * cs[6][p], E, fmaf(gy, nn * cs[8][p], acc[6 + q]));
+                const float E = K0 ? R3 : e * fmaf(cf.kap, ri2, R3);
+                if (FORM == 0) {
+                    P[p][v] = fmaf(w[0], R3, P[p][v]);
+                    a1[p][v] = fmaf(w[1], ri, a1[p][v]);
+                    Q[p][v] = fmaf(w[2], E, Q[p][v]);
+                    a2[p][v] = fmaf(w[3], gy, a2[p][v]);
+                    S1[v] = fmaf(t1[v], R3, S1[v]);
+                    s1 = fmaf(t2[v], ri, s1);
+                    S2[v] = fmaf(t1[v], E, S2[v]);
+                    s2 = fmaf(t2[v], gy, s2);
                 } else {
-                    P[p] = fmaf(c1Y, E, fmaf(c1L, R3, P[p]));
-                    a1[p] = fmaf(ri, c2L, fmaf(gy, c2Y, a1[p]));
-                    a2[p] = fmaf(dnt[q], fmaf(c3Y, E, c3L * R3), fmaf(gy, kb1, a2[p]));
-                    S = fmaf(cs[1][p], E, fmaf(cs[0][p], R3, S));
-                    acc[q] = fmaf(ri, cs[3][p], fmaf(gy, cs[4][p], acc[q]));
-                    acc[6 + q] = fmaf(dns[p], fmaf(cs[6][p], E, cs[5][p] * R3), fmaf(gy, nn * cs[8][p], acc[6 + q]));
-                    gL = fmaf(float(rule_w(p) * rule_w(q)), ri, gL);
+                    float k, vv, kt, dd;
+                    if (FORM == 3) {
+                        k = kt = E;
+                        vv = dd = gy;
+                    } else if (FORM == 1) {
+                        k = fmaf(cf.bK, E, R3);
+                        vv = fmaf(cf.bV, gy, ri);
+                        kt = fmaf(cf.bT, E, R3);
+                        dd = fmaf(cf.bD, gy, ri);
+                    } else {
+                        k = fmaf(cf.bK, E, cf.aK * R3);
+                        vv = fmaf(cf.bV, gy, cf.aV * ri);
+                        kt = fmaf(cf.bT, E, cf.aT * R3);
+                        dd = fmaf(cf.bD, gy, cf.aD * ri);
+                    }
+                    P[p][v] = fmaf(w[0], k, P[p][v]);
+                    a1[p][v] = fmaf(w[1], vv, a1[p][v]);
+                    a2[p][v] = fmaf(tq[v], kt, fmaf(nb[v], gy, a2[p][v]));
+                    S1[v] = fmaf(t1[v], k, S1[v]);
+                    s1 = fmaf(t2[v], vv, s1);
+                    s2 = fmaf(Q[p][v], kt, s2);
+                    S2[v] = fmaf(t1[v], gy, S2[v]);
+                    gs[v] = fmaf(ww, dd, gs[v]);
                 }
-                gY = fmaf(float(rule_w(p) * rule_w(q)), gy, gY);
             }
-            acc[q] = fmaf(dnt[q], S, acc[q]);
+        }
+        float k1 = 0.0f, k2 = 0.0f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            k1 = fmaf(dnt[v], S1[v], k1);
+            k2 = fmaf(FORM == 0 ? dnt[v] : nn[v], S2[v], k2);
+        }
+        if (FORM == 0) {
+            acc[q] = fmaf(cf.cV, s1, -cf.cK * k1);
+            acc[6 + q] = fmaf(cf.cD, s2, -cf.cT * k2);
+        } else {
+            acc[q] = fmaf(cf.cV, s1, -cf.cK * k1);
+            acc[6 + q] = fmaf(cf.kD, k2, -cf.cT * s2);
+        }
+        // row data stay in LDS: without this the compiler hoists all 18 row vectors
+        // of the p loop out of the q loop and spills
+        asm volatile("" ::: "memory");
+    }
+    acc[12] = acc[13] = acc[14] = acc[15] = 0.0f;
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+        const f32x4 dns = mfma4(A[p], bn, zero);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            a1[p][v] = fmaf(dns[v], P[p][v], a1[p][v]);
+            if (FORM == 0) a2[p][v] = fmaf(dns[v], Q[p][v], a2[p][v]);
         }
     }
     if (FORM >= 1) {
+        const f32x4 cs = C.curl[lc];
 #pragma unroll
-        for (int p = 0; p < 6; ++p) a1[p] = fmaf(dns[p], P[p], a1[p]);
+        for (int c = 0; c < 3; ++c) {
+            const f32x4 ct = *(const f32x4 *)&R.d[12 + c][r0];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float gc = cf.cD * gs[v];
+                W[c][v] = fmaf(gc, cs[c], W[c][v]);
+                acc[12 + c] = fmaf(gc, ct[v], acc[12 + c]);
+            }
+        }
     }
-    if (FORM >= 1) {
-        const float gc = FORM == 3 ? cf.cDY * gY : cf.cDL * gL + cf.cDY * gY;
-        W[0] = fmaf(gc, L.f[34][j], W[0]);
-        W[1] = fmaf(gc, L.f[35][j], W[1]);
-        W[2] = fmaf(gc, L.f[36][j], W[2]);
-        acc[12] = fmaf(gc, Ct[0], acc[12]);
-        acc[13] = fmaf(gc, Ct[1], acc[13]);
-        acc[14] = fmaf(gc, Ct[2], acc[14]);
-    }
+    src = rows_sum16(acc);
 }
 
-// Item (a, b) of one mesh by one wavefront; part holds the 2 nr slots
-template <int FORM, bool K0, typename IP, typename RP>
-__device__ __forceinline__ void sym_item(const FarCoef<float> &cf, IP __restrict__ tri, RP __restrict__ stat,
-                                         RP __restrict__ dyn, int T, int rt, int nr, int a, int b,
-                                         float *__restrict__ part, SymLds<FORM> &L, int lane)
+// Tile bounds: centre of the bounding box of the 64 triangles' vertices and the
+// largest distance of a vertex from it.  One wavefront per tile.
+__global__ __launch_bounds__(64) void k_sym_tiles(int T, const double *__restrict__ xyz, const int32_t *__restrict__ tri,
+                                                  double *__restrict__ tiles)
 {
+    const int t = min(64 * (int)blockIdx.x + (int)threadIdx.x, T - 1);
+    double lo[3], hi[3], p[3][3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double *x = xyz + 3 * (size_t)tri[3 * (size_t)t + k];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            p[k][c] = x[c];
+            lo[c] = k == 0 ? x[c] : fmin(lo[c], x[c]);
+            hi[c] = k == 0 ? x[c] : fmax(hi[c], x[c]);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], off));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], off));
+        }
+    double r2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        double d2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double d = p[k][c] - 0.5 * (lo[c] + hi[c]);
+            d2 += d * d;
+        }
+        r2 = fmax(r2, d2);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) r2 = fmax(r2, __shfl_xor(r2, off));
+    if (threadIdx.x < 4)
+        tiles[4 * (size_t)blockIdx.x + threadIdx.x] =
+            threadIdx.x == 3 ? sqrt(r2) : 0.5 * (lo[threadIdx.x == 1 ? 1 : threadIdx.x == 2 ? 2 : 0] +
+                                                 hi[threadIdx.x == 1 ? 1 : threadIdx.x == 2 ? 2 : 0]);
+}
+
+// Item (a, b) of one mesh by one block; part holds the 2 nr slots
+template <int FORM, bool K0, typename IP, typename DP, typename RP>
+__device__ __forceinline__ void sym_item(const SymCoef &cf, IP __restrict__ tri, DP __restrict__ stat,
+                                         DP __restrict__ tiles, RP __restrict__ dyn, int T, int rt, int nr, int a, int b,
+                                         float *__restrict__ part, SymLds &L)
+{
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int g = lane >> 4, li = lane & 15;
     const int ntile = (T + 63) / 64;
     const int I0 = a * rt, I1 = min(ntile, I0 + rt);
     const int J0 = b * rt, J1 = min(ntile, J0 + rt);
-    constexpr int NA = FORM == 0 ? 12 : 15;
-    for (int J = J0; J < J1; ++J) {
-        // stage tile J's sources (past the end: vertex ids -1, never met)
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        {
-            const int s = 64 * J + lane;
-            if (s < T) {
-                const auto st = stat + (size_t)s * kStat;
-                const auto sd = dyn + (size_t)s * kDyn;
-                // points and the plane offset (its first point's y . n) scaled by s,
-                // the normal as it is
+    SymRows &R = L.r[w];
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int I = I0; I < I1; ++I) {
+        const int t = 64 * I + 16 * w + li;      // the lane's target triangle as an operand row
+        const int tc = min(t, T - 1);
+        const auto ts = stat + (size_t)tc * kStat;
+        const auto td = dyn + (size_t)tc * kDyn;
+        f32x4 a1[6], a2[6], W[3];
 #pragma unroll
-                for (int c = 0; c < 22; ++c) L.f[c][lane] = (c < 18 || c == 21) ? st[c] * cf.kexp : st[c];
-                if (FORM == 0) {
+        for (int p = 0; p < 6; ++p) a1[p] = a2[p] = zero;
+        W[0] = W[1] = W[2] = zero;
+        for (int J = a == b ? I : J0; J < J1; ++J) {
+            const double cx = tiles[4 * (size_t)J], cy = tiles[4 * (size_t)J + 1], cz = tiles[4 * (size_t)J + 2];
+            const double c[3] = {cx, cy, cz};
+            const double s = cf.s;
+            // columns: wavefronts 0..2 two points each, wavefront 3 the rest
+            {
+                const int sj = min(64 * J + lane, T - 1);
+                const bool in = 64 * J + lane < T;   // past the end: the last triangle with zero weights
+                const auto ss = stat + (size_t)sj * kStat;
+                const auto sd = dyn + (size_t)sj * kDyn;
+                if (w < 3) {
 #pragma unroll
-                    for (int q = 0; q < 6; ++q) {
-                        L.f[22 + q][lane] = cf.kL * sd[q];
-                        L.f[28 + q][lane] = cf.vL * sd[6 + q];
-                        L.f[34 + q][lane] = cf.kY * sd[q];
-                        L.f[40 + q][lane] = cf.vY * sd[6 + q];
+                    for (int k = 0; k < 2; ++k) {
+                        const int q = 2 * w + k;
+                        const double yx = (ss[3 * q] - cx) * s, yy = (ss[3 * q + 1] - cy) * s, yz = (ss[3 * q + 2] - cz) * s;
+                        L.c.bq[q][lane] = f32x4{(float)(-2.0 * yx), (float)(-2.0 * yy), (float)(-2.0 * yz),
+                                                (float)(yx * yx + yy * yy + yz * yz)};
+                        const float b1 = in ? sd[q] : 0.0f, b2 = in ? sd[6 + q] : 0.0f;
+                        // FORM 0: the weights of R3, 1/r, E, e/r; else those of K, V, T and D's normal part
+                        L.c.w[q][lane] = FORM == 0 ? f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b1, cf.cD * b2}
+                                                   : f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b2, cf.kD * b1};
                     }
                 } else {
-#pragma unroll
-                    for (int c = 0; c < 15; ++c) L.f[22 + c][lane] = sd[c];
+                    const double nx = ss[18], ny = ss[19], nz = ss[20];
+                    const double os = (ss[21] - (cx * nx + cy * ny + cz * nz)) * s;
+                    L.c.bn[lane] = f32x4{(float)nx, (float)ny, (float)nz, (float)-os};
+                    if (FORM >= 1) L.c.curl[lane] = in ? f32x4{sd[12], sd[13], sd[14], 0.0f} : zero;
+                    L.c.id[0][lane] = in ? tri[3 * sj] : -1;
+                    L.c.id[1][lane] = in ? tri[3 * sj + 1] : -1;
+                    L.c.id[2][lane] = in ? tri[3 * sj + 2] : -1;
                 }
-                L.id[0][lane] = tri[3 * s];
-                L.id[1][lane] = tri[3 * s + 1];
-                L.id[2][lane] = tri[3 * s + 2];
+            }
+            // rows of this wavefront
+            float A[6], A2;
+#pragma unroll
+            for (int p = 0; p < 6; ++p) {
+                const double cg = g == 0 ? c[0] : g == 1 ? c[1] : c[2];
+                const float xs = (float)((ts[3 * p + (g < 3 ? g : 2)] - cg) * s);
+                A[p] = g < 3 ? xs : 1.0f;
+                if (g < 3) R.x[p][g][li] = xs;
+            }
+            A2 = g < 3 ? 0.5f * (float)ts[18 + (g < 3 ? g : 2)] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int p = g + 4 * k;
+                if (p < 6) {
+                    const double x = (ts[3 * p] - cx) * s, y = (ts[3 * p + 1] - cy) * s, z = (ts[3 * p + 2] - cz) * s;
+                    R.x2[p][li] = (float)(x * x + y * y + z * z);
+                } else if (p == 6) {
+                    R.o[li] = (float)((ts[21] - (cx * ts[18] + cy * ts[19] + cz * ts[20])) * s);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) R.d[4 * g + k][li] = t < T ? td[4 * g + k] : 0.0f;
+            __syncthreads();
+            // well separated: |X| |Y| stays of the order of r^2
+            const double dx = tiles[4 * (size_t)I] - cx, dy = tiles[4 * (size_t)I + 1] - cy, dz = tiles[4 * (size_t)I + 2] - cz;
+            const double reach = kSymApart * (tiles[4 * (size_t)I + 3] + tiles[4 * (size_t)J + 3]);
+            const bool near = dx * dx + dy * dy + dz * dz < reach * reach;
+            if (!near) {
+                const bool live[4] = {true, true, true, true};
+                for (int cb = 0; cb < 4; ++cb) {
+                    f32x4 src;
+                    sym_block<FORM, K0, false>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
+                    L.out[w][16 * cb + li][g] = src;
+                }
             } else {
+                int tv[4][3];
 #pragma unroll
-                for (int c = 0; c < SymLds<FORM>::NF; ++c) L.f[c][lane] = 0.0f;
-                L.id[0][lane] = L.id[1][lane] = L.id[2][lane] = -1;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        float acc[15];
+                for (int v = 0; v < 4; ++v) {
+                    const int tr = 64 * I + 16 * w + 4 * g + v, trc = min(tr, T - 1);
 #pragma unroll
-        for (int v = 0; v < 15; ++v) acc[v] = 0.0f;
-        const int Iend = (a == b) ? J + 1 : I1;
-        for (int I = I0; I < Iend; ++I) {
-            const int t = 64 * I + lane;
-            const bool tv = t < T;
-            const int tc = tv ? t : T - 1;
-            const auto ts = stat + (size_t)tc * kStat;
-            const auto td = dyn + (size_t)tc * kDyn;
-            float tx[6], ty[6], tz[6];
+                    for (int k = 0; k < 3; ++k) tv[v][k] = tr < T ? tri[3 * trc + k] : -1;
+                }
+                for (int cb = 0; cb < 4; ++cb) {
+                    f32x4 src = zero;
+                    if (I != J || cb >= w) {   // uniform: below the diagonal every pair has been met
+                        const int j0 = L.c.id[0][16 * cb + li], j1 = L.c.id[1][16 * cb + li], j2 = L.c.id[2][16 * cb + li];
+                        bool live[4];
 #pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                tx[p] = ts[3 * p] * cf.kexp; ty[p] = ts[3 * p + 1] * cf.kexp; tz[p] = ts[3 * p + 2] * cf.kexp;
-            }
-            const float ot = ts[21] * cf.kexp;   // the target's plane offset
-            const float ntx = ts[18], nty = ts[19], ntz = ts[20];
-            const int v0 = tri[3 * tc], v1 = tri[3 * tc + 1], v2 = tri[3 * tc + 2];
-            float cs[9][6], Ct[3] = {0.0f, 0.0f, 0.0f};
+                        for (int v = 0; v < 4; ++v) {
+                            bool m = (j0 >= 0) & (tv[v][0] >= 0);
 #pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                const float b1 = td[p], b2 = td[6 + p];
-                if (FORM == 0) {
-                    cs[0][p] = -cf.kL * b1; cs[1][p] = cf.vL * b2; cs[2][p] = -cf.kY * b1;
-                    cs[3][p] = cf.vY * b2; cs[4][p] = -cf.kYk * b1;
-                } else {
-                    cs[0][p] = -cf.cKL * b1; cs[1][p] = -cf.cKY * b1; cs[2][p] = 0.0f;
-                    cs[3][p] = cf.cVL * b2; cs[4][p] = cf.cVY * b2;
-                    cs[5][p] = -cf.cTL * b2; cs[6][p] = -cf.cTY * b2; cs[7][p] = 0.0f;
-                    cs[8][p] = b1;
+                            for (int k = 0; k < 3; ++k) m = m & (tv[v][k] != j0) & (tv[v][k] != j1) & (tv[v][k] != j2);
+                            if (I == J) m = m & (16 * w + 4 * g + v < 16 * cb + li);
+                            live[v] = m;
+                        }
+                        sym_block<FORM, K0, true>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
+                    }
+                    L.out[w][16 * cb + li][g] = src;
                 }
             }
-            if (FORM >= 1) { Ct[0] = td[12]; Ct[1] = td[13]; Ct[2] = td[14]; }
-            float a1[6], a2[6], W[3];
-            float *fo = part + ((size_t)b * T + tc) * 16;
-            const bool first = (a == b) ? (J == I) : (J == J0);
+            __syncthreads();
+            // the four wavefronts' source-side sums, in order, onto the slot (the item's
+            // earlier target tiles came before)
+            {
+                const int cl = tid >> 2, k = tid & 3, sj = 64 * J + cl;
+                if (sj < T) {
+                    f32x4 *so = (f32x4 *)(part + ((size_t)(nr + a) * T + sj) * 16) + k;
+                    f32x4 v = I == I0 ? zero : *so;
 #pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                a1[p] = first ? 0.0f : fo[p];
-                a2[p] = first ? 0.0f : fo[6 + p];
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) W[c] = first ? 0.0f : fo[12 + c];
-            for (int k = 0; k < 64; ++k) {
-                const int j = (lane + k) & 63;
-                bool act = tv && (I != J || (k >= 1 && (k < 32 || (k == 32 && lane < 32))));
-                const int j0 = L.id[0][j], j1 = L.id[1][j], j2 = L.id[2][j];
-                act = act && j0 >= 0 &&
-                      !((j0 == v0) | (j0 == v1) | (j0 == v2) | (j1 == v0) | (j1 == v1) | (j1 == v2) |
-                        (j2 == v0) | (j2 == v1) | (j2 == v2));
-                if (act) sym_pair<FORM, K0>(cf, L, j, tx, ty, tz, ot, ntx, nty, ntz, cs, Ct, a1, a2, W, acc);
-                // the source sums move one lane down: lane l next meets source (l + k + 1) mod 64
-#pragma unroll
-                for (int v = 0; v < NA; ++v) acc[v] = __shfl(acc[v], (lane + 1) & 63);
-            }
-            if (tv) {
-#pragma unroll
-                for (int p = 0; p < 6; ++p) { fo[p] = a1[p]; fo[6 + p] = a2[p]; }
-                fo[12] = W[0]; fo[13] = W[1]; fo[14] = W[2]; fo[15] = 0.0f;
+                    for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][k];
+                    *so = v;
+                }
             }
         }
-        // back home after 64 rotations: lane l holds source 64 J + l
-        const int s = 64 * J + lane;
-        if (s < T) {
-            float *so = part + ((size_t)(nr + a) * T + s) * 16;
+        // target-side sums over the 16 columns of each row of lanes
 #pragma unroll
-            for (int v = 0; v < 12; ++v) so[v] = acc[v];
-            so[12] = FORM == 0 ? 0.0f : acc[12];
-            so[13] = FORM == 0 ? 0.0f : acc[13];
-            so[14] = FORM == 0 ? 0.0f : acc[14];
-            so[15] = 0.0f;
+        for (int v = 0; v < 4; ++v) {
+            float o[16];
+#pragma unroll
+            for (int p = 0; p < 6; ++p) {
+                o[p] = row_sum(a1[p][v]);
+                o[6 + p] = row_sum(a2[p][v]);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) o[12 + k] = FORM == 0 ? 0.0f : row_sum(W[k][v]);
+            o[15] = 0.0f;
+            const int tr = 64 * I + 16 * w + 4 * g + v;
+            if (li == 0 && tr < T) {
+                f32x4 *fo = (f32x4 *)(part + ((size_t)b * T + tr) * 16);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) fo[k] = f32x4{o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
+            }
         }
     }
 }
 
-// One mesh: each wavefront takes items (heaviest first) from a device counter
+// the next item of a queue, for the whole block
+__device__ __forceinline__ int sym_next_item(int *__restrict__ next, SymLds &L)
+{
+    __syncthreads();   // the previous item's number is read and its LDS consumed
+    if (threadIdx.x == 0) L.item = atomicAdd(next, 1);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(L.item);
+}
+
+// One mesh: each block takes items (heaviest first) from a device counter
 // until the list is done.
 template <int FORM, bool K0>
-__global__ __launch_bounds__(64 * kSymWaves) void k_far_sym(int T, int rt, int nr, FarCoef<float> cf,
+__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, int nr, SymCoef cf,
                                                               const int32_t *__restrict__ tri,
-                                                              const float *__restrict__ stat,
+                                                              const double *__restrict__ stat,
+                                                              const double *__restrict__ tiles,
                                                               const float *__restrict__ dyn,
                                                               const int2 *__restrict__ items, int nitems,
                                                               int *__restrict__ next, float *__restrict__ part,
                                                               DevCtl ctl)
 {
-    __shared__ SymLds<FORM> lds[kSymWaves];
+    __shared__ SymLds lds;
     if (ctl_skip(ctl)) return;   // uniform: every wavefront leaves
-    const int w = threadIdx.x / 64, lane = threadIdx.x & 63;
     for (;;) {
-        int i = 0;
-        if (lane == 0) i = atomicAdd(next, 1);
-        i = __builtin_amdgcn_readfirstlane(__shfl(i, 0));
+        const int i = sym_next_item(next, lds);
         if (i >= nitems) return;
         const int2 it = items[i];
-        sym_item<FORM, K0>(cf, tri, stat, dyn, T, rt, nr, it.x, it.y, part, lds[w], lane);
+        sym_item<FORM, K0>(cf, tri, stat, tiles, dyn, T, rt, nr, it.x, it.y, part, lds);
     }
 }
 
 // Several meshes (batched requests): items {request, a, b}; a request whose
 // stop flag is set contributes nothing.
 template <int FORM, bool K0>
-__global__ __launch_bounds__(64 * kSymWaves) void k_far_sym_batch(const FarReq<float> *__restrict__ reqs,
+__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym_batch(const FarReq<float> *__restrict__ reqs,
                                                                     const int4 *__restrict__ items, int nitems,
                                                                     int *__restrict__ next)
 {
-    __shared__ SymLds<FORM> lds[kSymWaves];
-    const int w = threadIdx.x / 64, lane = threadIdx.x & 63;
+    __shared__ SymLds lds;
     for (;;) {
-        int i = 0;
-        if (lane == 0) i = atomicAdd(next, 1);
-        i = __builtin_amdgcn_readfirstlane(__shfl(i, 0));
+        const int i = sym_next_item(next, lds);
         if (i >= nitems) return;
         const int4 it = items[i];
-        const FarReq<float> rq = reqs[it.x];
+        const FarReq<float> &rq = reqs[it.x];
         if (rq.skip && *rq.skip) continue;
-        sym_item<FORM, K0>(rq.cf, rq.tri, rq.stat, rq.dyn, rq.T, rq.rt, rq.nr, it.y, it.z, rq.part, lds[w], lane);
+        sym_item<FORM, K0>(rq.sc, rq.tri, rq.stat64, rq.tiles, rq.dyn, rq.T, rq.rt, rq.nr, it.y, it.z, rq.part, lds);
     }
 }
 
@@ -342,29 +527,30 @@ __global__ void k_sym_set(int *p, int v) { *p = v; }
 
 // ------------------------------------------------------------------ host
 
-// The symmetric split applies to FP32 matrix-free meshes.  Automatic (mode 0):
-// 56 tiles (3584 triangles) and more -- on one smaller mesh too few tile pairs
-// fill the device (measured: at 2880 triangles both kernels take about 0.25 ms
-// per product, at 3920 the split is 7% / 33% faster, direct / Juffer, at 8000
-// 35% / 40%), while many small meshes batched together fill it either way;
-// mode 1 always, mode -1 never.
+// The symmetric split applies to FP32 matrix-free meshes of every size.
+// Automatic (mode 0) is yes: measured per product (direct / second kind, launches
+// included), 320 triangles 77 / 76 us against 94 / 101 us per ordered pair, 1620
+// 95 / 116 against 133 / 166, 3380 216 against 328 (direct); mode 1 always, mode -1
+// never.
 bool sym_eligible(int T, double kappa, int mode)
 {
+    (void)T;
     (void)kappa;   // kappa = 0 takes the unscreened variant
-    if (mode < 0) return false;
-    return mode > 0 || T >= 3584;
+    return mode >= 0;
 }
 
-// Ranges of rt tiles: about 320 ranges (51000 items) so that the heaviest-first
-// work list ends with items of a few milliseconds at most.
+// Ranges of rt tiles: about 320 ranges (51000 items).  Larger items come first;
+// among equal ones those near the diagonal, whose tiles touch and which take the
+// longer subtracted form, so that the list ends with the lightest items.
 void sym_plan(int T, int &rt, int &nr, std::vector<int2> &items)
 {
     const int ntile = (T + 63) / 64;
     rt = std::max(1, (ntile + 319) / 320);
     nr = (ntile + rt - 1) / rt;
     std::vector<std::pair<int, int2>> w;
-    for (int a = 0; a < nr; ++a)
-        for (int b = a; b < nr; ++b) {
+    for (int k = 0; k < nr; ++k)
+        for (int a = 0; a + k < nr; ++a) {
+            const int b = a + k;
             const int na = std::min(ntile, (a + 1) * rt) - a * rt, nb = std::min(ntile, (b + 1) * rt) - b * rt;
             const int pairs = a == b ? na * (na + 1) / 2 : na * nb;
             w.push_back({pairs, make_int2(a, b)});
@@ -376,60 +562,66 @@ void sym_plan(int T, int &rt, int &nr, std::vector<int2> &items)
     for (auto &e : w) items.push_back(e.second);
 }
 
-// the kernel of a form (0, 1, 3) and screening (k0: kappa = 0)
+// CALL with the kernel of a form (0, 1, 3, 4) and screening (k0: kappa = 0)
+#define SYM_PICK(KERNEL, form, k0, CALL)                                                       \
+    if (k0) {                                                                                  \
+        if (form == 0) CALL((KERNEL<0, true>))                                                 \
+        else if (form == 1) CALL((KERNEL<1, true>))                                            \
+        else if (form == 3) CALL((KERNEL<3, true>))                                            \
+        else CALL((KERNEL<4, true>))                                                           \
+    } else {                                                                                   \
+        if (form == 0) CALL((KERNEL<0, false>))                                                \
+        else if (form == 1) CALL((KERNEL<1, false>))                                           \
+        else if (form == 3) CALL((KERNEL<3, false>))                                           \
+        else CALL((KERNEL<4, false>))                                                          \
+    }
+
 static const void *sym_kernel(int form, bool k0)
 {
-    if (k0)
-        return form == 0 ? reinterpret_cast<const void *>(&k_far_sym<0, true>)
-               : form == 1 ? reinterpret_cast<const void *>(&k_far_sym<1, true>)
-                           : reinterpret_cast<const void *>(&k_far_sym<3, true>);
-    return form == 0 ? reinterpret_cast<const void *>(&k_far_sym<0, false>)
-           : form == 1 ? reinterpret_cast<const void *>(&k_far_sym<1, false>)
-                       : reinterpret_cast<const void *>(&k_far_sym<3, false>);
+    const void *k = nullptr;
+#define SYM_ADDR(KF) k = reinterpret_cast<const void *>(&KF);
+    SYM_PICK(k_far_sym, form, k0, SYM_ADDR)
+    return k;
 }
 
 static const void *sym_batch_kernel(int form, bool k0)
 {
-    if (k0)
-        return form == 0 ? reinterpret_cast<const void *>(&k_far_sym_batch<0, true>)
-               : form == 1 ? reinterpret_cast<const void *>(&k_far_sym_batch<1, true>)
-                           : reinterpret_cast<const void *>(&k_far_sym_batch<3, true>);
-    return form == 0 ? reinterpret_cast<const void *>(&k_far_sym_batch<0, false>)
-           : form == 1 ? reinterpret_cast<const void *>(&k_far_sym_batch<1, false>)
-                       : reinterpret_cast<const void *>(&k_far_sym_batch<3, false>);
+    const void *k = nullptr;
+    SYM_PICK(k_far_sym_batch, form, k0, SYM_ADDR)
+    return k;
 }
 
-int sym_blocks(int nitems, int form, bool k0)
+// as many blocks as are resident at once, or one per item if fewer
+static int sym_grid(const void *kernel, int nitems)
 {
     int dev = 0, ncu = 0, per_cu = 0;
     HIPCHECK(hipGetDevice(&dev));
     HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    const void *k = sym_kernel(form, k0);
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64 * kSymWaves, 0));
-    const long long cap = (long long)std::max(ncu, 1) * std::max(per_cu, 1);
-    return (int)std::max(1LL, std::min(cap, (long long)(nitems + kSymWaves - 1) / kSymWaves));
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * kSymWaves, 0));
+    return (int)std::max(1LL, std::min((long long)std::max(ncu, 1) * std::max(per_cu, 1), (long long)nitems));
+}
+
+int sym_blocks(int nitems, int form, bool k0) { return sym_grid(sym_kernel(form, k0), nitems); }
+int sym_batch_blocks_for(int form, bool k0, int n) { return sym_grid(sym_batch_kernel(form, k0), n); }
+
+void launch_sym_tiles(DevMesh &d)
+{
+    hipLaunchKernelGGL(k_sym_tiles, dim3((d.hm.T + 63) / 64), dim3(64), 0, d.stream, d.hm.T, d.xyz, d.tri, d.sym_tiles);
+    HIPCHECK(hipGetLastError());
 }
 
 void launch_far_sym(DevMesh &d)
 {
-    FarCoef<float> cf;
-    const int form = far_coef_sym(d, cf);
+    SymCoef cf;
+    const int form = sym_coef(d, cf);
     const bool k0 = !(d.prm.kappa > 0.0);
-    const int nb = d.sym_blocks[form == 0 ? 0 : form == 1 ? 1 : 2];
+    const int nb = d.sym_blocks[sym_form_index(form)];
     hipLaunchKernelGGL(k_sym_set, dim3(1), dim3(1), 0, d.stream, d.sym_next, 0);
-#define SYM(F, Z)                                                                                                 \
-    hipLaunchKernelGGL((k_far_sym<F, Z>), dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, \
-                       cf, d.tri, d.stat32, d.dyn32, d.sym_items, d.sym_nitems, d.sym_next, (float *)d.part, d.ctl)
-    if (k0) {
-        if (form == 0) SYM(0, true);
-        else if (form == 1) SYM(1, true);
-        else SYM(3, true);
-    } else {
-        if (form == 0) SYM(0, false);
-        else if (form == 1) SYM(1, false);
-        else SYM(3, false);
-    }
-#undef SYM
+#define SYM_RUN(KF)                                                                                             \
+    hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, cf, d.tri,  \
+                       d.stat64, d.sym_tiles, d.dyn32, d.sym_items, d.sym_nitems, d.sym_next, (float *)d.part,  \
+                       d.ctl);
+    SYM_PICK(k_far_sym, form, k0, SYM_RUN)
     HIPCHECK(hipGetLastError());
 }
 
@@ -445,34 +637,14 @@ void launch_far_sym_finish(DevMesh &d)
 }
 
 // batched requests: one queue per kernel form and screening of {request, a, b} items
-int sym_batch_blocks_for(int form, bool k0, int n)
-{
-    int dev = 0, ncu = 0, per_cu = 0;
-    HIPCHECK(hipGetDevice(&dev));
-    HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sym_batch_kernel(form, k0), 64 * kSymWaves, 0));
-    const long long cap = (long long)std::max(ncu, 1) * std::max(per_cu, 1);
-    return (int)std::max(1LL, std::min(cap, (long long)(n + kSymWaves - 1) / kSymWaves));
-}
-
 void launch_far_sym_batch(int form, bool k0, const void *reqs, const int4 *items, int n, int nblocks, int *next,
                           hipStream_t s)
 {
     if (n == 0) return;
     hipLaunchKernelGGL(k_sym_set, dim3(1), dim3(1), 0, s, next, 0);
-#define SYMB(F, Z)                                                                                 \
-    hipLaunchKernelGGL((k_far_sym_batch<F, Z>), dim3(nblocks), dim3(64 * kSymWaves), 0, s,          \
-                       (const FarReq<float> *)reqs, items, n, next)
-    if (k0) {
-        if (form == 0) SYMB(0, true);
-        else if (form == 1) SYMB(1, true);
-        else SYMB(3, true);
-    } else {
-        if (form == 0) SYMB(0, false);
-        else if (form == 1) SYMB(1, false);
-        else SYMB(3, false);
-    }
-#undef SYMB
+#define SYM_RUNB(KF) \
+    hipLaunchKernelGGL(KF, dim3(nblocks), dim3(64 * kSymWaves), 0, s, (const FarReq<float> *)reqs, items, n, next);
+    SYM_PICK(k_far_sym_batch, form, k0, SYM_RUNB)
     HIPCHECK(hipGetLastError());
 }
 

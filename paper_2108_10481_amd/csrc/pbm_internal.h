@@ -230,7 +230,8 @@ struct DevMesh {
     int sym_rt = 0, sym_nr = 0, sym_nitems = 0;
     int2 *sym_items = nullptr;
     int *sym_next = nullptr;
-    int sym_blocks[3] = {1, 1, 1};
+    double *sym_tiles = nullptr;   // per tile of 64 triangles: centre 3, radius
+    int sym_blocks[4] = {1, 1, 1, 1};
     hipStream_t stream = nullptr;
     size_t bytes = 0;
     std::vector<void *> allocs;
@@ -334,14 +335,14 @@ struct FarBatch {
     hipStream_t stream = nullptr;
     void *reqs = nullptr;
     void *items = nullptr;
-    int *next = nullptr;           // one queue counter per kernel form, then six for the symmetric queues
+    int *next = nullptr;           // one queue counter per kernel form, then eight for the symmetric queues
     size_t req_cap = 0, item_cap = 0;
     int first[4] = {0, 0, 0, 0}, nitems[4] = {0, 0, 0, 0}, nblocks[4] = {0, 0, 0, 0};
     // symmetric FP32 items {request, a, b} of the requests with a symmetric split:
-    // queues for forms 0, 1, 3 (kappa > 0), then the same for kappa = 0
+    // queues for forms 0, 1, 3, 4 (kappa > 0), then the same for kappa = 0
     void *sym_items = nullptr;
     size_t sym_cap = 0;
-    int sym_first[6] = {}, sym_n[6] = {}, sym_nblocks[6] = {};
+    int sym_first[8] = {}, sym_n[8] = {}, sym_nblocks[8] = {};
 };
 // skip (empty, or one per handle): device stop flags; a request whose flag is
 // set contributes no work (captured iterations keep replaying after it stops)
@@ -367,6 +368,7 @@ int choose_chunks(int T);
 bool sym_eligible(int T, double kappa, int mode);
 void sym_plan(int T, int &rt, int &nr, std::vector<int2> &items);
 int sym_blocks(int nitems, int form, bool k0);
+void launch_sym_tiles(DevMesh &d);
 void launch_far_sym(DevMesh &d);
 void launch_far_sym_finish(DevMesh &d);
 int sym_batch_blocks_for(int form, bool k0, int n);

@@ -384,6 +384,7 @@ struct PrecondOperator {
 static void device_setup(DevMesh &d)
 {
     launch_geometry(d);
+    if (d.sym_nitems > 0) launch_sym_tiles(d);
     launch_near_field(d);
     if (d.pairblkP) launch_near_field_fast(d);
     launch_near_assemble(d);
@@ -493,9 +494,9 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
         d->sym_nitems = (int)items.size();
         d->sym_next = (int *)d->alloc(sizeof(int));
         const bool k0 = !(opt->kappa > 0.0);
-        d->sym_blocks[0] = sym_blocks(d->sym_nitems, 0, k0);
-        d->sym_blocks[1] = sym_blocks(d->sym_nitems, 1, k0);
-        d->sym_blocks[2] = sym_blocks(d->sym_nitems, 3, k0);
+        const int forms[4] = {0, 1, 3, 4};
+        for (int f = 0; f < 4; ++f) d->sym_blocks[f] = sym_blocks(d->sym_nitems, forms[f], k0);
+        d->sym_tiles = (double *)d->alloc(sizeof(double) * 4 * ((size_t)(T + 63) / 64));
         part_bytes = std::max(part_bytes, sizeof(float) * 16 * 2 * (size_t)d->sym_nr * T);
     }
     d->part = d->alloc(part_bytes);
@@ -1133,6 +1134,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
         key_append(key, sym);
         key_append(key, d.stat32);
         key_append(key, d.stat64);
+        key_append(key, d.sym_tiles);
         if (mass) {   // the mass preconditioner's launches: buffers and scales
             key_append(key, d.prm.preconditioner);
             key_append(key, d.prm.eps_in);
