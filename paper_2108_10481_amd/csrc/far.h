@@ -38,14 +38,16 @@ struct FarCoef {
     R cKL, cKY, cVL, cVY, cTL, cTY, cDL, cDY;
 };
 
-// Coefficients of the symmetric FP32 kernel (k_far_sym.hip), set by sym_coef
+// Coefficients of the symmetric kernels (k_far_sym.hip, k_far_sym64.hip), set
+// by sym_coef
+template <typename R>
 struct SymCoef {
-    float s;                   // coordinate scale (kappa log2 e; 1 for kappa = 0)
-    float kap;                 // kappa / s
-    float cK, cV, cT, cD;      // factors of the four sums (FORM 0: kL, vL, kY, vY)
-    float kD;                  // 2 kappa^2 times the Yukawa coefficient of D
-    float aK, aV, aT, aD;      // FORM 4: Laplace coefficients inside the values
-    float bK, bV, bT, bD;      // FORM 1: Yukawa over Laplace; FORM 4: Yukawa coefficients
+    R s;                   // coordinate scale (kappa log2 e; 1 for kappa = 0)
+    R kap;                 // kappa / s
+    R cK, cV, cT, cD;      // factors of the four sums (FORM 0: kL, vL, kY, vY)
+    R kD;                  // kappa^2 times the Yukawa coefficient of D
+    R aK, aV, aT, aD;      // FORM 4: Laplace coefficients inside the values
+    R bK, bV, bT, bD;      // FORM 1: Yukawa over Laplace; FORM 4: Yukawa coefficients
 };
 
 // one request of the batched far field: its mesh data, partial-sum buffer and
@@ -59,8 +61,8 @@ struct FarReq {
     const int *skip;   // when set and nonzero (the request's GMRES stopped), its items do nothing
     FarCoef<R> cf;
     int T, chunk;
-    int rt, nr;        // symmetric split (k_far_sym.hip): tiles per range, ranges; 0 if unused
-    SymCoef sc;        // and its coefficients, FP64 records and tile bounds
+    int rt, nr, nz;    // symmetric split: tiles per range, ranges, parts of an item; 0 if unused
+    SymCoef<R> sc;        // and its coefficients, FP64 records and tile bounds
     const double *stat64, *tiles;
 };
 
@@ -208,22 +210,29 @@ __device__ __forceinline__ void finish_group(int t, int l, bool ok, int T, int S
     far_project(t, family, swap, geo, pot, triout);
 }
 
-// symmetric split (ranges of rt tiles of 64 triangles, nr ranges): target t's
-// nr + 1 slots, the target-side slots of the source ranges b >= c and the
-// source-side slots of the target ranges a <= c (c its own range)
-__device__ __forceinline__ void sym_finish_group(int t, int l, bool ok, int T, int rt, int nr, int family, int swap,
-                                                 const double *__restrict__ geo, const float *__restrict__ part,
+// tile record of the symmetric split: centre 3, radius, largest distance of a
+// quadrature point of one of its triangles from that triangle's centroid
+constexpr int kTileRec = 5;
+constexpr int kSymTile = 64;   // triangles per tile of the symmetric split
+
+// symmetric split (ranges of rt tiles, nr ranges, nz parts of each item): target
+// t's nr + 1 slots per part z, the target-side slots z nr + b of the source ranges
+// b >= c and the source-side slots (nz + z) nr + a of the target ranges a <= c (c
+// its own range)
+template <typename R>
+__device__ __forceinline__ void sym_finish_group(int t, int l, bool ok, int T, int rt, int nr, int nz, int family,
+                                                 int swap, const double *__restrict__ geo, const R *__restrict__ part,
                                                  double *__restrict__ triout)
 {
     double pot[15];
 #pragma unroll
     for (int v = 0; v < 15; ++v) pot[v] = 0.0;
     if (ok) {
-        const int c = (t / 64) / rt;
-        const int nslot = (nr - c) + (c + 1);
-        for (int k = l; k < nslot; k += kFinishLanes) {
-            const int slot = k < nr - c ? c + k : nr + (k - (nr - c));
-            const float *o = part + ((size_t)slot * T + t) * 16;
+        const int c = (t / kSymTile) / rt;
+        for (int k = l; k < (nr + 1) * nz; k += kFinishLanes) {
+            const int z = k / (nr + 1), i = k - z * (nr + 1);
+            const int slot = i < nr - c ? z * nr + c + i : (nz + z) * nr + i - (nr - c);
+            const R *o = part + ((size_t)slot * T + t) * 16;
 #pragma unroll
             for (int v = 0; v < 15; ++v) pot[v] += (double)o[v];
         }
@@ -260,7 +269,7 @@ inline int far_coef(const DevMesh &d, FarCoef<R> &cf)
     return yukawa_only(f) ? 3 : 1;
 }
 
-// Coefficients of the symmetric kernel (k_far_sym.hip), whose coordinates are
+// Coefficients of the symmetric kernels, whose coordinates are
 // scaled by s = kappa log2(e) (kappa > 0): with x' = s x, 1/r = s / r', the
 // normal-derivative factors (d.n)/r^3 = s^2 (d'.n)/r'^3 and exp(-kappa r) =
 // exp2(-r'), so the K- and T-type coefficients take s^2, the V- and D-type ones
@@ -268,37 +277,53 @@ inline int far_coef(const DevMesh &d, FarCoef<R> &cf)
 // coefficients as they are, kappa 0).  Returns the kernel FORM: 0 (direct), 1
 // (every operator has a Laplace term: its coefficient is taken out), 3 (none
 // has), 4 (some have: a combined field with one zero constant).
-inline int sym_coef(const DevMesh &d, SymCoef &sc)
+template <typename R>
+inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
 {
     FarCoef<double> c;
     int form = far_coef(d, c);
     const double s = d.prm.kappa > 0.0 ? d.prm.kappa * 1.4426950408889634 : 1.0, s2 = s * s;
-    sc = SymCoef{};
-    sc.s = (float)s;
-    sc.kap = (float)(d.prm.kappa / s);
-    sc.kD = (float)(2.0 * c.k2 * c.cDY * s);
+    sc = SymCoef<R>{};
+    sc.s = (R)s;
+    sc.kap = (R)(d.prm.kappa / s);
+    sc.kD = (R)(c.k2 * c.cDY * s);
     if (form == 0) {
-        sc.cK = (float)(c.kL * s2); sc.cV = (float)(c.vL * s);
-        sc.cT = (float)(c.kY * s2); sc.cD = (float)(c.vY * s);
+        sc.cK = (R)(c.kL * s2); sc.cV = (R)(c.vL * s);
+        sc.cT = (R)(c.kY * s2); sc.cD = (R)(c.vY * s);
         return 0;
     }
     if (form == 1 && !(c.cKL != 0.0 && c.cVL != 0.0 && c.cTL != 0.0 && c.cDL != 0.0)) form = 4;
     if (form == 1) {
-        sc.cK = (float)(c.cKL * s2); sc.cV = (float)(c.cVL * s);
-        sc.cT = (float)(c.cTL * s2); sc.cD = (float)(c.cDL * s);
-        sc.bK = (float)(c.cKY / c.cKL); sc.bV = (float)(c.cVY / c.cVL);
-        sc.bT = (float)(c.cTY / c.cTL); sc.bD = (float)(c.cDY / c.cDL);
+        sc.cK = (R)(c.cKL * s2); sc.cV = (R)(c.cVL * s);
+        sc.cT = (R)(c.cTL * s2); sc.cD = (R)(c.cDL * s);
+        sc.bK = (R)(c.cKY / c.cKL); sc.bV = (R)(c.cVY / c.cVL);
+        sc.bT = (R)(c.cTY / c.cTL); sc.bD = (R)(c.cDY / c.cDL);
     } else if (form == 3) {
-        sc.cK = (float)(c.cKY * s2); sc.cV = (float)(c.cVY * s);
-        sc.cT = (float)(c.cTY * s2); sc.cD = (float)(c.cDY * s);
+        sc.cK = (R)(c.cKY * s2); sc.cV = (R)(c.cVY * s);
+        sc.cT = (R)(c.cTY * s2); sc.cD = (R)(c.cDY * s);
     } else {
-        sc.cK = sc.cT = (float)s2;
-        sc.cV = sc.cD = (float)s;
-        sc.aK = (float)c.cKL; sc.aV = (float)c.cVL; sc.aT = (float)c.cTL; sc.aD = (float)c.cDL;
-        sc.bK = (float)c.cKY; sc.bV = (float)c.cVY; sc.bT = (float)c.cTY; sc.bD = (float)c.cDY;
+        sc.cK = sc.cT = (R)s2;
+        sc.cV = sc.cD = (R)s;
+        sc.aK = (R)c.cKL; sc.aV = (R)c.cVL; sc.aT = (R)c.cTL; sc.aD = (R)c.cDL;
+        sc.bK = (R)c.cKY; sc.bV = (R)c.cVY; sc.bT = (R)c.cTY; sc.bD = (R)c.cDY;
     }
     return form;
 }
+
+// CALL with the kernel of a form (0, 1, 3, 4) and screening (k0: kappa = 0)
+#define SYM_PICK(KERNEL, form, k0, CALL)                                                       \
+    if (k0) {                                                                                  \
+        if (form == 0) CALL((KERNEL<0, true>))                                                 \
+        else if (form == 1) CALL((KERNEL<1, true>))                                            \
+        else if (form == 3) CALL((KERNEL<3, true>))                                            \
+        else CALL((KERNEL<4, true>))                                                           \
+    } else {                                                                                   \
+        if (form == 0) CALL((KERNEL<0, false>))                                                \
+        else if (form == 1) CALL((KERNEL<1, false>))                                           \
+        else if (form == 3) CALL((KERNEL<3, false>))                                           \
+        else CALL((KERNEL<4, false>))                                                          \
+    }
+
 constexpr int kSymForms = 4;
 constexpr int kSymFormOf[kSymForms] = {0, 1, 3, 4};
 inline int sym_form_index(int form) { return form == 0 ? 0 : form == 1 ? 1 : form == 3 ? 2 : 3; }

@@ -395,8 +395,8 @@ __global__ __launch_bounds__(256) void k_bfinish(int NR, const TailReq *__restri
     if (ctl_skip(q.ctl)) return;   // uniform: the block belongs to one solve
     const int t = (int)(((blockIdx.x - boff[r]) * (size_t)blockDim.x + threadIdx.x) / kFinishLanes);
     const int l = threadIdx.x % kFinishLanes;
-    if (sizeof(R) == 4 && q.nr > 0)
-        sym_finish_group(t, l, t < q.T, q.T, q.rt, q.nr, q.family, q.swap, q.geo, (const float *)q.part, q.triout);
+    if (q.nr > 0)
+        sym_finish_group<R>(t, l, t < q.T, q.T, q.rt, q.nr, q.nz, q.family, q.swap, q.geo, (const R *)q.part, q.triout);
     else
         finish_group<R>(t, l, t < q.T, q.T, q.S, q.family, q.swap, q.geo, (const R *)q.part, q.triout);
 }
@@ -455,8 +455,9 @@ int choose_chunks(int T)
 template <typename R>
 static void far_launch(DevMesh &d, const R *stat, const R *dyn)
 {
-    if (sizeof(R) == 4 && d.sym_nitems > 0) {
-        launch_far_sym(d);   // FP32, every unordered pair once (k_far_sym.hip)
+    if (d.sym_nitems > 0) {   // every unordered pair once
+        if (sizeof(R) == 4) launch_far_sym(d);
+        else launch_far_sym64(d);
         return;
     }
     const int T = d.hm.T, S = d.S;
@@ -529,23 +530,22 @@ static void batch_plan(const std::vector<DevMesh *> &ds, const std::vector<int> 
         rq.skip = skip.empty() ? nullptr : skip[r];
         rq.T = T;
         rq.chunk = chunk;
-        rq.rt = rq.nr = 0;
-        if (sizeof(R) == 4 && d.sym_nitems > 0) {
+        rq.rt = rq.nr = rq.nz = 0;
+        if (d.sym_nitems > 0) {
             // symmetric split: the request's range pairs, in its own (heaviest first)
             // order, with the split's scaled coefficients
             const int sform = sym_coef(d, rq.sc);
             rq.stat64 = d.stat64;
             rq.tiles = d.sym_tiles;
-            rq.rt = d.sym_rt;
-            rq.nr = d.sym_nr;
-            std::vector<int2> its;
-            int rt = 0, nr = 0;
-            sym_plan(T, rt, nr, its);
+            std::vector<int4> its;
+            sym_plan(T, sizeof(R) == 4, r, rq.rt, rq.nr, rq.nz, its);
+            const int rt = rq.rt;
             const int sf = sym_form_index(sform) + (d.prm.kappa > 0.0 ? 0 : kSymForms);
-            for (const int2 &e : its) {
-                const int na = std::min((T + 63) / 64, (e.x + 1) * rt) - e.x * rt;
-                const int nb = std::min((T + 63) / 64, (e.y + 1) * rt) - e.y * rt;
-                sq[sf].push_back({e.x == e.y ? na * (na + 1) / 2 : na * nb, make_int4(r, e.x, e.y, 0)});
+            const int ntile = (T + kSymTile - 1) / kSymTile;
+            for (const int4 &e : its) {   // weighed by its tile pairs in units of a sixteenth
+                const int na = std::min(ntile, (e.y + 1) * rt) - e.y * rt;
+                const int nb = std::min(ntile, (e.z + 1) * rt) - e.z * rt;
+                sq[sf].push_back({(e.y == e.z ? na * (na + 1) / 2 : na * nb) * (16 / rq.nz), e});
             }
             continue;
         }
@@ -569,7 +569,7 @@ static void batch_plan(const std::vector<DevMesh *> &ds, const std::vector<int> 
         fb.sym_first[f] = (int)sitems.size();
         for (auto &e : sq[f]) sitems.push_back(e.second);
         fb.sym_n[f] = (int)sq[f].size();
-        fb.sym_nblocks[f] = fb.sym_n[f] ? sym_batch_blocks_for(kSymFormOf[f % kSymForms], f >= kSymForms, fb.sym_n[f]) : 0;
+        fb.sym_nblocks[f] = fb.sym_n[f] ? sym_batch_blocks_for(sizeof(R) == 4, kSymFormOf[f % kSymForms], f >= kSymForms, fb.sym_n[f]) : 0;
     }
     const size_t sb = sizeof(int4) * std::max<size_t>(sitems.size(), 1);
     if (sb > fb.sym_cap) {
@@ -631,6 +631,10 @@ void launch_far_batch(FarBatch &fb, bool fp32)
                                  fb.sym_n[f], fb.sym_nblocks[f], fb.next + 4 + f, fb.stream);
     } else {
         batch_launch<double, 0>(fb); batch_launch<double, 1>(fb); batch_launch<double, 3>(fb);
+        for (int f = 0; f < 2 * kSymForms; ++f)
+            launch_far_sym64_batch(kSymFormOf[f % kSymForms], f >= kSymForms, fb.reqs,
+                                   (const int4 *)fb.sym_items + fb.sym_first[f], fb.sym_n[f], fb.sym_nblocks[f],
+                                   fb.next + 4 + f, fb.stream);
     }
 }
 
@@ -674,7 +678,7 @@ void launch_far_centroid(DevMesh &d, bool fp32)
 
 void launch_far_finish(DevMesh &d, bool fp32)
 {
-    if (fp32 && d.sym_nitems > 0 && d.far_rule == 0 && !d.tree) {
+    if (d.sym_nitems > 0 && d.far_rule == 0 && !d.tree) {
         launch_far_sym_finish(d);   // the symmetric far field's slots
         return;
     }

@@ -133,7 +133,7 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
 // weights; its target side carries d.n_t b2 per source point, its source side
 // d.n_s b2_t per target point (wt).
 template <int FORM, bool K0, bool NEAR>
-__device__ __forceinline__ void sym_block(const SymCoef &cf, const SymCols &C, const SymRows &R, int col0, int lane,
+__device__ __forceinline__ void sym_block(const SymCoef<float> &cf, const SymCols &C, const SymRows &R, int col0, int lane,
                                           const float (&A)[6], float A2, const bool (&live)[4], f32x4 (&a1)[6],
                                           f32x4 (&a2)[6], f32x4 (&W)[3], f32x4 &src)
 {
@@ -145,7 +145,7 @@ __device__ __forceinline__ void sym_block(const SymCoef &cf, const SymCols &C, c
 #pragma unroll
     for (int p = 0; p < 6; ++p) P[p] = Q[p] = zero;
     if (FORM >= 1) {
-        nn = mfma4(A2, bn, zero);   // n_t . n_s / 2
+        nn = 2.0f * mfma4(A2, bn, zero);   // n_t . n_s
 #pragma unroll
         for (int p = 0; p < 6; ++p) Q[p] = mfma4(A[p], bn, zero) * *(const f32x4 *)&R.d[6 + p][r0];
     }
@@ -268,12 +268,13 @@ __device__ __forceinline__ void sym_block(const SymCoef &cf, const SymCols &C, c
     src = rows_sum16(acc);
 }
 
-// Tile bounds: centre of the bounding box of the 64 triangles' vertices and the
-// largest distance of a vertex from it.  One wavefront per tile.
+// Tile records (kTileRec): centre of the bounding box of the tile's (at most 64)
+// triangles' vertices, the largest distance of a vertex from it and of a
+// quadrature point from its triangle's centroid.  One wavefront per tile.
 __global__ __launch_bounds__(64) void k_sym_tiles(int T, const double *__restrict__ xyz, const int32_t *__restrict__ tri,
                                                   double *__restrict__ tiles)
 {
-    const int t = min(64 * (int)blockIdx.x + (int)threadIdx.x, T - 1);
+    const int t = min(kSymTile * (int)blockIdx.x + (int)threadIdx.x, T - 1);
     double lo[3], hi[3], p[3][3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -292,28 +293,38 @@ __global__ __launch_bounds__(64) void k_sym_tiles(int T, const double *__restric
             lo[c] = fmin(lo[c], __shfl_xor(lo[c], off));
             hi[c] = fmax(hi[c], __shfl_xor(hi[c], off));
         }
-    double r2 = 0.0;
+    double r2 = 0.0, h2 = 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        double d2 = 0.0;
+        double d2 = 0.0, e2 = 0.0;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const double d = p[k][c] - 0.5 * (lo[c] + hi[c]);
+            const double d = p[k][c] - 0.5 * (lo[c] + hi[c]), e = p[k][c] - (p[0][c] + p[1][c] + p[2][c]) / 3.0;
             d2 += d * d;
+            e2 += e * e;
         }
         r2 = fmax(r2, d2);
+        h2 = fmax(h2, e2);
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) r2 = fmax(r2, __shfl_xor(r2, off));
-    if (threadIdx.x < 4)
-        tiles[4 * (size_t)blockIdx.x + threadIdx.x] =
-            threadIdx.x == 3 ? sqrt(r2) : 0.5 * (lo[threadIdx.x == 1 ? 1 : threadIdx.x == 2 ? 2 : 0] +
-                                                 hi[threadIdx.x == 1 ? 1 : threadIdx.x == 2 ? 2 : 0]);
+    for (int off = 32; off > 0; off >>= 1) {
+        r2 = fmax(r2, __shfl_xor(r2, off));
+        h2 = fmax(h2, __shfl_xor(h2, off));
+    }
+    if (threadIdx.x == 0) {
+        double *o = tiles + kTileRec * (size_t)blockIdx.x;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = 0.5 * (lo[c] + hi[c]);
+        o[3] = sqrt(r2);
+        // the points' offsets from the centroid are 1 - 3 b = 0.7253 (outer orbit) of
+        // the vertices' at most
+        o[4] = (1.0 - 3.0 * kRuleB) * sqrt(h2);
+    }
 }
 
 // Item (a, b) of one mesh by one block; part holds the 2 nr slots
 template <int FORM, bool K0, typename IP, typename DP, typename RP>
-__device__ __forceinline__ void sym_item(const SymCoef &cf, IP __restrict__ tri, DP __restrict__ stat,
+__device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict__ tri, DP __restrict__ stat,
                                          DP __restrict__ tiles, RP __restrict__ dyn, int T, int rt, int nr, int a, int b,
                                          float *__restrict__ part, SymLds &L)
 {
@@ -334,7 +345,7 @@ __device__ __forceinline__ void sym_item(const SymCoef &cf, IP __restrict__ tri,
         for (int p = 0; p < 6; ++p) a1[p] = a2[p] = zero;
         W[0] = W[1] = W[2] = zero;
         for (int J = a == b ? I : J0; J < J1; ++J) {
-            const double cx = tiles[4 * (size_t)J], cy = tiles[4 * (size_t)J + 1], cz = tiles[4 * (size_t)J + 2];
+            const double cx = tiles[kTileRec * (size_t)J], cy = tiles[kTileRec * (size_t)J + 1], cz = tiles[kTileRec * (size_t)J + 2];
             const double c[3] = {cx, cy, cz};
             const double s = cf.s;
             // columns: wavefronts 0..2 two points each, wavefront 3 the rest
@@ -389,8 +400,8 @@ __device__ __forceinline__ void sym_item(const SymCoef &cf, IP __restrict__ tri,
             for (int k = 0; k < 4; ++k) R.d[4 * g + k][li] = t < T ? td[4 * g + k] : 0.0f;
             __syncthreads();
             // well separated: |X| |Y| stays of the order of r^2
-            const double dx = tiles[4 * (size_t)I] - cx, dy = tiles[4 * (size_t)I + 1] - cy, dz = tiles[4 * (size_t)I + 2] - cz;
-            const double reach = kSymApart * (tiles[4 * (size_t)I + 3] + tiles[4 * (size_t)J + 3]);
+            const double dx = tiles[kTileRec * (size_t)I] - cx, dy = tiles[kTileRec * (size_t)I + 1] - cy, dz = tiles[kTileRec * (size_t)I + 2] - cz;
+            const double reach = kSymApart * (tiles[kTileRec * (size_t)I + 3] + tiles[kTileRec * (size_t)J + 3]);
             const bool near = dx * dx + dy * dy + dz * dz < reach * reach;
             if (!near) {
                 const bool live[4] = {true, true, true, true};
@@ -473,12 +484,12 @@ __device__ __forceinline__ int sym_next_item(int *__restrict__ next, SymLds &L)
 // One mesh: each block takes items (heaviest first) from a device counter
 // until the list is done.
 template <int FORM, bool K0>
-__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, int nr, SymCoef cf,
+__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, int nr, SymCoef<float> cf,
                                                               const int32_t *__restrict__ tri,
                                                               const double *__restrict__ stat,
                                                               const double *__restrict__ tiles,
                                                               const float *__restrict__ dyn,
-                                                              const int2 *__restrict__ items, int nitems,
+                                                              const int4 *__restrict__ items, int nitems,
                                                               int *__restrict__ next, float *__restrict__ part,
                                                               DevCtl ctl)
 {
@@ -487,8 +498,8 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, in
     for (;;) {
         const int i = sym_next_item(next, lds);
         if (i >= nitems) return;
-        const int2 it = items[i];
-        sym_item<FORM, K0>(cf, tri, stat, tiles, dyn, T, rt, nr, it.x, it.y, part, lds);
+        const int4 it = items[i];
+        sym_item<FORM, K0>(cf, tri, stat, tiles, dyn, T, rt, nr, it.y, it.z, part, lds);
     }
 }
 
@@ -512,15 +523,16 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym_batch(const FarRe
 
 // kFinishLanes lanes per triangle over its nr + 1 slots, then the test
 // projection of k_far_finish (sym_finish_group, far.h)
-__global__ __launch_bounds__(256) void k_far_sym_finish(int T, int rt, int nr, int family, int swap,
+template <typename R>
+__global__ __launch_bounds__(256) void k_far_sym_finish(int T, int rt, int nr, int nz, int family, int swap,
                                                           const double *__restrict__ geo,
-                                                          const float *__restrict__ part,
+                                                          const R *__restrict__ part,
                                                           double *__restrict__ triout, DevCtl ctl)
 {
     if (ctl_skip(ctl)) return;
     const int t = (int)((blockIdx.x * (size_t)blockDim.x + threadIdx.x) / kFinishLanes);
     const int l = threadIdx.x % kFinishLanes;
-    sym_finish_group(t, l, t < T, T, rt, nr, family, swap, geo, part, triout);   // the group agrees on t < T
+    sym_finish_group<R>(t, l, t < T, T, rt, nr, nz, family, swap, geo, part, triout);   // the group agrees on t < T
 }
 
 __global__ void k_sym_set(int *p, int v) { *p = v; }
@@ -539,42 +551,38 @@ bool sym_eligible(int T, double kappa, int mode)
     return mode >= 0;
 }
 
-// Ranges of rt tiles: about 320 ranges (51000 items).  Larger items come first;
-// among equal ones those near the diagonal, whose tiles touch and which take the
-// longer subtracted form, so that the list ends with the lightest items.
-void sym_plan(int T, int &rt, int &nr, std::vector<int2> &items)
+// Ranges of rt tiles: at most 320 ranges (51000 items) in FP32, kSym64Ranges in
+// FP64, whose slots are twice as large.  In FP64 an item (64 steps of 36 point
+// pairs per lane, 16 for each wavefront) is cut into nz parts where the items
+// are few for the 512 resident blocks: into two below 2048 items, further below
+// 600 (measured per product, 1620 triangles / 351 items: 2 parts 138 us, 8 172 us,
+// 16 226 us; 3380 triangles / 1431 items: 1 part 444 us, 2 416 us).  Items {request, a, b, part}; larger ones come
+// first, among equal ones those near the diagonal, whose tiles touch and take
+// longer, so that the list ends with the lightest.
+void sym_plan(int T, bool fp32, int request, int &rt, int &nr, int &nz, std::vector<int4> &items)
 {
-    const int ntile = (T + 63) / 64;
-    rt = std::max(1, (ntile + 319) / 320);
+    const int most = fp32 ? 320 : kSym64Ranges, ntile = (T + kSymTile - 1) / kSymTile;
+    rt = std::max(1, (ntile + most - 1) / most);
     nr = (ntile + rt - 1) / rt;
-    std::vector<std::pair<int, int2>> w;
+    nz = 1;
+    if (!fp32) {
+        const int n = nr * (nr + 1) / 2;
+        while (nz < 16 && n * nz < (nz == 1 ? 2048 : 600)) nz *= 2;
+    }
+    std::vector<std::pair<int, int4>> w;
     for (int k = 0; k < nr; ++k)
         for (int a = 0; a + k < nr; ++a) {
             const int b = a + k;
             const int na = std::min(ntile, (a + 1) * rt) - a * rt, nb = std::min(ntile, (b + 1) * rt) - b * rt;
             const int pairs = a == b ? na * (na + 1) / 2 : na * nb;
-            w.push_back({pairs, make_int2(a, b)});
+            for (int z = 0; z < nz; ++z) w.push_back({pairs, make_int4(request, a, b, z)});
         }
-    std::stable_sort(w.begin(), w.end(), [](const std::pair<int, int2> &x, const std::pair<int, int2> &y) {
+    std::stable_sort(w.begin(), w.end(), [](const std::pair<int, int4> &x, const std::pair<int, int4> &y) {
         return x.first > y.first;
     });
     items.clear();
     for (auto &e : w) items.push_back(e.second);
 }
-
-// CALL with the kernel of a form (0, 1, 3, 4) and screening (k0: kappa = 0)
-#define SYM_PICK(KERNEL, form, k0, CALL)                                                       \
-    if (k0) {                                                                                  \
-        if (form == 0) CALL((KERNEL<0, true>))                                                 \
-        else if (form == 1) CALL((KERNEL<1, true>))                                            \
-        else if (form == 3) CALL((KERNEL<3, true>))                                            \
-        else CALL((KERNEL<4, true>))                                                           \
-    } else {                                                                                   \
-        if (form == 0) CALL((KERNEL<0, false>))                                                \
-        else if (form == 1) CALL((KERNEL<1, false>))                                           \
-        else if (form == 3) CALL((KERNEL<3, false>))                                           \
-        else CALL((KERNEL<4, false>))                                                          \
-    }
 
 static const void *sym_kernel(int form, bool k0)
 {
@@ -592,31 +600,40 @@ static const void *sym_batch_kernel(int form, bool k0)
 }
 
 // as many blocks as are resident at once, or one per item if fewer
-static int sym_grid(const void *kernel, int nitems)
+int resident_blocks(const void *kernel, int threads, int nitems)
 {
     int dev = 0, ncu = 0, per_cu = 0;
     HIPCHECK(hipGetDevice(&dev));
     HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * kSymWaves, 0));
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0));
     return (int)std::max(1LL, std::min((long long)std::max(ncu, 1) * std::max(per_cu, 1), (long long)nitems));
 }
 
-int sym_blocks(int nitems, int form, bool k0) { return sym_grid(sym_kernel(form, k0), nitems); }
-int sym_batch_blocks_for(int form, bool k0, int n) { return sym_grid(sym_batch_kernel(form, k0), n); }
+int sym_blocks(bool fp32, int nitems, int form, bool k0)
+{
+    return fp32 ? resident_blocks(sym_kernel(form, k0), 64 * kSymWaves, nitems) : sym64_blocks(nitems, form, k0);
+}
+int sym_batch_blocks_for(bool fp32, int form, bool k0, int n)
+{
+    return fp32 ? resident_blocks(sym_batch_kernel(form, k0), 64 * kSymWaves, n) : sym64_batch_blocks(form, k0, n);
+}
 
 void launch_sym_tiles(DevMesh &d)
 {
-    hipLaunchKernelGGL(k_sym_tiles, dim3((d.hm.T + 63) / 64), dim3(64), 0, d.stream, d.hm.T, d.xyz, d.tri, d.sym_tiles);
+    hipLaunchKernelGGL(k_sym_tiles, dim3((d.hm.T + kSymTile - 1) / kSymTile), dim3(64), 0, d.stream, d.hm.T, d.xyz, d.tri,
+                       d.sym_tiles);
     HIPCHECK(hipGetLastError());
 }
 
+void launch_sym_reset(hipStream_t s, int *next) { hipLaunchKernelGGL(k_sym_set, dim3(1), dim3(1), 0, s, next, 0); }
+
 void launch_far_sym(DevMesh &d)
 {
-    SymCoef cf;
+    SymCoef<float> cf;
     const int form = sym_coef(d, cf);
     const bool k0 = !(d.prm.kappa > 0.0);
     const int nb = d.sym_blocks[sym_form_index(form)];
-    hipLaunchKernelGGL(k_sym_set, dim3(1), dim3(1), 0, d.stream, d.sym_next, 0);
+    launch_sym_reset(d.stream, d.sym_next);
 #define SYM_RUN(KF)                                                                                             \
     hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, cf, d.tri,  \
                        d.stat64, d.sym_tiles, d.dyn32, d.sym_items, d.sym_nitems, d.sym_next, (float *)d.part,  \
@@ -630,9 +647,13 @@ void launch_far_sym_finish(DevMesh &d)
     const int T = d.hm.T;
     const FormCoef &f = d.fm;
     const int swap = f.family == 0 && laplace_row(f) == 1;
-    hipLaunchKernelGGL(k_far_sym_finish, dim3((unsigned)(((size_t)T * kFinishLanes + 255) / 256)), dim3(256), 0,
-                       d.stream, T, d.sym_rt, d.sym_nr, f.family, swap, d.geo, (const float *)d.part, d.triout,
-                       d.ctl);
+    const dim3 grid((unsigned)(((size_t)T * kFinishLanes + 255) / 256)), block(256);
+    if (d.prm.precision == PB_FP64)
+        hipLaunchKernelGGL(k_far_sym_finish<double>, grid, block, 0, d.stream, T, d.sym_rt, d.sym_nr, d.sym_nz, f.family, swap,
+                           d.geo, (const double *)d.part, d.triout, d.ctl);
+    else
+        hipLaunchKernelGGL(k_far_sym_finish<float>, grid, block, 0, d.stream, T, d.sym_rt, d.sym_nr, d.sym_nz, f.family, swap,
+                           d.geo, (const float *)d.part, d.triout, d.ctl);
     HIPCHECK(hipGetLastError());
 }
 
@@ -641,7 +662,7 @@ void launch_far_sym_batch(int form, bool k0, const void *reqs, const int4 *items
                           hipStream_t s)
 {
     if (n == 0) return;
-    hipLaunchKernelGGL(k_sym_set, dim3(1), dim3(1), 0, s, next, 0);
+    launch_sym_reset(s, next);
 #define SYM_RUNB(KF) \
     hipLaunchKernelGGL(KF, dim3(nblocks), dim3(64 * kSymWaves), 0, s, (const FarReq<float> *)reqs, items, n, next);
     SYM_PICK(k_far_sym_batch, form, k0, SYM_RUNB)

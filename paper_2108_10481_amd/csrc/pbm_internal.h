@@ -130,7 +130,7 @@ struct KrylovReq {
 };
 struct TailReq {
     int T, V, S;               // triangles, vertices, source chunks of the regular split
-    int rt, nr;                // symmetric split (nr = 0: regular)
+    int rt, nr, nz;            // symmetric split (nr = 0: regular)
     int family, swap, precond;
     const int32_t *tri;
     const double *geo;
@@ -225,12 +225,12 @@ struct DevMesh {
     Params prm;
     pb_options opt;
     int S = 1;                     // far-field source chunks
-    // symmetric FP32 far field (k_far_sym.hip): tiles per range, ranges, work
+    // symmetric far field (k_far_sym.hip, k_far_sym64.hip): tiles per range, ranges, parts, work
     // list of range pairs (heaviest first), its counter, blocks per kernel form
-    int sym_rt = 0, sym_nr = 0, sym_nitems = 0;
-    int2 *sym_items = nullptr;
+    int sym_rt = 0, sym_nr = 0, sym_nz = 1, sym_nitems = 0;
+    int4 *sym_items = nullptr;
     int *sym_next = nullptr;
-    double *sym_tiles = nullptr;   // per tile of 64 triangles: centre 3, radius
+    double *sym_tiles = nullptr;   // per tile: centre 3, radius
     int sym_blocks[4] = {1, 1, 1, 1};
     hipStream_t stream = nullptr;
     size_t bytes = 0;
@@ -364,14 +364,23 @@ void launch_pair_blocks_subset(DevMesh &d, int n, const int32_t *t_sorted, const
 void ss_group(const std::vector<int32_t> &tri, int n, const int32_t *t, const int32_t *s, std::vector<int32_t> &idx,
               int count[4]);
 int choose_chunks(int T);
-// symmetric FP32 far field (k_far_sym.hip)
+// symmetric far field (k_far_sym.hip)
 bool sym_eligible(int T, double kappa, int mode);
-void sym_plan(int T, int &rt, int &nr, std::vector<int2> &items);
-int sym_blocks(int nitems, int form, bool k0);
+void sym_plan(int T, bool fp32, int request, int &rt, int &nr, int &nz, std::vector<int4> &items);
+int resident_blocks(const void *kernel, int threads, int nitems);
+int sym_blocks(bool fp32, int nitems, int form, bool k0);
+void launch_sym_reset(hipStream_t s, int *next);
+// the same in FP64 (k_far_sym64.hip): ranges at most (2 x 96 slots of 16 doubles per triangle)
+constexpr int kSym64Ranges = 96;
+int sym64_blocks(int nitems, int form, bool k0);
+int sym64_batch_blocks(int form, bool k0, int n);
+void launch_far_sym64(DevMesh &d);
+void launch_far_sym64_batch(int form, bool k0, const void *reqs, const int4 *items, int n, int nblocks, int *next,
+                            hipStream_t s);
 void launch_sym_tiles(DevMesh &d);
 void launch_far_sym(DevMesh &d);
 void launch_far_sym_finish(DevMesh &d);
-int sym_batch_blocks_for(int form, bool k0, int n);
+int sym_batch_blocks_for(bool fp32, int form, bool k0, int n);
 void launch_far_sym_batch(int form, bool k0, const void *reqs, const int4 *items, int n, int nblocks, int *next,
                           hipStream_t s);
 int reduction_chunks(int T);

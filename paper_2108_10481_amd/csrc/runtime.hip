@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "dense.h"
+#include "far.h"
 #include "trace.h"
 
 namespace pbm {
@@ -405,6 +406,8 @@ static void setup_and_wait(DevMesh &d)
     HIPCHECK(hipStreamSynchronize(d.stream));
 }
 
+size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64);
+
 static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCache *cache = nullptr)
 {
     check_options(opt);
@@ -485,19 +488,37 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     d->dyn64 = (double *)d->alloc(sizeof(double) * kDyn * T);
     d->dyn32 = (float *)d->alloc(sizeof(float) * kDyn * T);
     size_t part_bytes = sizeof(double) * 16 * (size_t)d->S * T;
-    if (opt->precision == PB_FP32 && opt->operator_mode != PB_TREECODE && d->far_rule == 0 &&
-        sym_eligible(T, opt->kappa, opt->far_symmetric)) {
-        // symmetric FP32 far field: 2 nr slots of 16 values per triangle
-        std::vector<int2> items;
-        sym_plan(T, d->sym_rt, d->sym_nr, items);
+    const bool fp32 = opt->precision == PB_FP32;
+    // every unordered pair once, FP32 or FP64 (FP64 only when the far field is
+    // known to stay matrix-free); under a memory budget the automatic choice
+    // takes it where the handle's expected footprint with its slots fits
+    bool sym = (fp32 || (opt->precision == PB_FP64 && opt->operator_mode == PB_MATRIX_FREE)) &&
+               opt->operator_mode != PB_TREECODE && d->far_rule == 0 && sym_eligible(T, opt->kappa, fp32 ? opt->far_symmetric : 0);
+    if (sym && !fp32) {
+        // the FP64 kernel's exponential takes scaled distances below 2^30
+        double lo[3] = {hm.xyz[0], hm.xyz[1], hm.xyz[2]}, hi[3] = {lo[0], lo[1], lo[2]}, span = 0.0;
+        for (size_t i = 0; i < hm.xyz.size(); ++i) {
+            lo[i % 3] = std::min(lo[i % 3], hm.xyz[i]);
+            hi[i % 3] = std::max(hi[i % 3], hm.xyz[i]);
+        }
+        for (int c = 0; c < 3; ++c) span += hi[c] - lo[c];
+        sym = span * opt->kappa * 1.4426950408889634 < 1073741824.0;
+    }
+    if (sym && opt->memory_budget && (!fp32 || (opt->far_symmetric == 0 && T < 3584)) &&
+        estimate_device_bytes(V, T, opt, true) > opt->memory_budget)
+        sym = false;
+    if (sym) {
+        // 2 nr nz slots of 16 values per triangle
+        std::vector<int4> items;
+        sym_plan(T, fp32, 0, d->sym_rt, d->sym_nr, d->sym_nz, items);
         d->sym_items = upload(*d, items);
         d->sym_nitems = (int)items.size();
         d->sym_next = (int *)d->alloc(sizeof(int));
         const bool k0 = !(opt->kappa > 0.0);
-        const int forms[4] = {0, 1, 3, 4};
-        for (int f = 0; f < 4; ++f) d->sym_blocks[f] = sym_blocks(d->sym_nitems, forms[f], k0);
-        d->sym_tiles = (double *)d->alloc(sizeof(double) * 4 * ((size_t)(T + 63) / 64));
-        part_bytes = std::max(part_bytes, sizeof(float) * 16 * 2 * (size_t)d->sym_nr * T);
+        for (int f = 0; f < kSymForms; ++f) d->sym_blocks[f] = sym_blocks(fp32, d->sym_nitems, kSymFormOf[f], k0);
+        d->sym_tiles = (double *)d->alloc(sizeof(double) * kTileRec * ((size_t)(T + kSymTile - 1) / kSymTile));
+        part_bytes = std::max(part_bytes,
+                              (fp32 ? sizeof(float) : sizeof(double)) * 16 * 2 * (size_t)d->sym_nr * d->sym_nz * T);
     }
     d->part = d->alloc(part_bytes);
     d->triout = (double *)d->alloc(sizeof(double) * 6 * T);
@@ -528,7 +549,8 @@ DevMesh *create_mesh_checked(const pb_mesh *mesh, const pb_options *opt, BlockCa
 // near blocks (about 14 T pairs and 20 V nonzeros per block on molecular
 // surfaces, with margin), work vectors, the Arnoldi basis, and the dense far
 // field in assembled modes.
-size_t estimate_device_bytes(int V, int T, const pb_options *o)
+// sym64: a matrix-free FP64 handle takes the symmetric split's slots
+size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64)
 {
     const double v = V, t = T, n = 2.0 * V;
     // a buffer of kCacheMin bytes or more may come from a server's block cache,
@@ -541,6 +563,12 @@ size_t estimate_device_bytes(int V, int T, const pb_options *o)
         sym_eligible(T, o->kappa, o->far_symmetric)) {
         const double ntile = std::ceil(t / 64.0), rt = std::ceil(ntile / 320.0);
         part = std::max(part, 2.0 * std::ceil(ntile / rt) * t * 16 * 4);   // the symmetric far field's slots
+    }
+    if (sym64 && o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE && o->regular_order != 1) {
+        int rt, nr, nz;
+        std::vector<int4> items;
+        sym_plan(T, false, 0, rt, nr, nz, items);
+        part = std::max(part, 2.0 * nr * nz * t * 16 * 8);
     }
     b += buf(part);
     b += buf(16.0 * t * (36 * 8 + 3 * 4));
@@ -1092,7 +1120,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
         DevMesh &d = *ds[r];
         GraphGmres &g = *G[r];
         const bool mass = mass_mode(d);
-        const bool sym = fp32 && d.sym_nitems > 0;
+        const bool sym = d.sym_nitems > 0;
         TailReq &t = tq[k];
         t = TailReq{};
         t.T = d.hm.T;
@@ -1100,6 +1128,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
         t.S = d.S;
         t.rt = sym ? d.sym_rt : 0;
         t.nr = sym ? d.sym_nr : 0;
+        t.nz = sym ? d.sym_nz : 0;
         t.family = d.fm.family;
         t.swap = d.fm.family == 0 && laplace_row(d.fm) == 1;
         t.precond = mass ? 0 : 1;
@@ -1607,7 +1636,7 @@ pb_status pb_mesh_get_info(const pb_mesh_handle *h, pb_mesh_info *info)
     info->source_chunks = d.S;
     info->assembled = d.dense ? 1 : 0;
     info->device_bytes = d.bytes;
-    info->far_symmetric = (d.sym_nitems > 0 && !d.dense && !d.tree) ? 1 : 0;
+    info->far_symmetric = (d.prm.precision == PB_FP32 && d.sym_nitems > 0 && !d.dense && !d.tree) ? 1 : 0;
     return PB_OK;
     PB_CATCH
 }

@@ -21,7 +21,7 @@
 
 namespace pbm {
 DevMesh *create_mesh_checked(const pb_mesh *mesh, const pb_options *opt, BlockCache *cache);
-size_t estimate_device_bytes(int V, int T, const pb_options *opt);
+size_t estimate_device_bytes(int V, int T, const pb_options *opt, bool sym64);
 }  // namespace pbm
 
 using namespace pbm;
@@ -153,7 +153,7 @@ pb_status pb_estimate_device_bytes(const pb_mesh *mesh, const pb_options *opt, s
 {
     SV_TRY
     if (!mesh || !opt || !bytes) fail(PB_E_INVALID_ARG, "NULL argument");
-    *bytes = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt);
+    *bytes = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt, true);
     return PB_OK;
     SV_CATCH
 }
@@ -220,7 +220,9 @@ pb_status pb_submit(pb_server *s, const pb_mesh *mesh, const pb_charges *charges
     r->qxyz.assign(charges->xyz, charges->xyz + 3 * (size_t)charges->n);
     r->q.assign(charges->q, charges->q + charges->n);
     r->opt = *opt;
-    r->est = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt);
+    r->est = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt, true);
+    // an FP64 handle that its symmetric split's slots would keep out runs per ordered pair
+    if (r->est > s->budget) r->est = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt, false);
     if (r->est > s->budget) fail(PB_E_NOMEM, "request footprint exceeds the server's device-memory budget");
     // the handle may not outgrow its admission footprint
     if (r->opt.memory_budget == 0 || r->opt.memory_budget > r->est) r->opt.memory_budget = r->est;
