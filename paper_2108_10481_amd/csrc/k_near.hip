@@ -5,25 +5,12 @@
 // block-diagonal preconditioner (Preconditioning, Algebraic preconditioners).
 // Everything here is FP64 in every precision mode.
 #include <mutex>
+#include <vector>
 
+#include "fp64.h"
 #include "pbm_internal.h"
 
 namespace pbm {
-
-constexpr int kMaxGL = 16;
-__constant__ double c_gl_x[kMaxGL + 1][kMaxGL];
-__constant__ double c_gl_w[kMaxGL + 1][kMaxGL];
-
-void upload_gauss_tables()
-{
-    static std::once_flag once;
-    std::call_once(once, [] {
-        static double hx[kMaxGL + 1][kMaxGL] = {}, hw[kMaxGL + 1][kMaxGL] = {};
-        for (int n = 1; n <= kMaxGL; ++n) gauss_legendre01(n, hx[n], hw[n]);
-        HIPCHECK(hipMemcpyToSymbol(HIP_SYMBOL(c_gl_x), hx, sizeof(hx)));
-        HIPCHECK(hipMemcpyToSymbol(HIP_SYMBOL(c_gl_w), hw, sizeof(hw)));
-    });
-}
 
 // Reference triangle {0 <= u2 <= u1 <= 1}, chi(u) = P0 + u1 (P1 - P0) + u2 (P2 - P1),
 // barycentrics (1 - u1, u1 - u2, u2), surface element 2|T| du.  The unit
@@ -31,7 +18,7 @@ void upload_gauss_tables()
 // reference triangles with Jacobians that cancel the 1/r singularity.
 struct SSPoint { double u1, u2, v1, v2, jac; };
 
-__device__ inline SSPoint ss_map(int cas, int r, double xi, double a, double b, double c)
+static SSPoint ss_map(int cas, int r, double xi, double a, double b, double c)
 {
     SSPoint m;
     if (cas == 3) {          // identical triangles: 6 regions
@@ -59,6 +46,60 @@ __device__ inline SSPoint ss_map(int cas, int r, double xi, double a, double b, 
         else { m.u1 = xi * b; m.u2 = xi * b * c; m.v1 = xi; m.v2 = xi * a; }
     }
     return m;
+}
+
+// The rule's points, the same for every pair of a case: u1, u2, v1, v2, then the
+// nine weights w lambda_k(u) mu_l(v) (Jacobian included), padded to 16 doubles
+// (two 64-byte scalar loads).  Cases in the order identical, edge, vertex.
+constexpr int kSSRec = 16;
+constexpr int kMaxSS = 8;                          // singular_order
+constexpr int kSSRegions[4] = {0, 2, 5, 6};        // by shared vertices
+struct SSTable {
+    const double *pts = nullptr;
+    int first[4] = {}, count[4] = {};              // by shared vertices
+};
+
+// Device table of order n on the current device: built at its first use and kept
+// until the process ends (13 n^4 records of 128 bytes, 426 KB at order 4)
+static SSTable ss_table(int n)
+{
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static SSTable tab[kMaxDevices][kMaxSS + 1];
+    int dev = -1;
+    HIPCHECK(hipGetDevice(&dev));
+    if (dev < 0 || dev >= kMaxDevices) fail(PB_E_DEVICE, "device index out of range for the quadrature tables");
+    std::lock_guard<std::mutex> lk(mu);
+    SSTable &t = tab[dev][n];
+    if (t.pts) return t;
+    std::vector<double> x(n), w(n), rec;
+    gauss_legendre01(n, x.data(), w.data());
+    SSTable s;
+    for (int cas = 3; cas >= 1; --cas) {
+        s.first[cas] = (int)(rec.size() / kSSRec);
+        for (int r = 0; r < kSSRegions[cas]; ++r)
+            for (int i0 = 0; i0 < n; ++i0)
+                for (int i1 = 0; i1 < n; ++i1)
+                    for (int i2 = 0; i2 < n; ++i2)
+                        for (int i3 = 0; i3 < n; ++i3) {
+                            const SSPoint m = ss_map(cas, r, x[i0], x[i1], x[i2], x[i3]);
+                            const double W = w[i0] * w[i1] * w[i2] * w[i3] * m.jac;
+                            const double lx[3] = {1.0 - m.u1, m.u1 - m.u2, m.u2};
+                            const double ly[3] = {1.0 - m.v1, m.v1 - m.v2, m.v2};
+                            double q[kSSRec] = {m.u1, m.u2, m.v1, m.v2};
+                            for (int k = 0; k < 3; ++k)
+                                for (int l = 0; l < 3; ++l) q[4 + 3 * k + l] = W * lx[k] * ly[l];
+                            rec.insert(rec.end(), q, q + kSSRec);
+                        }
+        s.count[cas] = (int)(rec.size() / kSSRec) - s.first[cas];
+    }
+    void *p = nullptr;
+    HIPCHECK(hipMalloc(&p, sizeof(double) * rec.size()));
+    const hipError_t e = hipMemcpy(p, rec.data(), sizeof(double) * rec.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) (void)hipFree(p);
+    HIPCHECK(e);
+    s.pts = (const double *)p;
+    return t = s;
 }
 
 // Local vertex order: shared vertices first.  Identical: stored order.  Edge:
@@ -89,112 +130,159 @@ __device__ inline int ss_order(int t, int s, const int *tv, const int *sv, int *
     return ns;
 }
 
-// 1/sqrt(x) in FP64: hardware estimate and two Newton steps
-__device__ inline double rsq64(double x)
+// One lane per ordered pair (t, s): the WAVES wavefronts of a block hold the same
+// 64 pairs of one case (CASE shared vertices) and take a part of the rule's points
+// each, which are then uniform across the wavefront: a point and its nine weights
+// come through scalar loads and feed the vector unit as scalar operands, and the
+// 36 sums need no reduction across lanes, only over the wavefronts (LDS).
+// out[36 p + 9 op + 3 a + b], op = V_L, K_L, V_Y, K_Y; a, b local vertex ids of t
+// and s in stored order; p = idx[item].  SMALL: every kappa log2(e) r of a near
+// pair is at most kExpSmall, 8 instead of 15 instructions for its exponential.
+// Identical triangles lie in one plane: d.n = 0, K = 0, only V is summed.
+// Bound: the FP64 vector rate, 75 instructions per point and pair (68 SMALL; 39
+// and 32 for identical triangles); with a group of lanes per pair (points, weights
+// and basis formed by every lane, 36 butterfly reductions) it was about 130.
+// Refresh of a 24500-triangle matrix-free handle (all of the near field): 1.67 ->
+// 0.81 ms.
+template <int CASE, bool SMALL, int WAVES>
+__device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__restrict__ idx,
+                                         const int32_t *__restrict__ pair_t, const int32_t *__restrict__ pair_s,
+                                         const int32_t *__restrict__ tri, const double *__restrict__ xyz,
+                                         const double *__restrict__ geo, double kl, double kappa,
+                                         const double *__restrict__ pts, int npts, double *__restrict__ out,
+                                         double (*__restrict__ red)[18][64])
 {
-    double y = __builtin_amdgcn_rsq(x);
-    double h = x * y;
-    y = fma(0.5 * y, fma(-h, y, 1.0), y);
-    h = x * y;
-    y = fma(0.5 * y, fma(-h, y, 1.0), y);
-    return y;
-}
-
-// LANES lanes per ordered pair (t, s), 64 / LANES pairs per wavefront, all of
-// one case (CASE shared vertices, so the region of a Gauss point is uniform
-// across the wavefront).  Lanes stride over the regions x N^4 Gauss points;
-// each lane accumulates the 4 x 3 x 3 products in FP64, then a butterfly
-// reduction inside the lane group.  out[36 p + 9 op + 3 a + b], op = V_L, K_L,
-// V_Y, K_Y; a, b local vertex ids of t and s in stored order; p = idx[item].
-template <int N, int CASE, int LANES>
-__global__ __launch_bounds__(256) void k_near_ss(int count, const int32_t *__restrict__ idx,
-                                                 const int32_t *__restrict__ pair_t, const int32_t *__restrict__ pair_s,
-                                                 const int32_t *__restrict__ tri, const double *__restrict__ xyz,
-                                                 const double *__restrict__ geo, double kappa, double *__restrict__ out)
-{
-    constexpr int G = 64 / LANES;
-    const int lane = threadIdx.x & 63, sub = lane % LANES;
-    const int first = (blockIdx.x * 4 + (threadIdx.x >> 6)) * G;
-    if (first >= count) return;   // whole wavefront idle
-    const int item = first + lane / LANES;
-    const bool active = item < count;   // idle groups repeat the last pair and do not store
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int item = first + lane;
+    const bool active = item < count;   // lanes past the end repeat the last pair and do not store
     const int p = idx[active ? item : count - 1];
     const int t = pair_t[p], s = pair_s[p];
     int tv[3], sv[3];
     for (int k = 0; k < 3; ++k) { tv[k] = tri[3 * t + k]; sv[k] = tri[3 * s + k]; }
     int pt[3], ps[3];
     (void)ss_order(t, s, tv, sv, pt, ps);
-    double P[3][3], Q[3][3];
-    for (int m = 0; m < 3; ++m)
-        for (int c = 0; c < 3; ++c) {
-            P[m][c] = xyz[3 * tv[pt[m]] + c];
-            Q[m][c] = xyz[3 * sv[ps[m]] + c];
-        }
-    const double *gs = geo + (size_t)s * kGeo;
-    const double nsx = gs[18], nsy = gs[19], nsz = gs[20];
-    const double at = geo[(size_t)t * kGeo + 21], as = gs[21];
-    double e1[3], e2[3], f1[3], f2[3];
+    double A[3], e1[3], e2[3], f1[3], f2[3], ns[3];
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
-        e1[c] = P[1][c] - P[0][c]; e2[c] = P[2][c] - P[1][c];
-        f1[c] = Q[1][c] - Q[0][c]; f2[c] = Q[2][c] - Q[1][c];
+        const double P0 = xyz[3 * tv[pt[0]] + c], P1 = xyz[3 * tv[pt[1]] + c], P2 = xyz[3 * tv[pt[2]] + c];
+        const double Q0 = xyz[3 * sv[ps[0]] + c], Q1 = xyz[3 * sv[ps[1]] + c], Q2 = xyz[3 * sv[ps[2]] + c];
+        A[c] = P0 - Q0;
+        e1[c] = P1 - P0; e2[c] = P2 - P1;
+        f1[c] = Q1 - Q0; f2[c] = Q2 - Q1;
+        ns[c] = geo[(size_t)s * kGeo + 18 + c];
     }
-    constexpr int N4 = N * N * N * N;
-    constexpr int nreg = CASE == 3 ? 6 : CASE == 2 ? 5 : 2;
-    constexpr int npts = nreg * N4;
-    double acc[36];
+    constexpr int NK = CASE == 3 ? 1 : 2;   // V alone, or V and K, per kernel
+    double aL[NK][9], aY[NK][9];
 #pragma unroll
-    for (int v = 0; v < 36; ++v) acc[v] = 0.0;
-    for (int ix = sub; ix < npts; ix += LANES) {
-        const int r = ix / N4;
-        int rem = ix - r * N4;
-        const int i0 = rem / (N * N * N); rem -= i0 * N * N * N;
-        const int i1 = rem / (N * N); rem -= i1 * N * N;
-        const int i2 = rem / N;
-        const int i3 = rem - i2 * N;
-        const SSPoint m = ss_map(CASE, r, c_gl_x[N][i0], c_gl_x[N][i1], c_gl_x[N][i2], c_gl_x[N][i3]);
-        const double W = c_gl_w[N][i0] * c_gl_w[N][i1] * c_gl_w[N][i2] * c_gl_w[N][i3] * m.jac;
-        const double dx = (P[0][0] + m.u1 * e1[0] + m.u2 * e2[0]) - (Q[0][0] + m.v1 * f1[0] + m.v2 * f2[0]);
-        const double dy = (P[0][1] + m.u1 * e1[1] + m.u2 * e2[1]) - (Q[0][1] + m.v1 * f1[1] + m.v2 * f2[1]);
-        const double dz = (P[0][2] + m.u1 * e1[2] + m.u2 * e2[2]) - (Q[0][2] + m.v1 * f1[2] + m.v2 * f2[2]);
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        const double ri = rsq64(r2);
-        const double rr = r2 * ri;
-        const double ek = exp(-kappa * rr);
-        const double dn = dx * nsx + dy * nsy + dz * nsz;
-        const double ri3 = ri * ri * ri;
-        const double gL = ri, fL = dn * ri3, gY = ek * ri, fY = ek * (1.0 + kappa * rr) * dn * ri3;
-        const double lx[3] = {1.0 - m.u1, m.u1 - m.u2, m.u2};
-        const double ly[3] = {1.0 - m.v1, m.v1 - m.v2, m.v2};
+    for (int o = 0; o < NK; ++o)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double wk = W * lx[k];
+        for (int v = 0; v < 9; ++v) aL[o][v] = aY[o][v] = 0.0;
+    using CD = const __attribute__((address_space(4))) double *;
+    const int i0 = (int)((long long)npts * w / WAVES), i1 = (int)((long long)npts * (w + 1) / WAVES);
+    CD rec = (CD)(pts + (size_t)i0 * kSSRec);
+    double cur[13];
 #pragma unroll
-            for (int l = 0; l < 3; ++l) {
-                const double bb = wk * ly[l];
-                acc[3 * k + l] += bb * gL;
-                acc[9 + 3 * k + l] += bb * fL;
-                acc[18 + 3 * k + l] += bb * gY;
-                acc[27 + 3 * k + l] += bb * fY;
+    for (int k = 0; k < 13; ++k) cur[k] = rec[k];
+    for (int i = i0; i < i1; ++i) {
+        // the next point's record is loaded while this one is summed
+        CD nxt = rec + (i + 1 < i1 ? kSSRec : 0);
+        double nx[13];
+#pragma unroll
+        for (int k = 0; k < 13; ++k) nx[k] = nxt[k];
+        rec = nxt;
+        double d[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            d[c] = fma(cur[0], e1[c], fma(cur[1], e2[c], fma(-cur[2], f1[c], fma(-cur[3], f2[c], A[c]))));
+        const double r2[1] = {d[0] * d[0] + d[1] * d[1] + d[2] * d[2]};
+        double ri[1], ek[1];
+        rsqrt3_n<1>(r2, ri);
+        ek[0] = kl * r2[0] * ri[0];
+        if (SMALL) exp2small_n<1>(ek);
+        else exp2neg_n<1>(ek);
+        const double gL = ri[0], gY = ek[0] * ri[0];
+        double fL = 0.0, fY = 0.0;
+        if (CASE != 3) {
+            const double dn = d[0] * ns[0] + d[1] * ns[1] + d[2] * ns[2];
+            const double ri2 = gL * gL, ri3 = gL * ri2;
+            fL = dn * ri3;
+            fY = dn * (ek[0] * fma(kappa, ri2, ri3));
+        }
+#pragma unroll
+        for (int v = 0; v < 9; ++v) {
+            aL[0][v] = fma(cur[4 + v], gL, aL[0][v]);
+            aY[0][v] = fma(cur[4 + v], gY, aY[0][v]);
+            if (CASE != 3) {
+                aL[NK - 1][v] = fma(cur[4 + v], fL, aL[NK - 1][v]);
+                aY[NK - 1][v] = fma(cur[4 + v], fY, aY[NK - 1][v]);
             }
         }
-    }
 #pragma unroll
-    for (int v = 0; v < 36; ++v) {
-        double x = acc[v];
-#pragma unroll
-        for (int off = LANES / 2; off > 0; off >>= 1) x += __shfl_xor(x, off);
-        acc[v] = x;
+        for (int k = 0; k < 13; ++k) cur[k] = nx[k];
     }
-    if (active && sub == 0) {
-        const double scale = at * as / kPi;   // (2|t|)(2|s|) / (4 pi)
+    // the wavefronts' sums, in order, onto the first wavefront's: Laplace, then Yukawa
+    auto join = [&](double (&a)[NK][9]) {
+        __syncthreads();
+        if (w > 0) {
+#pragma unroll
+            for (int o = 0; o < NK; ++o)
+#pragma unroll
+                for (int v = 0; v < 9; ++v) red[w - 1][9 * o + v][lane] = a[o][v];
+        }
+        __syncthreads();
+        if (w == 0) {
+#pragma unroll
+            for (int o = 0; o < NK; ++o)
+#pragma unroll
+                for (int v = 0; v < 9; ++v)
+                    for (int u = 0; u < WAVES - 1; ++u) a[o][v] += red[u][9 * o + v][lane];
+        }
+    };
+    join(aL);
+    join(aY);
+    if (w == 0 && active) {
+        const double scale = geo[(size_t)t * kGeo + 21] * geo[(size_t)s * kGeo + 21] / kPi;   // (2|t|)(2|s|) / (4 pi)
         double *o = out + (size_t)p * 36;
 #pragma unroll
-        for (int op = 0; op < 4; ++op)
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int l = 0; l < 3; ++l) o[9 * op + 3 * pt[k] + ps[l]] = acc[9 * op + 3 * k + l] * scale;
+            for (int l = 0; l < 3; ++l) {
+                double *ol = o + 3 * pt[k] + ps[l];
+                ol[0] = aL[0][3 * k + l] * scale;
+                ol[9] = CASE == 3 ? 0.0 : aL[NK - 1][3 * k + l] * scale;
+                ol[18] = aY[0][3 * k + l] * scale;
+                ol[27] = CASE == 3 ? 0.0 : aY[NK - 1][3 * k + l] * scale;
+            }
     }
+}
+
+// All pairs in one launch, blocks of 64 pairs of one case: identical, edge, then
+// vertex pairs (fewest, with the most points, first)
+struct SSRange { int first, count, blocks, npts; const double *pts; };
+template <bool SMALL, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_near_ss(SSRange r3, SSRange r2, SSRange r1, const int32_t *__restrict__ idx,
+                                                        const int32_t *__restrict__ pair_t,
+                                                        const int32_t *__restrict__ pair_s,
+                                                        const int32_t *__restrict__ tri, const double *__restrict__ xyz,
+                                                        const double *__restrict__ geo, double kl, double kappa,
+                                                        double *__restrict__ out)
+{
+    __shared__ double red[WAVES - 1][18][64];
+    int b = blockIdx.x;
+    if (b < r3.blocks) {
+        ss_pairs<3, SMALL, WAVES>(64 * b, r3.count, idx + r3.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r3.pts,
+                                  r3.npts, out, red);
+        return;
+    }
+    b -= r3.blocks;
+    if (b < r2.blocks) {
+        ss_pairs<2, SMALL, WAVES>(64 * b, r2.count, idx + r2.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r2.pts,
+                                  r2.npts, out, red);
+        return;
+    }
+    b -= r2.blocks;
+    ss_pairs<1, SMALL, WAVES>(64 * b, r1.count, idx + r1.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r1.pts, r1.npts,
+                              out, red);
 }
 
 // Pair indices 0..n-1 grouped by the number of shared vertices: identical,
@@ -216,37 +304,34 @@ void ss_group(const std::vector<int32_t> &tri, int n, const int32_t *t, const in
     if (count[0]) fail(PB_E_INVALID_ARG, "pair does not share a vertex");
 }
 
-template <int N>
-static void launch_ss_n(hipStream_t st, const int count[4], const int32_t *idx, const int32_t *pt, const int32_t *ps,
-                        const DevMesh &d, double kap, double *out)
-{
-    const int n3 = count[3], n2 = count[2], n1 = count[1];
-    // wavefronts of 64 / LANES pairs, 4 wavefronts per block
-    auto grid = [](int n, int lanes) { const int per = 4 * (64 / lanes); return dim3((n + per - 1) / per); };
-    if (n3)
-        hipLaunchKernelGGL((k_near_ss<N, 3, 64>), grid(n3, 64), dim3(256), 0, st, n3, idx, pt, ps, d.tri, d.xyz, d.geo,
-                           kap, out);
-    if (n2)
-        hipLaunchKernelGGL((k_near_ss<N, 2, 32>), grid(n2, 32), dim3(256), 0, st, n2, idx + n3, pt, ps, d.tri, d.xyz,
-                           d.geo, kap, out);
-    if (n1)
-        hipLaunchKernelGGL((k_near_ss<N, 1, 16>), grid(n1, 16), dim3(256), 0, st, n1, idx + n3 + n2, pt, ps, d.tri,
-                           d.xyz, d.geo, kap, out);
-}
-
 static void launch_ss(DevMesh &d, const int count[4], const int32_t *idx, const int32_t *pt, const int32_t *ps,
                       double *out, int order)
 {
     if (count[1] + count[2] + count[3] == 0) return;
-    upload_gauss_tables();
-    const double kap = d.prm.kappa;
-    switch (order) {
-#define SS_CASE(n) \
-    case n: launch_ss_n<n>(d.stream, count, idx, pt, ps, d, kap, out); break;
-        SS_CASE(1) SS_CASE(2) SS_CASE(3) SS_CASE(4) SS_CASE(5) SS_CASE(6) SS_CASE(7) SS_CASE(8)
-#undef SS_CASE
-    default: fail(PB_E_INVALID_ARG, "singular_order must be in [1, 8]");
+    if (order < 1 || order > kMaxSS) fail(PB_E_INVALID_ARG, "singular_order must be in [1, 8]");
+    const SSTable tab = ss_table(order);
+    SSRange r[4];
+    int blocks = 0, first = 0;
+    for (int c = 3; c >= 1; --c) {
+        r[c] = SSRange{first, count[c], (count[c] + 63) / 64, tab.count[c], tab.pts + (size_t)tab.first[c] * kSSRec};
+        first += count[c];
+        blocks += r[c].blocks;
     }
+    const double kl = d.prm.kappa * 1.4426950408889634;
+    // a near pair's points are at most two longest edges apart
+    const bool small = 2.0 * d.max_edge * kl <= kExpSmall;
+#define SS_RUN(SM, W)                                                                                               \
+    hipLaunchKernelGGL((k_near_ss<SM, W>), dim3(blocks), dim3(64 * W), 0, d.stream, r[3], r[2], r[1], idx, pt, ps, \
+                       d.tri, d.xyz, d.geo, kl, d.prm.kappa, out)
+    // eight wavefronts share a block's pairs while four would leave compute units idle
+    if (blocks < 256) {
+        if (small) SS_RUN(true, 8);
+        else SS_RUN(false, 8);
+    } else {
+        if (small) SS_RUN(true, 4);
+        else SS_RUN(false, 4);
+    }
+#undef SS_RUN
     HIPCHECK(hipGetLastError());
 }
 

@@ -275,6 +275,7 @@ struct DevMesh {
     DevCtl ctl;                    // set while a GMRES iteration is being captured
     GraphGmres *gg[2] = {nullptr, nullptr};   // per operator level
     double t_setup = 0.0;
+    double max_edge = 0.0;         // longest triangle edge
     bool want_dense = false;
     // charges workspace
     double *qbuf = nullptr;        // 7 x qcap: SoA x, y, z, q then AoS xyz

@@ -433,6 +433,13 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
         d->S = tree_splits(*d->tree);
     }
 
+    for (size_t i = 0; i < hm.tri.size(); ++i) {
+        const double *p = &hm.xyz[3 * (size_t)hm.tri[i]], *q = &hm.xyz[3 * (size_t)hm.tri[i % 3 == 2 ? i - 2 : i + 1]];
+        const double dx = p[0] - q[0], dy = p[1] - q[1], dz = p[2] - q[2];
+        d->max_edge = std::max(d->max_edge, dx * dx + dy * dy + dz * dz);
+    }
+    d->max_edge = std::sqrt(d->max_edge);
+
     d->xyz = upload(*d, hm.xyz);
     d->tri = upload(*d, hm.tri);
     d->inc_ptr = upload(*d, hm.inc_ptr);
