@@ -327,11 +327,10 @@ pb_status pb_mesh_reaction_potential(pb_mesh_handle *h, const double *phi, const
  * pts_device: npts x 3 doubles (row-major points); out_device: npts doubles.
  * All three are device pointers owned by the caller.  Runs on hip_stream
  * (NULL = the handle's stream) and returns without synchronising.
- * Per-point partial sums over the source chunks (min(1, ceil(T / 4096)) of
- * them) go to a static device array of 4 MiB (524288 doubles) that each GPU the
- * library runs on holds until the process ends: npts x chunks above 524288 is
- * rejected with PB_E_INVALID_ARG (at 81920 triangles, 20 chunks, up to 26214
- * points).  Every call on one GPU shares that array, so calls that overlap in
+ * Per-point partial sums over source chunks go to a static device array of 4
+ * MiB (524288 doubles) that each GPU the library runs on holds until the
+ * process ends: npts x max(1, ceil(T / 4096)) above 524288 is rejected with
+ * PB_E_INVALID_ARG (at 81920 triangles up to 26214 points).  Every call on one GPU shares that array, so calls that overlap in
  * time on one GPU (any handles, any streams) race; every call writes all the
  * partial sums it reads, so nothing needs clearing between calls.  Results
  * equal pb_mesh_reaction_potential's bit for bit. */

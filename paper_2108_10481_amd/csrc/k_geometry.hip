@@ -1,7 +1,10 @@
 // Geometry, charge-to-surface projections (Eq. sources), reaction potential
 // (Eq. phireac_bie) and the charge-inside-surface check.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
+#include "fp64.h"
 #include "pbm_internal.h"
 
 namespace pbm {
@@ -77,10 +80,14 @@ void launch_geometry(DevMesh &d)
 }
 
 // ------------------------------------------------------------------ sources
-// One thread per quadrature point: phi_D and phi_N of Eq. sources without the
-// 1/(4 pi eps_in) factor.  Charges are read with uniform (scalar) loads.
-__global__ void k_source_field(int T, int nq, const double *__restrict__ geo, const double *__restrict__ qb,
-                               double *__restrict__ f)
+// One thread per quadrature point and chunk of charges (grid.y): phi_D and phi_N of
+// Eq. sources without the 1/(4 pi eps_in) factor, f[c][2][6 T].  Charges are read
+// with uniform (scalar) loads, two at a time.  Bound: the FP64 vector rate, 19
+// instructions per point and charge (a division by the square root took about 50);
+// 40500 triangles, 2000 charges: the projections and the potential below together
+// went from 2.40 to 0.83 ms, host copies included.
+__global__ __launch_bounds__(256) void k_source_field(int T, int nq, int chunk, const double *__restrict__ geo,
+                                                      const double *__restrict__ qb, double *__restrict__ f)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 6 * T) return;
@@ -90,26 +97,47 @@ __global__ void k_source_field(int T, int nq, const double *__restrict__ geo, co
     double nx = g[18], ny = g[19], nz = g[20];
     const double *qx = qb, *qy = qb + nq, *qz = qb + 2 * nq, *qq = qb + 3 * nq;
     double sD = 0.0, sN = 0.0;
-    for (int j = 0; j < nq; ++j) {
-        double dx = x - qx[j], dy = y - qy[j], dz = z - qz[j];
-        double r2 = dx * dx + dy * dy + dz * dz;
-        double ri = 1.0 / sqrt(r2);
-        sD += qq[j] * ri;
-        sN -= qq[j] * (dx * nx + dy * ny + dz * nz) * ri * ri * ri;
-    }
-    f[i] = sD;
-    f[(size_t)6 * T + i] = sN;
+    const int j0 = blockIdx.y * chunk, j1 = min(nq, j0 + chunk);
+    auto add = [&](int j, auto n) {
+        constexpr int N = decltype(n)::value;
+        double r2[N], ri[N], dn[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const double dx = x - qx[j + k], dy = y - qy[j + k], dz = z - qz[j + k];
+            r2[k] = dx * dx + dy * dy + dz * dz;
+            dn[k] = dx * nx + dy * ny + dz * nz;
+        }
+        rsqrt3_n<N>(r2, ri);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const double a = qq[j + k] * ri[k];
+            sD += a;
+            sN = fma(-dn[k] * (ri[k] * ri[k]), a, sN);
+        }
+    };
+    int j = j0;
+    for (; j + 1 < j1; j += 2) add(j, std::integral_constant<int, 2>());
+    if (j < j1) add(j, std::integral_constant<int, 1>());
+    double *o = f + (size_t)blockIdx.y * 12 * T;
+    o[i] = sD;
+    o[(size_t)6 * T + i] = sN;
 }
 
-// per-triangle P1 test projection of point values: out[t][k] = |t| sum_p w_p lambda_k(p) f[t][p] * scale
-__global__ void k_project2(int T, const double *__restrict__ geo, const double *__restrict__ f, double scale,
+// per-triangle P1 test projection of point values (summed over the C chunks of
+// charges): out[t][k] = |t| sum_p w_p lambda_k(p) f[t][p] * scale
+__global__ void k_project2(int T, int C, const double *__restrict__ geo, const double *__restrict__ f, double scale,
                            double *__restrict__ triout)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
     double area = geo[(size_t)t * kGeo + 21];
     for (int h = 0; h < 2; ++h) {
-        const double *fp = f + (size_t)h * 6 * T + 6 * (size_t)t;
+        double fp[6];
+#pragma unroll
+        for (int p = 0; p < 6; ++p) {
+            fp[p] = 0.0;
+            for (int c = 0; c < C; ++c) fp[p] += f[((size_t)c * 2 + h) * 6 * T + 6 * (size_t)t + p];
+        }
         for (int k = 0; k < 3; ++k) {
             double s = 0.0;
 #pragma unroll
@@ -139,9 +167,15 @@ __global__ void k_gather_tri(int V, const int32_t *__restrict__ inc_ptr, const i
 void launch_rhs(DevMesh &d, int nq, const double *qbuf, double *b)
 {
     int T = d.hm.T, V = d.hm.V;
-    hipLaunchKernelGGL(k_source_field, dim3((6 * T + 255) / 256), dim3(256), 0, d.stream, T, nq, d.geo, qbuf,
-                       d.fpts);
-    hipLaunchKernelGGL(k_project2, dim3((T + 255) / 256), dim3(256), 0, d.stream, T, d.geo, d.fpts,
+    // chunks of charges while the points alone give less than about 8 wavefronts per
+    // SIMD, of at least 16 charges; their values go to the far field's partial sums,
+    // which hold at least 16 T doubles per source chunk
+    int C = std::max(1, std::min({8192 / ((6 * T + 63) / 64), nq / 16, d.S}));
+    const int chunk = (nq + C - 1) / C;
+    C = (nq + chunk - 1) / chunk;
+    double *f = C > 1 ? (double *)d.part : d.fpts;
+    hipLaunchKernelGGL(k_source_field, dim3((6 * T + 255) / 256, C), dim3(256), 0, d.stream, T, nq, chunk, d.geo, qbuf, f);
+    hipLaunchKernelGGL(k_project2, dim3((T + 255) / 256), dim3(256), 0, d.stream, T, C, d.geo, f,
                        kInv4Pi / d.prm.eps_in, d.triout);
     hipLaunchKernelGGL(k_gather_tri, dim3((V + 255) / 256), dim3(256), 0, d.stream, V, d.inc_ptr, d.inc_tk,
                        d.triout, b);
@@ -169,10 +203,59 @@ void formulation_rhs(DevMesh &d, int nq, const double *qbuf, double *b)
 }
 
 // --------------------------------------------------------- reaction potential
-// grid (point k, source chunk c); each block sums, over its chunk of source
-// triangles, G(x_k, y) b2 - dG/dn_y(x_k, y) b1 with the Laplace kernel (no 4 pi),
-// where b1 = w|s| phi(y), b2 = w|s| dphi(y) are the FP64 dynamic records of
-// the traces.  Fixed-shape tree reduction -> deterministic partials.
+// One wavefront per 64 points and chunk of source triangles: a lane per point, the
+// triangles through scalar loads.  Sums G(x_k, y) b2 - dG/dn_y(x_k, y) b1 with the
+// Laplace kernel (no 4 pi), where b1 = w|s| phi(y), b2 = w|s| dphi(y) are the FP64
+// dynamic records of the traces; d.n is the same for a triangle's six points.
+// Bound: the FP64 vector rate, 16 instructions per pair; with a block per point
+// and the lanes over the sources every block read all records again (36 GB of
+// cache traffic at 40500 triangles and 2000 points).
+__global__ __launch_bounds__(256) void k_reaction(int T, int npts, int C, int chunk, const double *__restrict__ pts,
+                                                  const double *__restrict__ stat, const double *__restrict__ dyn,
+                                                  double *__restrict__ part)
+{
+    const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int c = id % C, k = (id / C) * 64 + ((int)threadIdx.x & 63);
+    if ((id / C) * 64 >= npts) return;
+    const int kc = min(k, npts - 1);
+    const double x = pts[3 * kc], y = pts[3 * kc + 1], z = pts[3 * kc + 2];
+    const int s0 = c * chunk, s1 = min(T, s0 + chunk);
+    using CD = const __attribute__((address_space(4))) double *;
+    double acc = 0.0;
+    for (int s = s0; s < s1; ++s) {
+        CD st = (CD)(stat + (size_t)s * kStat), dy = (CD)(dyn + (size_t)s * kDyn);
+        double r2[6], ri[6], dn = 0.0, a = 0.0;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const double dx = x - st[3 * q], dyy = y - st[3 * q + 1], dz = z - st[3 * q + 2];
+            r2[q] = dx * dx + dyy * dyy + dz * dz;
+            if (q == 0) dn = dx * st[18] + dyy * st[19] + dz * st[20];
+        }
+        rsqrt3_n<6>(r2, ri);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            acc = fma(ri[q], dy[6 + q], acc);
+            a = fma(ri[q] * (ri[q] * ri[q]), dy[q], a);
+        }
+        acc = fma(-dn, a, acc);
+    }
+    if (k < npts) part[(size_t)k * C + c] = acc;
+}
+
+// out[k] = (sum over chunks of part[k C + c]) / (4 pi): one wavefront per point
+__global__ __launch_bounds__(256) void k_reaction_finish(int npts, int C, const double *__restrict__ part,
+                                                         double *__restrict__ out)
+{
+    const int k = blockIdx.x * 4 + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (k >= npts) return;
+    double s = 0.0;
+    for (int c = lane; c < C; c += 64) s += part[(size_t)k * C + c];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) out[k] = s * kInv4Pi;
+}
+
+// Fixed-shape tree reduction -> deterministic partials.
 constexpr int kRedBlock = 256;
 
 __device__ inline double block_sum(double v, double *sh)
@@ -186,29 +269,6 @@ __device__ inline double block_sum(double v, double *sh)
     double r = sh[0];
     __syncthreads();
     return r;
-}
-
-__global__ __launch_bounds__(kRedBlock) void k_reaction(int T, int chunk, const double *__restrict__ pts,
-                                                        const double *__restrict__ stat,
-                                                        const double *__restrict__ dyn, double *__restrict__ part)
-{
-    __shared__ double sh[kRedBlock];
-    int k = blockIdx.x, c = blockIdx.y;
-    double x = pts[3 * k], y = pts[3 * k + 1], z = pts[3 * k + 2];
-    int s0 = c * chunk, s1 = min(T, s0 + chunk);
-    double acc = 0.0;
-    for (int i = s0 * 6 + threadIdx.x; i < s1 * 6; i += kRedBlock) {
-        int s = i / 6, q = i - 6 * s;
-        const double *st = stat + (size_t)s * kStat;
-        const double *dy = dyn + (size_t)s * kDyn;
-        double dx = x - st[3 * q], dyy = y - st[3 * q + 1], dz = z - st[3 * q + 2];
-        double r2 = dx * dx + dyy * dyy + dz * dz;
-        double ri = 1.0 / sqrt(r2);
-        double dn = dx * st[18] + dyy * st[19] + dz * st[20];
-        acc += ri * dy[6 + q] - dn * ri * ri * ri * dy[q];
-    }
-    double tot = block_sum(acc, sh);
-    if (threadIdx.x == 0) part[(size_t)k * gridDim.y + c] = tot;
 }
 
 // Solid angle subtended by each triangle at point k (Van Oosterom-Strackee);
@@ -245,12 +305,25 @@ __global__ __launch_bounds__(kRedBlock) void k_solid_angle(int T, int chunk, con
 
 static int red_chunks(int T) { return T < 4096 ? 1 : (T + 4095) / 4096; }
 
-void launch_reaction(DevMesh &d, int nq, const double *qpts, double *out_part)
+// Source chunks of the reaction potential at npts points: about four wavefronts
+// per SIMD, chunks of at least 8 triangles, and at most the allocation-free entry
+// point's scratch for the partial sums (a function of T and npts alone, so both
+// entry points sum alike)
+int reaction_chunks(int T, int npts)
 {
-    int T = d.hm.T, C = red_chunks(T);
-    int chunk = (T + C - 1) / C;
-    hipLaunchKernelGGL(k_reaction, dim3(nq, C), dim3(kRedBlock), 0, d.stream, T, chunk, qpts, d.stat64, d.dyn64,
-                       out_part);
+    const int waves = (npts + 63) / 64;
+    const int most = std::max(1, (int)(kNoAllocScratchDoubles / (size_t)npts));
+    return std::max(1, std::min({4096 / waves, T / 8, most}));
+}
+
+// part: npts x reaction_chunks partial sums; out: npts potentials
+void launch_reaction(DevMesh &d, int npts, const double *pts, double *part, double *out)
+{
+    const int T = d.hm.T, C = reaction_chunks(T, npts), chunk = (T + C - 1) / C;
+    const long long waves = (long long)((npts + 63) / 64) * C;
+    hipLaunchKernelGGL(k_reaction, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, d.stream, T, npts, C, chunk, pts,
+                       d.stat64, d.dyn64, part);
+    hipLaunchKernelGGL(k_reaction_finish, dim3((npts + 3) / 4), dim3(256), 0, d.stream, npts, C, part, out);
     HIPCHECK(hipGetLastError());
 }
 
@@ -291,17 +364,6 @@ static double *noalloc_scratch()
     return addr[dev];
 }
 
-// out[k] = (sum over chunks c, in order, of part[k C + c]) / (4 pi): the same
-// sum, in the same order, as the host finish of pb_mesh_reaction_potential
-__global__ void k_reaction_finish(int npts, int C, const double *__restrict__ part, double *__restrict__ out)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= npts) return;
-    double s = 0.0;
-    for (int c = 0; c < C; ++c) s += part[(size_t)k * C + c];
-    out[k] = s * kInv4Pi;
-}
-
 void reaction_potential_noalloc(DevMesh &d, const double *traces, int npts, const double *pts, double *out,
                                 hipStream_t stream)
 {
@@ -317,9 +379,7 @@ void reaction_potential_noalloc(DevMesh &d, const double *traces, int npts, cons
         ~StreamSwap() { d.stream = keep; }
     } swap(d, stream);
     launch_source_prep(d, traces, false);
-    launch_reaction(d, npts, pts, part);
-    hipLaunchKernelGGL(k_reaction_finish, dim3((npts + 255) / 256), dim3(256), 0, d.stream, npts, C, part, out);
-    HIPCHECK(hipGetLastError());
+    launch_reaction(d, npts, pts, part, out);
 }
 
 }  // namespace pbm

@@ -358,7 +358,8 @@ void apply_operator(DevMesh &d, const double *x, double *y, int flags, hipStream
 void launch_rhs(DevMesh &d, int nq, const double *qbuf, double *b);
 // launch_rhs combined into the formulation's right-hand side rows
 void formulation_rhs(DevMesh &d, int nq, const double *qbuf, double *b);
-void launch_reaction(DevMesh &d, int nq, const double *qpts, double *out);
+int reaction_chunks(int T, int npts);
+void launch_reaction(DevMesh &d, int npts, const double *pts, double *part, double *out);
 void launch_inside_test(DevMesh &d, int nq, const double *qbuf, double *out);
 void launch_pair_blocks_subset(DevMesh &d, int n, const int32_t *t_sorted, const int32_t *s_sorted,
                                const int32_t *idx, const int count[4], double *out);

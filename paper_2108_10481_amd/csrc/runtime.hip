@@ -1410,12 +1410,11 @@ void charges_to_device(DevMesh &d, const pb_charges *c)
     HIPCHECK(hipMemcpyAsync(d.qbuf, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, d.stream));
 }
 
-static double *reduction_buffer(DevMesh &d, int npts)
+static double *reduction_buffer(DevMesh &d, size_t need)
 {
-    const int need = npts * reduction_chunks(d.hm.T);
-    if (need > d.redcap) {
+    if (need > (size_t)d.redcap) {
         d.red = (double *)d.alloc(sizeof(double) * need);
-        d.redcap = need;
+        d.redcap = (int)need;
     }
     return d.red;
 }
@@ -1423,7 +1422,7 @@ static double *reduction_buffer(DevMesh &d, int npts)
 void check_charges_inside(DevMesh &d, int nq)
 {
     const int C = reduction_chunks(d.hm.T);
-    double *part = reduction_buffer(d, nq);
+    double *part = reduction_buffer(d, (size_t)nq * C);
     launch_inside_test(d, nq, d.qbuf + 4 * (size_t)nq, part);
     std::vector<double> h((size_t)nq * C);
     HIPCHECK(hipMemcpyAsync(h.data(), part, sizeof(double) * h.size(), hipMemcpyDeviceToHost, d.stream));
@@ -1438,18 +1437,13 @@ void check_charges_inside(DevMesh &d, int nq)
 // phi_reac at npts device points (AoS) from the device traces u (2V)
 static void reaction_potential(DevMesh &d, const double *u, int npts, const double *pts_dev, double *out_host)
 {
-    const int C = reduction_chunks(d.hm.T);
+    const size_t C = (size_t)reaction_chunks(d.hm.T, npts);
     launch_source_prep(d, u, false);
-    double *part = reduction_buffer(d, npts);
-    launch_reaction(d, npts, pts_dev, part);
-    std::vector<double> h((size_t)npts * C);
-    HIPCHECK(hipMemcpyAsync(h.data(), part, sizeof(double) * h.size(), hipMemcpyDeviceToHost, d.stream));
+    double *part = reduction_buffer(d, (size_t)npts * (C + 1));
+    double *out = part + (size_t)npts * C;
+    launch_reaction(d, npts, pts_dev, part, out);
+    HIPCHECK(hipMemcpyAsync(out_host, out, sizeof(double) * npts, hipMemcpyDeviceToHost, d.stream));
     HIPCHECK(hipStreamSynchronize(d.stream));
-    for (int k = 0; k < npts; ++k) {
-        double s = 0.0;
-        for (int c = 0; c < C; ++c) s += h[(size_t)k * C + c];
-        out_host[k] = s * kInv4Pi;
-    }
 }
 
 static void rhs_device(DevMesh &d, int nq, double *b)
