@@ -54,6 +54,10 @@ struct Dense {
     // so each of the GEMM's loads reads 1 KB of consecutive bytes; refreshed
     // when the 16-bit copy is rewritten (the versions differ)
     uint16_t *A16t = nullptr;
+    // partial sums of products split over the columns, and the accurate batched
+    // product's x (split_space, k_batch.hip)
+    double *P64 = nullptr, *X64 = nullptr;
+    bool p64_failed = false;
     bool a16t_failed = false;      // no room for it: the GEMM reads the row-major copy
     unsigned a16_version = 0, a16t_version = 0;
 };

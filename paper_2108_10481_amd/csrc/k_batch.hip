@@ -24,8 +24,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-pb_status finish_result(DevMesh &d, const pb_charges *ch, const double *pb, double *u, int its, int outer,
-                        double t_rhs, double t_prec, double t_gmres, pb_result *res);
 void charges_to_device(DevMesh &d, const pb_charges *c);
 void check_charges_inside(DevMesh &d, int nq);
 
@@ -94,11 +92,15 @@ __global__ __launch_bounds__(256) void k_gemm16(int n, int V, size_t Vp, size_t 
 // in the first column block; lane l reads the 16 bytes at (tile nk + s) 512 +
 // 8 l, so a wavefront's load is 1 KB of consecutive bytes.  The MFMA sequence
 // and every lane's operands are those of k_gemm16<KIND, 1>, so the results are
-// bitwise the same.
+// bitwise the same (KS = 1).  KS > 1: a wavefront takes one of KS parts of the
+// steps and writes its partial sums to P[part][row][system] (k_join_parts adds
+// them): at 10242 vertices the 1281 row tiles alone leave most of the device's
+// wavefront slots empty, 345 us per product against 226 us in four parts.
 template <int KIND>
-__global__ __launch_bounds__(256) void k_gemm16t(int n, int V, int nk0, int nk, size_t ld,
+__global__ __launch_bounds__(256) void k_gemm16t(int n, int V, int nk0, int nk, size_t ld, int KS,
                                                  const uint16_t *__restrict__ At, const uint16_t *__restrict__ X,
-                                                 float i0, float i1, float i2, float i3, double *__restrict__ Y)
+                                                 float i0, float i1, float i2, float i3, double *__restrict__ Y,
+                                                 double *__restrict__ P)
 {
     const int lane = threadIdx.x & 63;
     const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6;
@@ -107,22 +109,115 @@ __global__ __launch_bounds__(256) void k_gemm16t(int n, int V, int nk0, int nk, 
     const int kq = (lane >> 4) * 8;
     const int cl = lane & 15;
     const uint16_t *xrow = X + (size_t)cl * ld + kq;
-    for (int tile = wave; tile < ntile; tile += nwave) {
+    for (int u = wave; u < ntile * KS; u += nwave) {
+        const int tile = u / KS, ks = u - tile * KS;
+        const int st0 = (int)((long long)nk * ks / KS), st1 = (int)((long long)nk * (ks + 1) / KS);
         const uint16_t *at = At + (size_t)tile * nk * 512 + 8 * lane;
         f32x4 c0 = f32x4{0.f, 0.f, 0.f, 0.f}, c1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-        for (int st = 0; st < nk0; ++st) c0 = mfma16<KIND>(at + (size_t)st * 512, xrow + (size_t)st * 32, c0);
+        for (int st = st0; st < min(st1, nk0); ++st) c0 = mfma16<KIND>(at + (size_t)st * 512, xrow + (size_t)st * 32, c0);
 #pragma unroll 4
-        for (int st = nk0; st < nk; ++st) c1 = mfma16<KIND>(at + (size_t)st * 512, xrow + (size_t)st * 32, c1);
+        for (int st = max(st0, nk0); st < st1; ++st) c1 = mfma16<KIND>(at + (size_t)st * 512, xrow + (size_t)st * 32, c1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = tile * 16 + 4 * (lane >> 4) + i;
             if (r < n) {
                 const bool top = r < V;
-                Y[(size_t)cl * n + r] = (double)c0[i] * (top ? i0 : i2) + (double)c1[i] * (top ? i1 : i3);
+                const double v = (double)c0[i] * (top ? i0 : i2) + (double)c1[i] * (top ? i1 : i3);
+                if (KS > 1) P[((size_t)ks * n + r) * 16 + cl] = v;
+                else Y[(size_t)cl * n + r] = v;
             }
         }
     }
+}
+
+// Y[s][r] = sum over the KS parts of P[part][r][s]
+__global__ void k_join_parts(int n, int nb, int KS, const double *__restrict__ P, double *__restrict__ Y)
+{
+    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (size_t)n * 16) return;
+    const int s = (int)(e & 15), r = (int)(e >> 4);
+    if (s >= nb) return;
+    double v = 0.0;
+    for (int k = 0; k < KS; ++k) v += P[(size_t)k * n * 16 + e];
+    Y[(size_t)s * n + r] = v;
+}
+
+// The accurate (FP32-stored) operator of the refinement sweeps on all 16 systems
+// in one pass over the matrix: Y = A X with FP64 vectors and sums on
+// v_mfma_f64_16x16x4 (lane l: A[row l%16][k l/16], B[k l/16][system l%16]; result
+// D[row l/16 + 4 v][system l%16], v = 0..3).  A wavefront takes 32 rows and one of
+// KS parts of the columns; per 32 columns a lane reads 32 bytes of its two rows
+// and eight x values, used for both.  Bound: the FP64 matrix rate and HBM alike
+// (16 FMAs per 4-byte entry); one product per system read the matrix 16 times:
+// at 10242 vertices 16 x 0.252 ms against 0.483 ms.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kHiRows = 2;   // 16-row tiles per wavefront
+__global__ __launch_bounds__(256) void k_gemm32(int n, size_t ld, int KS, const float *__restrict__ A,
+                                                const double *__restrict__ X, double *__restrict__ P)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, li = lane & 15;
+    const int u = blockIdx.x * 4 + ((int)threadIdx.x >> 6);
+    const int ntile = (n + 16 * kHiRows - 1) / (16 * kHiRows);
+    if (u >= ntile * KS) return;
+    const int tile = u / KS, ks = u - tile * KS, nst = (int)(ld / 32);
+    const int s0 = (int)((long long)nst * ks / KS), s1 = (int)((long long)nst * (ks + 1) / KS);
+    const float *row[kHiRows];
+    f64x4 c[kHiRows];
+#pragma unroll
+    for (int t = 0; t < kHiRows; ++t) {
+        // rows past n re-read row n-1; their results are dropped
+        row[t] = A + (size_t)min((tile * kHiRows + t) * 16 + li, n - 1) * ld + 8 * g;
+        c[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    }
+    const double *x = X + (size_t)(8 * g) * 16 + li;
+#pragma unroll 2
+    for (int st = s0; st < s1; ++st) {
+        f32x4 a[kHiRows][2];
+        double b[8];
+#pragma unroll
+        for (int t = 0; t < kHiRows; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) a[t][h] = __builtin_nontemporal_load((const f32x4 *)(row[t] + (size_t)st * 32) + h);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) b[e] = x[((size_t)st * 32 + e) * 16];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int t = 0; t < kHiRows; ++t)
+                c[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[t][e >> 2][e & 3], b[e], c[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < kHiRows; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = (tile * kHiRows + t) * 16 + g + 4 * v;
+            if (r < n) P[((size_t)ks * n + r) * 16 + li] = c[t][v];
+        }
+}
+
+// X[k][s] in the padded column layout, s < nb from the FP64 systems, zero otherwise
+__global__ void k_pad_hi(int V, int n, int nb, size_t Vp, size_t ld, const int32_t *__restrict__ vperm,
+                         const double *__restrict__ Xs, double *__restrict__ X)
+{
+    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= ld * 16) return;
+    const size_t k = e >> 4;
+    const int s = (int)(e & 15);
+    double v = 0.0;
+    if (s < nb) {
+        if (k < (size_t)V) v = Xs[(size_t)s * n + vperm[k]];
+        else if (k >= Vp && k < Vp + (size_t)V) v = Xs[(size_t)s * n + V + vperm[k - Vp]];
+    }
+    X[e] = v;
+}
+
+// R = PB - Z for every system
+__global__ void k_residual(size_t total, const double *__restrict__ PB, const double *__restrict__ Z,
+                           double *__restrict__ R)
+{
+    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < total) R[e] = PB[e] - Z[e];
 }
 
 // Row-major 16-bit copy -> tiled copy (k_gemm16t's operand order); rows past
@@ -167,9 +262,13 @@ __global__ void k_pad_batch(int V, int n, int nb, size_t Vp, size_t ld, int kind
     X16[(size_t)c * ld + k] = o;
 }
 
-// per (vertex i, system s): far part from Y16, near-field CSR product,
-// optional 2x2 preconditioner
-__global__ void k_gather_batch(int V, int n, int precond, const int32_t *__restrict__ row_ptr,
+// per vertex i and group of kGatherSys systems: far part from Y16, near-field CSR
+// product, optional 2x2 preconditioner.  Bound: the caches (a row's entries are
+// read once per group, the vectors at scattered vertices); one system per thread
+// read them 16 times, 57 us per product of 16 systems at 10242 vertices
+// against 20 us.
+constexpr int kGatherSys = 4;
+__global__ void k_gather_batch(int V, int n, int nb, int precond, const int32_t *__restrict__ row_ptr,
                                const int32_t *__restrict__ col, const double *__restrict__ N, int64_t nnz,
                                const double *__restrict__ pinv, const int32_t *__restrict__ vpos,
                                const double *__restrict__ Yfar, const double *__restrict__ X, double *__restrict__ Y)
@@ -177,26 +276,48 @@ __global__ void k_gather_batch(int V, int n, int precond, const int32_t *__restr
     // kRowLanes lanes per row, the same slot order and butterfly as k_gather
     const int i = (blockIdx.x * blockDim.x + threadIdx.x) / kRowLanes;
     const int c = threadIdx.x % kRowLanes;
-    const int s = blockIdx.y;
+    const int s0 = blockIdx.y * kGatherSys;
     if (i >= V) return;
-    const double *x = X + (size_t)s * n;
-    double n1 = 0.0, n2 = 0.0;
+    const double *x[kGatherSys];
+    double n1[kGatherSys], n2[kGatherSys];
+#pragma unroll
+    for (int q = 0; q < kGatherSys; ++q) {
+        x[q] = X + (size_t)min(s0 + q, nb - 1) * n;   // past the last: repeat it, dropped below
+        n1[q] = 0.0;
+        n2[q] = 0.0;
+    }
     for (int sl = row_ptr[i] + c; sl < row_ptr[i + 1]; sl += kRowLanes) {
         const int j = col[sl];
-        const double x1 = x[j], x2 = x[V + j];
-        n1 += N[sl] * x1 + N[nnz + sl] * x2;
-        n2 += N[2 * nnz + sl] * x1 + N[3 * nnz + sl] * x2;
+        const double a0 = N[sl], a1 = N[nnz + sl], a2 = N[2 * nnz + sl], a3 = N[3 * nnz + sl];
+#pragma unroll
+        for (int q = 0; q < kGatherSys; ++q) {
+            const double x1 = x[q][j], x2 = x[q][V + j];
+            n1[q] += a0 * x1 + a1 * x2;
+            n2[q] += a2 * x1 + a3 * x2;
+        }
     }
 #pragma unroll
-    for (int off = 1; off < kRowLanes; off <<= 1) {
-        n1 += __shfl_xor(n1, off);
-        n2 += __shfl_xor(n2, off);
-    }
-    if (c != 0) return;
+    for (int q = 0; q < kGatherSys; ++q)
+#pragma unroll
+        for (int off = 1; off < kRowLanes; off <<= 1) {
+            n1[q] += __shfl_xor(n1[q], off);
+            n2[q] += __shfl_xor(n2[q], off);
+        }
+    // lane c finishes system s0 + c
+    static_assert(kGatherSys == kRowLanes, "one lane of the row per system");
+    const int s = s0 + c;
+    if (s >= nb) return;
+    double m1 = n1[0], m2 = n2[0];
+#pragma unroll
+    for (int q = 1; q < kGatherSys; ++q)
+        if (c == q) {
+            m1 = n1[q];
+            m2 = n2[q];
+        }
     const int r = vpos[i];   // dense row order
     double y1 = Yfar[(size_t)s * n + r], y2 = Yfar[(size_t)s * n + V + r];
-    y1 += n1;
-    y2 += n2;
+    y1 += m1;
+    y2 += m2;
     if (precond) {
         const double *P = pinv + 4 * (size_t)i;
         const double z1 = P[0] * y1 + P[1] * y2, z2 = P[2] * y1 + P[3] * y2;
@@ -296,6 +417,70 @@ void destroy_batch(DevMesh &d)
     d.bw = nullptr;
 }
 
+// near field and preconditioner of nb systems after a dense product into Y16
+static void gather_all(DevMesh &d, int nb, const double *X, double *Y)
+{
+    const int V = d.hm.V, n = 2 * V;
+    Dense *D = d.dense;
+    const dim3 grid((V + 256 / kRowLanes - 1) / (256 / kRowLanes), (nb + kGatherSys - 1) / kGatherSys);
+    const bool mass = mass_mode(d);
+    hipLaunchKernelGGL(k_gather_batch, grid, dim3(256), 0, d.stream, V, n, nb, mass ? 0 : 1, d.row_ptr, d.col, d.N, d.nnz(),
+                       d.pinv, D->vpos, D->Y16, X, mass ? d.mtmp : Y);
+    if (mass) mass_precond(d, nb, d.mtmp, Y, DevCtl());
+}
+
+// Workspace of the split products (up to kMaxParts parts of n x 16 sums, and the
+// accurate product's x): allocated once where the handle's budget has room for
+// it, else the products stay unsplit and one per system.
+constexpr int kMaxParts = 8;
+static bool split_space(DevMesh &d)
+{
+    Dense *D = d.dense;
+    if (D->P64) return true;
+    if (D->p64_failed) return false;
+    const size_t n = 2 * (size_t)d.hm.V, need = sizeof(double) * 16 * (kMaxParts * n + D->ld);
+    D->p64_failed = true;
+    // leave what a later single solve takes: the Krylov basis and a few vectors
+    const size_t later = sizeof(double) * n * (std::max(d.opt.max_iter, d.opt.inner_max_iter) + 8) + ((size_t)32 << 20);
+    if (d.opt.memory_budget && d.bytes + need + later > d.opt.memory_budget) return false;
+    try {
+        double *p = (double *)d.alloc(need);
+        D->X64 = p + 16 * kMaxParts * n;
+        D->P64 = p;
+    } catch (const Error &) {
+        (void)hipGetLastError();
+        return false;
+    }
+    D->p64_failed = false;
+    return true;
+}
+// parts of the columns so that tiles x parts is about four wavefronts per SIMD
+static int parts_for(DevMesh &d, int tiles)
+{
+    const int KS = std::max(1, std::min(kMaxParts, (4096 + tiles - 1) / tiles));
+    return KS > 1 && split_space(d) ? KS : 1;
+}
+
+// Y = P^-1 A X with the accurate operator for nb systems: one pass over the
+// FP32 matrix (mixed modes), or one product per system
+static void apply_accurate(DevMesh &d, int nb, const double *X, double *Y)
+{
+    const int V = d.hm.V, n = 2 * V;
+    Dense *D = d.dense;
+    if (nb < 2 || !D->A32 || d.prof.on(0) || !D->Y16 || !split_space(d)) {
+        for (int s = 0; s < nb; ++s) apply_operator(d, X + (size_t)s * n, Y + (size_t)s * n, PB_APPLY_PRECOND, nullptr);
+        return;
+    }
+    const int ntile = (n + 16 * kHiRows - 1) / (16 * kHiRows), KS = parts_for(d, ntile);
+    hipLaunchKernelGGL(k_pad_hi, dim3((unsigned)((16 * D->ld + 255) / 256)), dim3(256), 0, d.stream, V, n, nb, D->Vp,
+                       D->ld, D->vperm, X, D->X64);
+    hipLaunchKernelGGL(k_gemm32, dim3((ntile * KS + 3) / 4), dim3(256), 0, d.stream, n, D->ld, KS, D->A32, D->X64, D->P64);
+    hipLaunchKernelGGL(k_join_parts, dim3((unsigned)((16 * (size_t)n + 255) / 256)), dim3(256), 0, d.stream, n, nb, KS,
+                       D->P64, D->Y16);
+    gather_all(d, nb, X, Y);
+    HIPCHECK(hipGetLastError());
+}
+
 // P^-1 A applied to nb systems: one MFMA GEMM on the 16-bit far field, or one
 // accurate product per system.
 static void apply_batch(DevMesh &d, int nb, const double *X, double *Y)
@@ -325,15 +510,19 @@ static void apply_batch(DevMesh &d, int nb, const double *X, double *Y)
             hipLaunchKernelGGL(k_tile16, dim3(8192), dim3(256), 0, d.stream, n, D->ld, ntile, nk, D->A16, D->A16t);
             D->a16t_version = D->a16_version;
         }
+        const int KS = D->A16t ? parts_for(d, ntile) : 1;
         auto launch = [&]() {
             if (D->A16t) {
-                const int nwg = std::min((ntile + 3) / 4, 4096);
+                const int nwg = std::min((ntile * KS + 3) / 4, 4096);
                 if (D->kind16 == 1)
-                    hipLaunchKernelGGL((k_gemm16t<1>), dim3(nwg), dim3(256), 0, d.stream, n, V, nk0, nk, D->ld,
-                                       D->A16t, D->X16, inv[0], inv[1], inv[2], inv[3], D->Y16);
+                    hipLaunchKernelGGL((k_gemm16t<1>), dim3(nwg), dim3(256), 0, d.stream, n, V, nk0, nk, D->ld, KS,
+                                       D->A16t, D->X16, inv[0], inv[1], inv[2], inv[3], D->Y16, D->P64);
                 else
-                    hipLaunchKernelGGL((k_gemm16t<2>), dim3(nwg), dim3(256), 0, d.stream, n, V, nk0, nk, D->ld,
-                                       D->A16t, D->X16, inv[0], inv[1], inv[2], inv[3], D->Y16);
+                    hipLaunchKernelGGL((k_gemm16t<2>), dim3(nwg), dim3(256), 0, d.stream, n, V, nk0, nk, D->ld, KS,
+                                       D->A16t, D->X16, inv[0], inv[1], inv[2], inv[3], D->Y16, D->P64);
+                if (KS > 1)
+                    hipLaunchKernelGGL(k_join_parts, dim3((unsigned)((16 * (size_t)n + 255) / 256)), dim3(256), 0,
+                                       d.stream, n, nb, KS, D->P64, D->Y16);
                 return;
             }
             const int nt2 = (n + 31) / 32;
@@ -357,14 +546,7 @@ static void apply_batch(DevMesh &d, int nb, const double *X, double *Y)
             HIPCHECK(hipEventRecord(e1, d.stream));
             pf.record(0, e0, e1, (double)n * n * 2.0 + kMaxBatch * (double)n * (2.0 + 8.0));
         }
-        if (mass_mode(d)) {
-            hipLaunchKernelGGL(k_gather_batch, dim3((V + 256 / kRowLanes - 1) / (256 / kRowLanes), nb), dim3(256), 0, d.stream, V, n, 0, d.row_ptr,
-                               d.col, d.N, d.nnz(), d.pinv, D->vpos, D->Y16, X, d.mtmp);
-            mass_precond(d, nb, d.mtmp, Y, DevCtl());
-        } else {
-            hipLaunchKernelGGL(k_gather_batch, dim3((V + 256 / kRowLanes - 1) / (256 / kRowLanes), nb), dim3(256), 0, d.stream, V, n, 1, d.row_ptr,
-                               d.col, d.N, d.nnz(), d.pinv, D->vpos, D->Y16, X, Y);
-        }
+        gather_all(d, nb, X, Y);
         HIPCHECK(hipGetLastError());
     } else {
         for (int s = 0; s < nb; ++s) apply_operator(d, X + (size_t)s * n, Y + (size_t)s * n, PB_APPLY_PRECOND, nullptr);
@@ -516,10 +698,10 @@ pb_status solve_multi(DevMesh &d, int n_sets, const pb_charges *sets, pb_result 
                     itot[s] += its[s];
                     outer[s] = k;
                     kr_axpy(st, n, 1.0, w.C + (size_t)s * n, w.U + (size_t)s * n);
-                    apply_operator(d, w.U + (size_t)s * n, w.R + (size_t)s * n, PB_APPLY_PRECOND, nullptr);
-                    kr_scale_copy(st, n, w.R + (size_t)s * n, -1.0, w.R + (size_t)s * n);
-                    kr_axpy(st, n, 1.0, w.PB + (size_t)s * n, w.R + (size_t)s * n);
                 }
+                apply_accurate(d, nb, w.U, w.Z);
+                hipLaunchKernelGGL(k_residual, dim3((unsigned)(((size_t)n * nb + 255) / 256)), dim3(256), 0, st,
+                                   (size_t)n * nb, w.PB, w.Z, w.R);
                 hipLaunchKernelGGL(k_bdots, dim3(1, nb), dim3(kDotThreads), 0, st, n, 1, w.R, w.R, w.kbuf, 1);
                 std::vector<double> r2(nb);
                 HIPCHECK(hipMemcpyAsync(r2.data(), w.kbuf, sizeof(double) * nb, hipMemcpyDeviceToHost, st));
@@ -543,9 +725,22 @@ pb_status solve_multi(DevMesh &d, int n_sets, const pb_charges *sets, pb_result 
         }
         HIPCHECK(hipStreamSynchronize(st));
         const double t3 = now_s();
+        // mixed modes: the final residuals of all systems in one accurate product
+        std::vector<double> rr;
+        if (D.A16) {
+            rr.resize(2 * (size_t)nb);
+            apply_accurate(d, nb, w.U, w.Z);
+            hipLaunchKernelGGL(k_residual, dim3((unsigned)(((size_t)n * nb + 255) / 256)), dim3(256), 0, st,
+                               (size_t)n * nb, w.PB, w.Z, w.R);
+            hipLaunchKernelGGL(k_bdots, dim3(1, nb), dim3(kDotThreads), 0, st, n, 1, w.R, w.R, w.kbuf, 2);
+            hipLaunchKernelGGL(k_bdots, dim3(1, nb), dim3(kDotThreads), 0, st, n, 1, w.PB, w.PB, w.kbuf + 1, 2);
+            HIPCHECK(hipMemcpyAsync(rr.data(), w.kbuf, sizeof(double) * 2 * nb, hipMemcpyDeviceToHost, st));
+            HIPCHECK(hipStreamSynchronize(st));
+        }
         for (int s = 0; s < nb; ++s) {
             pb_status r = finish_result(d, &sets[c0 + s], w.PB + (size_t)s * n, w.U + (size_t)s * n, itot[s], outer[s],
-                                        (t1 - t0) / nb, (t2 - t1) / nb, (t3 - t2) / nb, &out[c0 + s]);
+                                        (t1 - t0) / nb, (t2 - t1) / nb, (t3 - t2) / nb, &out[c0 + s],
+                                        rr.empty() ? nullptr : &rr[2 * s]);
             if (r < 0) return r;
             worst = std::max(worst, r);
         }

@@ -414,8 +414,9 @@ void check_charges_inside(DevMesh &d, int nq);
 constexpr size_t kNoAllocScratchDoubles = size_t(1) << 19;   // 4 MiB
 void reaction_potential_noalloc(DevMesh &d, const double *traces, int npts, const double *pts, double *out,
                                 hipStream_t stream);
+// norms2 (may be null): |residual|^2 and |pb|^2 if the caller has them
 pb_status finish_result(DevMesh &d, const pb_charges *ch, const double *pb, double *u, int its, int outer,
-                        double t_rhs, double t_prec, double t_gmres, pb_result *res);
+                        double t_rhs, double t_prec, double t_gmres, pb_result *res, const double *norms2 = nullptr);
 
 // Krylov kernels (k_krylov.hip)
 void kr_dots(hipStream_t s, int n, int nvec, const double *V, size_t ldv, const double *w, double *out);

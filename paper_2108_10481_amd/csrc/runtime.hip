@@ -1454,17 +1454,22 @@ static void rhs_device(DevMesh &d, int nq, double *b)
 // Accurate preconditioned residual, reaction potential and Delta G for the
 // solution u of one charge set; fills *res.
 pb_status finish_result(DevMesh &d, const pb_charges *ch, const double *pb, double *u, int its, int outer,
-                        double t_rhs, double t_prec, double t_gmres, pb_result *res)
+                        double t_rhs, double t_prec, double t_gmres, pb_result *res, const double *norms2)
 {
     TraceRange range("pb.dG");
     const int V = d.hm.V, n = 2 * V;
     const double t3 = now();
-        apply_operator(d, u, d.ztmp, PB_APPLY_PRECOND, nullptr);
-    kr_axpy(d.stream, n, -1.0, pb, d.ztmp);
-    kr_dots(d.stream, n, 1, d.ztmp, n, d.ztmp, d.red1);
-    kr_dots(d.stream, n, 1, pb, n, pb, d.red1 + 1);
     double rr[2];
-    HIPCHECK(hipMemcpyAsync(rr, d.red1, sizeof(rr), hipMemcpyDeviceToHost, d.stream));
+    if (norms2) {
+        rr[0] = norms2[0];
+        rr[1] = norms2[1];
+    } else {
+        apply_operator(d, u, d.ztmp, PB_APPLY_PRECOND, nullptr);
+        kr_axpy(d.stream, n, -1.0, pb, d.ztmp);
+        kr_dots(d.stream, n, 1, d.ztmp, n, d.ztmp, d.red1);
+        kr_dots(d.stream, n, 1, pb, n, pb, d.red1 + 1);
+        HIPCHECK(hipMemcpyAsync(rr, d.red1, sizeof(rr), hipMemcpyDeviceToHost, d.stream));
+    }
     // exterior unknowns -> interior traces (interface conditions)
     if (d.fm.exterior) kr_scale_copy(d.stream, V, u + V, d.prm.eps_out / d.prm.eps_in, u + V);
     charges_to_device(d, ch);
