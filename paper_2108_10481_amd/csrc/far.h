@@ -22,6 +22,34 @@ __device__ __forceinline__ double rsqrt_r(double x)
 __device__ __forceinline__ float expneg(float kl, float r) { return __builtin_amdgcn_exp2f(-kl * r); }
 __device__ __forceinline__ double expneg(double k, double r) { return exp(-k * r); }
 
+// 16 x 16 matrix tiles of v_mfma_f32_16x16x4: lane l gives row (column) l mod 16,
+// k = l / 16, and holds column l mod 16 of the rows 4 (l / 16) + v
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Sum of 16 values per lane over the four 16-lane rows of the wavefront: v_m of
+// all rows end as w_(m mod 4) of row m / 4 (v_permlane32_swap and
+// v_permlane16_swap exchange half-wavefronts and rows of two registers)
+__device__ __forceinline__ f32x4 lane_rows_sum(const float (&v)[16])
+{
+    float u[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[m]), __float_as_uint(v[m + 8]), false, false);
+        u[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    f32x4 w;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[m]), __float_as_uint(u[m + 4]), false, false);
+        w[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    return w;
+}
+
 template <typename R>
 struct FarCoef {
     R kappa;   // screening
@@ -213,7 +241,6 @@ __device__ __forceinline__ void finish_group(int t, int l, bool ok, int T, int S
 // tile record of the symmetric split: centre 3, radius, largest distance of a
 // quadrature point of one of its triangles from that triangle's centroid
 constexpr int kTileRec = 5;
-constexpr int kSymTile = 64;   // triangles per tile of the symmetric split
 
 // symmetric split (ranges of rt tiles, nr ranges, nz parts of each item): target
 // t's nr + 1 slots per part z, the target-side slots z nr + b of the source ranges
@@ -323,6 +350,13 @@ inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
         else if (form == 3) CALL((KERNEL<3, false>))                                           \
         else CALL((KERNEL<4, false>))                                                          \
     }
+
+// Tiles I, J are apart when their centres are at least kSymApart times the sum
+// of their radii apart: then r >= (kSymApart - 1)(rad_I + rad_J) and the terms of
+// r^2 that cancel, 2 |X| |Y|, are a small multiple of r^2
+constexpr double kSymApart = 1.25;
+
+void launch_sym_list(DevMesh &d, const int4 *items, int nitems, const int2 *entries, const double *tiles, float *slots);
 
 constexpr int kSymForms = 4;
 constexpr int kSymFormOf[kSymForms] = {0, 1, 3, 4};

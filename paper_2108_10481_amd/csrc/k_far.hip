@@ -682,6 +682,10 @@ void launch_far_finish(DevMesh &d, bool fp32)
         launch_far_sym_finish(d);   // the symmetric far field's slots
         return;
     }
+    if (d.tree && d.far_rule == 0 && tree_splits(*d.tree) == 0) {
+        launch_tree_finish(d);
+        return;
+    }
     const int T = d.hm.T;
     dim3 grid((unsigned)(((size_t)T * kFinishLanes + 255) / 256)), block(256);
     const FormCoef &f = d.fm;

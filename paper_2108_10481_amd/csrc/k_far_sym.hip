@@ -53,12 +53,6 @@
 namespace pbm {
 
 constexpr int kSymWaves = 4;   // wavefronts per block, 16 rows of the target tile each
-// Tiles I, J are apart when their centres are at least kSymApart times the sum
-// of their radii apart: then r >= (kSymApart - 1)(rad_I + rad_J) and the terms of
-// r^2 that cancel, 2 |X| |Y|, are a small multiple of r^2
-constexpr double kSymApart = 1.25;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 // LDS of one block: the columns (sources of tile J) and per wavefront the rows
 // (its 16 targets), relative to tile J's centre
 struct SymCols {
@@ -81,26 +75,6 @@ struct SymLds {
     int item;
 };
 
-// Sum of 16 values per lane over the four 16-lane rows of the wavefront: v_m of
-// all rows end as w_(m mod 4) of row m / 4 (v_permlane32_swap and
-// v_permlane16_swap exchange half-wavefronts and rows of two registers)
-__device__ __forceinline__ f32x4 rows_sum16(const float (&v)[16])
-{
-    float u[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[m]), __float_as_uint(v[m + 8]), false, false);
-        u[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    f32x4 w;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[m]), __float_as_uint(u[m + 4]), false, false);
-        w[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    return w;
-}
-
 // sum over the 16 lanes of a row, in every lane of it
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float x)
@@ -110,11 +84,6 @@ __device__ __forceinline__ float dpp_add(float x)
 __device__ __forceinline__ float row_sum(float x)
 {
     return dpp_add<0x121>(dpp_add<0x122>(dpp_add<0x124>(dpp_add<0x128>(x))));   // row_ror 8, 4, 2, 1
-}
-
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 // One wavefront's 16 targets against one group of 16 sources (columns col0..):
@@ -265,7 +234,70 @@ __device__ __forceinline__ void sym_block(const SymCoef<float> &cf, const SymCol
             }
         }
     }
-    src = rows_sum16(acc);
+    src = lane_rows_sum(acc);
+}
+
+// Staging of one column (source triangle sj, zero weights unless `in`) per lane,
+// relative to the centre c of its tile: wavefronts 0..2 two points each,
+// wavefront 3 the rest
+template <int FORM, typename IP, typename DP, typename RP>
+__device__ __forceinline__ void sym_cols(const SymCoef<float> &cf, SymCols &C, int w, int lane, int sj, bool in,
+                                         const double (&c)[3], IP __restrict__ tri, DP __restrict__ stat, RP __restrict__ dyn)
+{
+    const double s = cf.s;
+    const auto ss = stat + (size_t)sj * kStat;
+    const auto sd = dyn + (size_t)sj * kDyn;
+    if (w < 3) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int q = 2 * w + k;
+            const double yx = (ss[3 * q] - c[0]) * s, yy = (ss[3 * q + 1] - c[1]) * s, yz = (ss[3 * q + 2] - c[2]) * s;
+            C.bq[q][lane] = f32x4{(float)(-2.0 * yx), (float)(-2.0 * yy), (float)(-2.0 * yz),
+                                  (float)(yx * yx + yy * yy + yz * yz)};
+            const float b1 = in ? sd[q] : 0.0f, b2 = in ? sd[6 + q] : 0.0f;
+            // FORM 0: the weights of R3, 1/r, E, e/r; else those of K, V, T and D's normal part
+            C.w[q][lane] = FORM == 0 ? f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b1, cf.cD * b2}
+                                     : f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b2, cf.kD * b1};
+        }
+    } else {
+        const double nx = ss[18], ny = ss[19], nz = ss[20];
+        const double os = (ss[21] - (c[0] * nx + c[1] * ny + c[2] * nz)) * s;
+        C.bn[lane] = f32x4{(float)nx, (float)ny, (float)nz, (float)-os};
+        if (FORM >= 1) C.curl[lane] = in ? f32x4{sd[12], sd[13], sd[14], 0.0f} : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        C.id[0][lane] = in ? tri[3 * sj] : -1;
+        C.id[1][lane] = in ? tri[3 * sj + 1] : -1;
+        C.id[2][lane] = in ? tri[3 * sj + 2] : -1;
+    }
+}
+
+// ... and of a wavefront's 16 rows (records ts, td of the lane's row l mod 16, zero
+// weights unless `in`): A, A2 the matrix operands
+template <typename DP, typename RP>
+__device__ __forceinline__ void sym_rows(const SymCoef<float> &cf, SymRows &R, int lane, bool in, const double (&c)[3],
+                                         DP ts, RP td, float (&A)[6], float &A2)
+{
+    const int g = lane >> 4, li = lane & 15;
+    const double s = cf.s;
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+        const double cg = g == 0 ? c[0] : g == 1 ? c[1] : c[2];
+        const float xs = (float)((ts[3 * p + (g < 3 ? g : 2)] - cg) * s);
+        A[p] = g < 3 ? xs : 1.0f;
+        if (g < 3) R.x[p][g][li] = xs;
+    }
+    A2 = g < 3 ? 0.5f * (float)ts[18 + (g < 3 ? g : 2)] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int p = g + 4 * k;
+        if (p < 6) {
+            const double x = (ts[3 * p] - c[0]) * s, y = (ts[3 * p + 1] - c[1]) * s, z = (ts[3 * p + 2] - c[2]) * s;
+            R.x2[p][li] = (float)(x * x + y * y + z * z);
+        } else if (p == 6) {
+            R.o[li] = (float)((ts[21] - (c[0] * ts[18] + c[1] * ts[19] + c[2] * ts[20])) * s);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) R.d[4 * g + k][li] = in ? td[4 * g + k] : 0.0f;
 }
 
 // Tile records (kTileRec): centre of the bounding box of the tile's (at most 64)
@@ -322,153 +354,123 @@ __global__ __launch_bounds__(64) void k_sym_tiles(int T, const double *__restric
     }
 }
 
+// Row tile I against nk column tiles by one block: tile_of(k) the k-th, src_slot(k,
+// sj, cl) where its triangle sj (column cl) takes its 16 sums (null: nowhere;
+// added to what is there if `add`), row_slot(t) where triangle t of I takes its
+template <int FORM, bool K0, typename IP, typename DP, typename RP, typename TileOf, typename SrcSlot, typename RowSlot>
+__device__ __forceinline__ void sym_row(const SymCoef<float> &cf, IP __restrict__ tri, DP __restrict__ stat,
+                                        DP __restrict__ tiles, RP __restrict__ dyn, int T, int I, int nk, TileOf tile_of,
+                                        SrcSlot src_slot, bool add, RowSlot row_slot, SymLds &L)
+{
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int g = lane >> 4, li = lane & 15;
+    SymRows &R = L.r[w];
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const int t = 64 * I + 16 * w + li;      // the lane's target triangle as an operand row
+    const int tc = min(t, T - 1);
+    const auto ts = stat + (size_t)tc * kStat;
+    const auto td = dyn + (size_t)tc * kDyn;
+    f32x4 a1[6], a2[6], W[3];
+#pragma unroll
+    for (int p = 0; p < 6; ++p) a1[p] = a2[p] = zero;
+    W[0] = W[1] = W[2] = zero;
+    for (int k = 0; k < nk; ++k) {
+        const int J = tile_of(k);
+        const double cx = tiles[kTileRec * (size_t)J], cy = tiles[kTileRec * (size_t)J + 1], cz = tiles[kTileRec * (size_t)J + 2];
+        const double c[3] = {cx, cy, cz};
+        const int sj = 64 * J + lane;
+        sym_cols<FORM>(cf, L.c, w, lane, min(sj, T - 1), sj < T, c, tri, stat, dyn);
+        float A[6], A2;
+        sym_rows(cf, R, lane, t < T, c, ts, td, A, A2);
+        __syncthreads();
+        // well separated: |X| |Y| stays of the order of r^2
+        const double dx = tiles[kTileRec * (size_t)I] - cx, dy = tiles[kTileRec * (size_t)I + 1] - cy, dz = tiles[kTileRec * (size_t)I + 2] - cz;
+        const double reach = kSymApart * (tiles[kTileRec * (size_t)I + 3] + tiles[kTileRec * (size_t)J + 3]);
+        const bool near = dx * dx + dy * dy + dz * dz < reach * reach;
+        if (!near) {
+            const bool live[4] = {true, true, true, true};
+            for (int cb = 0; cb < 4; ++cb) {
+                f32x4 src;
+                sym_block<FORM, K0, false>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
+                L.out[w][16 * cb + li][g] = src;
+            }
+        } else {
+            int tv[4][3];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int tr = 64 * I + 16 * w + 4 * g + v, trc = min(tr, T - 1);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) tv[v][k] = tr < T ? tri[3 * trc + k] : -1;
+            }
+            for (int cb = 0; cb < 4; ++cb) {
+                f32x4 src = zero;
+                if (I != J || cb >= w) {   // uniform: below the diagonal every pair has been met
+                    const int j0 = L.c.id[0][16 * cb + li], j1 = L.c.id[1][16 * cb + li], j2 = L.c.id[2][16 * cb + li];
+                    bool live[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        bool m = (j0 >= 0) & (tv[v][0] >= 0);
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) m = m & (tv[v][k] != j0) & (tv[v][k] != j1) & (tv[v][k] != j2);
+                        if (I == J) m = m & (16 * w + 4 * g + v < 16 * cb + li);
+                        live[v] = m;
+                    }
+                    sym_block<FORM, K0, true>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
+                }
+                L.out[w][16 * cb + li][g] = src;
+            }
+        }
+        __syncthreads();
+        // the four wavefronts' source-side sums, in order, onto the slot (the item's
+        // earlier target tiles came before)
+        {
+            const int cl = tid >> 2, m = tid & 3, sj = 64 * J + cl;
+            float *o = sj < T ? src_slot(k, sj, cl) : nullptr;
+            if (o) {
+                f32x4 *so = (f32x4 *)o + m;
+                f32x4 v = add ? *so : zero;
+#pragma unroll
+                for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][m];
+                *so = v;
+            }
+        }
+    }
+    // target-side sums over the 16 columns of each row of lanes
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        float o[16];
+#pragma unroll
+        for (int p = 0; p < 6; ++p) {
+            o[p] = row_sum(a1[p][v]);
+            o[6 + p] = row_sum(a2[p][v]);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) o[12 + k] = FORM == 0 ? 0.0f : row_sum(W[k][v]);
+        o[15] = 0.0f;
+        const int tr = 64 * I + 16 * w + 4 * g + v;
+        if (li == 0 && tr < T) {
+            f32x4 *fo = (f32x4 *)row_slot(tr);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) fo[k] = f32x4{o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
+        }
+    }
+}
+
 // Item (a, b) of one mesh by one block; part holds the 2 nr slots
 template <int FORM, bool K0, typename IP, typename DP, typename RP>
 __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict__ tri, DP __restrict__ stat,
                                          DP __restrict__ tiles, RP __restrict__ dyn, int T, int rt, int nr, int a, int b,
                                          float *__restrict__ part, SymLds &L)
 {
-    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int g = lane >> 4, li = lane & 15;
     const int ntile = (T + 63) / 64;
     const int I0 = a * rt, I1 = min(ntile, I0 + rt);
     const int J0 = b * rt, J1 = min(ntile, J0 + rt);
-    SymRows &R = L.r[w];
-    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int I = I0; I < I1; ++I) {
-        const int t = 64 * I + 16 * w + li;      // the lane's target triangle as an operand row
-        const int tc = min(t, T - 1);
-        const auto ts = stat + (size_t)tc * kStat;
-        const auto td = dyn + (size_t)tc * kDyn;
-        f32x4 a1[6], a2[6], W[3];
-#pragma unroll
-        for (int p = 0; p < 6; ++p) a1[p] = a2[p] = zero;
-        W[0] = W[1] = W[2] = zero;
-        for (int J = a == b ? I : J0; J < J1; ++J) {
-            const double cx = tiles[kTileRec * (size_t)J], cy = tiles[kTileRec * (size_t)J + 1], cz = tiles[kTileRec * (size_t)J + 2];
-            const double c[3] = {cx, cy, cz};
-            const double s = cf.s;
-            // columns: wavefronts 0..2 two points each, wavefront 3 the rest
-            {
-                const int sj = min(64 * J + lane, T - 1);
-                const bool in = 64 * J + lane < T;   // past the end: the last triangle with zero weights
-                const auto ss = stat + (size_t)sj * kStat;
-                const auto sd = dyn + (size_t)sj * kDyn;
-                if (w < 3) {
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const int q = 2 * w + k;
-                        const double yx = (ss[3 * q] - cx) * s, yy = (ss[3 * q + 1] - cy) * s, yz = (ss[3 * q + 2] - cz) * s;
-                        L.c.bq[q][lane] = f32x4{(float)(-2.0 * yx), (float)(-2.0 * yy), (float)(-2.0 * yz),
-                                                (float)(yx * yx + yy * yy + yz * yz)};
-                        const float b1 = in ? sd[q] : 0.0f, b2 = in ? sd[6 + q] : 0.0f;
-                        // FORM 0: the weights of R3, 1/r, E, e/r; else those of K, V, T and D's normal part
-                        L.c.w[q][lane] = FORM == 0 ? f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b1, cf.cD * b2}
-                                                   : f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b2, cf.kD * b1};
-                    }
-                } else {
-                    const double nx = ss[18], ny = ss[19], nz = ss[20];
-                    const double os = (ss[21] - (cx * nx + cy * ny + cz * nz)) * s;
-                    L.c.bn[lane] = f32x4{(float)nx, (float)ny, (float)nz, (float)-os};
-                    if (FORM >= 1) L.c.curl[lane] = in ? f32x4{sd[12], sd[13], sd[14], 0.0f} : zero;
-                    L.c.id[0][lane] = in ? tri[3 * sj] : -1;
-                    L.c.id[1][lane] = in ? tri[3 * sj + 1] : -1;
-                    L.c.id[2][lane] = in ? tri[3 * sj + 2] : -1;
-                }
-            }
-            // rows of this wavefront
-            float A[6], A2;
-#pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                const double cg = g == 0 ? c[0] : g == 1 ? c[1] : c[2];
-                const float xs = (float)((ts[3 * p + (g < 3 ? g : 2)] - cg) * s);
-                A[p] = g < 3 ? xs : 1.0f;
-                if (g < 3) R.x[p][g][li] = xs;
-            }
-            A2 = g < 3 ? 0.5f * (float)ts[18 + (g < 3 ? g : 2)] : 0.0f;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int p = g + 4 * k;
-                if (p < 6) {
-                    const double x = (ts[3 * p] - cx) * s, y = (ts[3 * p + 1] - cy) * s, z = (ts[3 * p + 2] - cz) * s;
-                    R.x2[p][li] = (float)(x * x + y * y + z * z);
-                } else if (p == 6) {
-                    R.o[li] = (float)((ts[21] - (cx * ts[18] + cy * ts[19] + cz * ts[20])) * s);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) R.d[4 * g + k][li] = t < T ? td[4 * g + k] : 0.0f;
-            __syncthreads();
-            // well separated: |X| |Y| stays of the order of r^2
-            const double dx = tiles[kTileRec * (size_t)I] - cx, dy = tiles[kTileRec * (size_t)I + 1] - cy, dz = tiles[kTileRec * (size_t)I + 2] - cz;
-            const double reach = kSymApart * (tiles[kTileRec * (size_t)I + 3] + tiles[kTileRec * (size_t)J + 3]);
-            const bool near = dx * dx + dy * dy + dz * dz < reach * reach;
-            if (!near) {
-                const bool live[4] = {true, true, true, true};
-                for (int cb = 0; cb < 4; ++cb) {
-                    f32x4 src;
-                    sym_block<FORM, K0, false>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
-                    L.out[w][16 * cb + li][g] = src;
-                }
-            } else {
-                int tv[4][3];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int tr = 64 * I + 16 * w + 4 * g + v, trc = min(tr, T - 1);
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) tv[v][k] = tr < T ? tri[3 * trc + k] : -1;
-                }
-                for (int cb = 0; cb < 4; ++cb) {
-                    f32x4 src = zero;
-                    if (I != J || cb >= w) {   // uniform: below the diagonal every pair has been met
-                        const int j0 = L.c.id[0][16 * cb + li], j1 = L.c.id[1][16 * cb + li], j2 = L.c.id[2][16 * cb + li];
-                        bool live[4];
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            bool m = (j0 >= 0) & (tv[v][0] >= 0);
-#pragma unroll
-                            for (int k = 0; k < 3; ++k) m = m & (tv[v][k] != j0) & (tv[v][k] != j1) & (tv[v][k] != j2);
-                            if (I == J) m = m & (16 * w + 4 * g + v < 16 * cb + li);
-                            live[v] = m;
-                        }
-                        sym_block<FORM, K0, true>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
-                    }
-                    L.out[w][16 * cb + li][g] = src;
-                }
-            }
-            __syncthreads();
-            // the four wavefronts' source-side sums, in order, onto the slot (the item's
-            // earlier target tiles came before)
-            {
-                const int cl = tid >> 2, k = tid & 3, sj = 64 * J + cl;
-                if (sj < T) {
-                    f32x4 *so = (f32x4 *)(part + ((size_t)(nr + a) * T + sj) * 16) + k;
-                    f32x4 v = I == I0 ? zero : *so;
-#pragma unroll
-                    for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][k];
-                    *so = v;
-                }
-            }
-        }
-        // target-side sums over the 16 columns of each row of lanes
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            float o[16];
-#pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                o[p] = row_sum(a1[p][v]);
-                o[6 + p] = row_sum(a2[p][v]);
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) o[12 + k] = FORM == 0 ? 0.0f : row_sum(W[k][v]);
-            o[15] = 0.0f;
-            const int tr = 64 * I + 16 * w + 4 * g + v;
-            if (li == 0 && tr < T) {
-                f32x4 *fo = (f32x4 *)(part + ((size_t)b * T + tr) * 16);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) fo[k] = f32x4{o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
-            }
-        }
+        const int first = a == b ? I : J0;
+        // the item's earlier target tiles came before
+        sym_row<FORM, K0>(cf, tri, stat, tiles, dyn, T, I, J1 - first, [&](int k) { return first + k; },
+                          [&](int k, int sj, int cl) { return part + ((size_t)(nr + a) * T + sj) * 16; }, I != I0,
+                          [&](int tr) { return part + ((size_t)b * T + tr) * 16; }, L);
     }
 }
 
@@ -519,6 +521,30 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym_batch(const FarRe
         if (rq.skip && *rq.skip) continue;
         sym_item<FORM, K0>(rq.sc, rq.tri, rq.stat64, rq.tiles, rq.dyn, rq.T, rq.rt, rq.nr, it.y, it.z, rq.part, lds);
     }
+}
+
+// Listed pairs of tiles (the treecode's direct part): item {row tile I, first and
+// end entry, slot}, entry {column tile J, slot or -1}.  The item's slot takes I's
+// sums over its entries, an entry's slot those of its column tile (-1: dropped,
+// that tile meets I through proxies).
+template <int FORM, bool K0>
+__global__ __launch_bounds__(64 * kSymWaves, 2) void k_sym_list(int T, SymCoef<float> cf, const int32_t *__restrict__ tri,
+                                                               const double *__restrict__ stat,
+                                                               const double *__restrict__ tiles,
+                                                               const float *__restrict__ dyn,
+                                                               const int4 *__restrict__ items,
+                                                               const int2 *__restrict__ entries,
+                                                               float *__restrict__ slots, DevCtl ctl)
+{
+    __shared__ SymLds lds;
+    if (ctl_skip(ctl)) return;
+    const int4 it = items[blockIdx.x];
+    sym_row<FORM, K0>(cf, tri, stat, tiles, dyn, T, it.x, it.z - it.y, [&](int k) { return entries[it.y + k].x; },
+                      [&](int k, int sj, int cl) {
+                          const int slot = entries[it.y + k].y;
+                          return slot < 0 ? nullptr : slots + ((size_t)slot * kSymTile + cl) * 16;
+                      },
+                      false, [&](int tr) { return slots + ((size_t)it.w * kSymTile + tr - kSymTile * it.x) * 16; }, lds);
 }
 
 // kFinishLanes lanes per triangle over its nr + 1 slots, then the test
@@ -639,6 +665,18 @@ void launch_far_sym(DevMesh &d)
                        d.stat64, d.sym_tiles, d.dyn32, d.sym_items, d.sym_nitems, d.sym_next, (float *)d.part,  \
                        d.ctl);
     SYM_PICK(k_far_sym, form, k0, SYM_RUN)
+    HIPCHECK(hipGetLastError());
+}
+
+void launch_sym_list(DevMesh &d, const int4 *items, int nitems, const int2 *entries, const double *tiles, float *slots)
+{
+    SymCoef<float> cf;
+    const int form = sym_coef(d, cf);
+    const bool k0 = !(d.prm.kappa > 0.0);
+#define SYM_RUN_LIST(KF)                                                                                           \
+    hipLaunchKernelGGL(KF, dim3(nitems), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, cf, d.tri, d.stat64, tiles, d.dyn32, \
+                       items, entries, slots, d.ctl);
+    SYM_PICK(k_sym_list, form, k0, SYM_RUN_LIST)
     HIPCHECK(hipGetLastError());
 }
 

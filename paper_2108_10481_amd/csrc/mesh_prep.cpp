@@ -122,7 +122,61 @@ static void parallel_chunks(int n, int nw, F &&fn)
     if (err) std::rethrow_exception(err);
 }
 
-void build_host_mesh(const pb_mesh *m, HostMesh &hm)
+// Reorders `key` (Morton code and triangle number) by a balanced k-d tree of the
+// centroids: a node of more than `tile` triangles is split at half of its tiles
+// (tile_split) along the longest side of its centroids' box, ties by key.
+static void kd_order(const HostMesh &hm, const int32_t *tri, int tile, std::vector<uint64_t> &key)
+{
+    const int T = (int)key.size();
+    struct Rec {
+        double x[3];
+        uint64_t key;
+    };
+    std::vector<Rec> rec(T);
+    for (int t = 0; t < T; ++t) {
+        rec[t].key = key[t];
+        const int32_t *v = tri + 3 * (size_t)(key[t] & 0xffffffffu);
+        for (int c = 0; c < 3; ++c) {
+            rec[t].x[c] = hm.xyz[3 * (size_t)v[0] + c] + hm.xyz[3 * (size_t)v[1] + c] + hm.xyz[3 * (size_t)v[2] + c];
+        }
+    }
+    // level by level, the nodes of a level on several threads
+    std::vector<std::pair<int, int>> level(1, {0, T}), next;
+    while (!level.empty()) {
+        const int n = (int)level.size();
+        parallel_chunks(n, std::min(n, prep_workers(T, kPrepMinRows)), [&](int, int b, int e) {
+            for (int i = b; i < e; ++i) {
+                const int lo = level[i].first, hi = level[i].second;
+                if (hi - lo <= tile) continue;
+                double mn[3], mx[3];
+                for (int c = 0; c < 3; ++c) mn[c] = mx[c] = rec[lo].x[c];
+                for (int t = lo; t < hi; ++t)
+                    for (int c = 0; c < 3; ++c) {
+                        mn[c] = std::min(mn[c], rec[t].x[c]);
+                        mx[c] = std::max(mx[c], rec[t].x[c]);
+                    }
+                int ax = 0;
+                for (int c = 1; c < 3; ++c)
+                    if (mx[c] - mn[c] > mx[ax] - mn[ax]) ax = c;
+                std::nth_element(rec.begin() + lo, rec.begin() + lo + tile_split(hi - lo, tile), rec.begin() + hi,
+                                 [ax](const Rec &p, const Rec &q) { return p.x[ax] != q.x[ax] ? p.x[ax] < q.x[ax] : p.key < q.key; });
+            }
+        });
+        next.clear();
+        for (auto [lo, hi] : level)
+            if (hi - lo > tile) {
+                const int m = lo + tile_split(hi - lo, tile);
+                next.push_back({lo, m});
+                next.push_back({m, hi});
+            }
+        level.swap(next);
+    }
+    // inside a tile in Morton order
+    for (int t = 0; t < T; ++t) key[t] = rec[t].key;
+    for (int b = 0; b < T; b += tile) std::sort(key.begin() + b, key.begin() + std::min(T, b + tile));
+}
+
+void build_host_mesh(const pb_mesh *m, HostMesh &hm, int tile)
 {
     if (!m || !m->xyz || !m->tri) fail(PB_E_INVALID_ARG, "mesh pointers must not be NULL");
     const int V = m->n_vertices, T = m->n_triangles;
@@ -195,8 +249,13 @@ void build_host_mesh(const pb_mesh *m, HostMesh &hm)
     std::sort(key.begin(), key.end());
     hm.perm.resize(T);
     hm.iperm.resize(T);
-    hm.mkey.resize(T);
-    for (int t = 0; t < T; ++t) hm.mkey[t] = (uint32_t)(key[t] >> 32);
+    hm.tile = tile;
+    if (tile > 0) {
+        kd_order(hm, tri, tile, key);
+    } else {
+        hm.mkey.resize(T);
+        for (int t = 0; t < T; ++t) hm.mkey[t] = (uint32_t)(key[t] >> 32);
+    }
     hm.tri.resize(3 * (size_t)T);
     for (int t = 0; t < T; ++t) {
         int orig = (int)(key[t] & 0xffffffffu);

@@ -51,6 +51,7 @@ struct HostMesh {
     std::vector<int32_t> tri;         // T x 3, sorted triangle order, input local order
     std::vector<int32_t> perm;        // sorted position -> input triangle id
     std::vector<uint32_t> mkey;       // 30-bit Morton code of each sorted triangle's centroid (ascending)
+    int tile = 0;                     // 0: Morton order; else k-d order with nodes of whole tiles (no mkey)
     std::vector<int32_t> iperm;       // input triangle id -> sorted position
     std::vector<int32_t> inc_ptr;     // V + 1
     std::vector<int32_t> inc_tk;      // 4 t + k for each incidence (t sorted id)
@@ -63,7 +64,12 @@ struct HostMesh {
     std::vector<int32_t> slot_ptr;    // nnz + 1
     std::vector<uint32_t> slot_code;  // p << 4 | k << 2 | l per contribution, in row visiting order
 };
-void build_host_mesh(const pb_mesh *m, HostMesh &hm);
+constexpr int kSymTile = 64;   // triangles per tile of the symmetric far field and the tiled treecode
+
+// tile > 0: order the triangles by a balanced k-d tree over tiles of that many
+void build_host_mesh(const pb_mesh *m, HostMesh &hm, int tile = 0);
+// triangles left of the split of a k-d node of n triangles: half of its tiles
+inline int tile_split(int n, int tile) { return (n + tile - 1) / tile / 2 * tile; }
 
 // ------------------------------------------------------------ device state
 // Source / target records of the far-field kernels, one per triangle:
@@ -393,9 +399,13 @@ void destroy_graphs(DevMesh &d);
 void check_solvable(const DevMesh &d);   // PB_E_STATE for systems that are no formulation
 
 // treecode far field (k_tree.hip): plan built on the host at creation; the
-// product writes d.part in the layout of tree_splits() source chunks
+// product writes d.part in the layout of tree_splits() source chunks, or, where
+// that is 0, in slots of tree_slot_bytes() that launch_tree_finish adds
+bool tree_ordered(const pb_options &o);   // wants the k-d order
 Tree *tree_create(DevMesh &d);
 int tree_splits(const Tree &t);
+size_t tree_slot_bytes(const Tree &t);
+void launch_tree_finish(DevMesh &d);
 void tree_destroy(DevMesh &d);
 void launch_tree_far(DevMesh &d, bool fp32);
 

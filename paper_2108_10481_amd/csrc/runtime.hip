@@ -420,7 +420,7 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     d->fm = formulation_coef(opt->formulation, opt->eps_in, opt->eps_out, opt->cfie_alpha, opt->cfie_beta);
     if (is_calderon(opt->preconditioner))
         d->fmP = calderon_coef(opt->formulation, opt->preconditioner, opt->eps_in, opt->eps_out);
-    build_host_mesh(mesh, d->hm);   // validation happens before any device call
+    build_host_mesh(mesh, d->hm, tree_ordered(*opt) ? kSymTile : 0);   // validation happens before any device call
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) fail(PB_E_DEVICE, "no HIP device available");
     HIPCHECK(hipSetDevice(0));
@@ -430,7 +430,7 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     d->S = opt->source_chunks > 0 ? std::min(opt->source_chunks, T) : choose_chunks(T);
     if (opt->operator_mode == PB_TREECODE) {
         d->tree = tree_create(*d);
-        d->S = tree_splits(*d->tree);
+        if (tree_splits(*d->tree) > 0) d->S = tree_splits(*d->tree);
     }
 
     for (size_t i = 0; i < hm.tri.size(); ++i) {
@@ -495,6 +495,7 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     d->dyn64 = (double *)d->alloc(sizeof(double) * kDyn * T);
     d->dyn32 = (float *)d->alloc(sizeof(float) * kDyn * T);
     size_t part_bytes = sizeof(double) * 16 * (size_t)d->S * T;
+    if (d->tree) part_bytes = std::max(part_bytes, tree_slot_bytes(*d->tree));
     const bool fp32 = opt->precision == PB_FP32;
     // every unordered pair once, FP32 or FP64 (FP64 only when the far field is
     // known to stay matrix-free); under a memory budget the automatic choice
