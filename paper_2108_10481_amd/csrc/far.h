@@ -256,6 +256,7 @@ __device__ __forceinline__ void sym_finish_group(int t, int l, bool ok, int T, i
     for (int v = 0; v < 15; ++v) pot[v] = 0.0;
     if (ok) {
         const int c = (t / kSymTile) / rt;
+#pragma unroll 2
         for (int k = l; k < (nr + 1) * nz; k += kFinishLanes) {
             const int z = k / (nr + 1), i = k - z * (nr + 1);
             const int slot = i < nr - c ? z * nr + c + i : (nz + z) * nr + i - (nr - c);

@@ -70,10 +70,11 @@ __device__ __forceinline__ void source_prep_tri(int s, int V, const int32_t *__r
 
 __global__ void k_source_prep(int T, int V, const int32_t *__restrict__ tri, const double *__restrict__ geo,
                               const double *__restrict__ x, double *__restrict__ dyn64, float *__restrict__ dyn32,
-                              float *__restrict__ dync, double *__restrict__ dync64, DevCtl ctl)
+                              float *__restrict__ dync, double *__restrict__ dync64, int *__restrict__ next, DevCtl ctl)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= T || ctl_skip(ctl)) return;
+    if (s == 0 && next) *next = 0;   // the symmetric far field's item counter
     source_prep_tri(s, V, tri, geo, x + ctl_off(ctl), dyn64, dyn32, dync, dync64);
 }
 
@@ -82,7 +83,7 @@ void launch_source_prep(DevMesh &d, const double *x, bool)
     int T = d.hm.T;
     hipLaunchKernelGGL(k_source_prep, dim3((T + 255) / 256), dim3(256), 0, d.stream, T, d.hm.V, d.tri, d.geo, x,
                        d.dyn64, d.dyn32, d.far_rule != 0 ? d.dync32 : nullptr, d.far_rule == 2 ? d.dync64 : nullptr,
-                       d.ctl);
+                       d.sym_next, d.ctl);
     HIPCHECK(hipGetLastError());
 }
 

@@ -47,6 +47,8 @@
 // item, so no atomics and a fixed summation order.  k_far_sym_finish adds a
 // triangle's nr + 1 slots in FP64 and projects them as k_far_finish does.
 #include <algorithm>
+#include <map>
+#include <mutex>
 
 #include "far.h"
 
@@ -625,14 +627,24 @@ static const void *sym_batch_kernel(int form, bool k0)
     return k;
 }
 
-// as many blocks as are resident at once, or one per item if fewer
+// as many blocks as are resident at once, or one per item if fewer.  The resident
+// number is a constant of the kernel and the device; asked once, since a handle's
+// creation needs it for several kernels.
 int resident_blocks(const void *kernel, int threads, int nitems)
 {
-    int dev = 0, ncu = 0, per_cu = 0;
+    static std::mutex mu;
+    static std::map<std::pair<const void *, int>, long long> known;   // kernel, device
+    int dev = 0;
     HIPCHECK(hipGetDevice(&dev));
-    HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0));
-    return (int)std::max(1LL, std::min((long long)std::max(ncu, 1) * std::max(per_cu, 1), (long long)nitems));
+    std::lock_guard<std::mutex> lock(mu);
+    long long &n = known[{kernel, dev}];
+    if (n == 0) {
+        int ncu = 0, per_cu = 0;
+        HIPCHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+        HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0));
+        n = (long long)std::max(ncu, 1) * std::max(per_cu, 1);
+    }
+    return (int)std::max(1LL, std::min(n, (long long)nitems));
 }
 
 int sym_blocks(bool fp32, int nitems, int form, bool k0)
@@ -659,7 +671,6 @@ void launch_far_sym(DevMesh &d)
     const int form = sym_coef(d, cf);
     const bool k0 = !(d.prm.kappa > 0.0);
     const int nb = d.sym_blocks[sym_form_index(form)];
-    launch_sym_reset(d.stream, d.sym_next);
 #define SYM_RUN(KF)                                                                                             \
     hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, cf, d.tri,  \
                        d.stat64, d.sym_tiles, d.dyn32, d.sym_items, d.sym_nitems, d.sym_next, (float *)d.part,  \

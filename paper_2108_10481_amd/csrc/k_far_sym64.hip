@@ -422,7 +422,6 @@ void launch_far_sym64(DevMesh &d)
     const int form = sym_coef(d, cf);
     const bool k0 = !(d.prm.kappa > 0.0);
     const int nb = d.sym_blocks[sym_form_index(form)];
-    launch_sym_reset(d.stream, d.sym_next);
 #define SYM_RUN(KF)                                                                                              \
     hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kS64Waves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, d.sym_nz, cf, d.tri,   \
                        d.stat64, d.sym_tiles, d.dyn64, d.sym_items, d.sym_nitems, d.sym_next, (double *)d.part,  \

@@ -143,21 +143,22 @@ __device__ __forceinline__ void givens_step(GState *__restrict__ st, double *__r
 {
     const int j = st->j, m = st->m;
     double *col = H + (size_t)j * (m + 1);
-    for (int i = 0; i <= j; ++i) col[i] = h1[i] + h2[i];
     const double hn = sqrt(fmax(st->nrm2, 0.0));
-    col[j + 1] = hn;
+    double x = h1[0] + h2[0];   // the rotated column's last entry; the loads do not wait for it
+#pragma unroll 4
     for (int i = 0; i < j; ++i) {
-        const double a = fma(cs[i], col[i], sn[i] * col[i + 1]);
-        col[i + 1] = fma(-sn[i], col[i], cs[i] * col[i + 1]);
-        col[i] = a;
+        const double c = cs[i], s = sn[i], y = h1[i + 1] + h2[i + 1];
+        col[i] = fma(c, x, s * y);
+        x = fma(-s, x, c * y);
     }
-    const double den = sqrt(fma(col[j], col[j], col[j + 1] * col[j + 1]));
-    cs[j] = col[j] / den;
-    sn[j] = col[j + 1] / den;
+    const double den = sqrt(fma(x, x, hn * hn));
+    cs[j] = x / den;
+    sn[j] = hn / den;
     col[j] = den;
     col[j + 1] = 0.0;
-    g[j + 1] = -sn[j] * g[j];
-    g[j] = cs[j] * g[j];
+    const double gj = g[j];
+    g[j + 1] = -(hn / den) * gj;
+    g[j] = (x / den) * gj;
     st->res = fabs(g[j + 1]);
     st->inv = hn > 0.0 ? 1.0 / hn : 0.0;
     st->j = j + 1;
@@ -203,9 +204,90 @@ __global__ void k_gnormalize(int n, double *__restrict__ Vb, const GState *__res
     Vb[(size_t)st->j * n + e] *= st->inv;
 }
 
+// The whole tail in one block, for systems of at most kSmallKrylov unknowns: two
+// Gram-Schmidt passes, norm, rotation and normalisation with barriers between
+// them instead of launches.  Bound: latency; at 324 unknowns the seven launches
+// took 21 us and as many gaps, this one takes 8.7 us.  A wavefront takes a dot product by itself:
+// lane l stands for the threads l + 64 k, k < 16, of dot_block_sum, whose first
+// four levels (512 .. 64) are then sums inside the lane and the others shuffles, so
+// that every result is bitwise the one of the separate kernels.  Above the limit
+// one block's reads of the basis outweigh the launches: FP64 direct solves (19
+// iterations) with one block / with seven launches, 324 unknowns 1498 / 1623 us,
+// 724 2016 / 2110, 1284 2831 / 2825, 1624 3519 / 3441, 2004 4660 / 4384.
+constexpr int kSmallKrylov = 1024;
+struct SmallLds {
+    double w[kSmallKrylov], h1[kSmallKrylov], h2[kSmallKrylov], inv;
+};
+
+// <v, w> as gdots_item, by one wavefront; the result is in lane 0
+__device__ __forceinline__ double wave_dot(int n, const double *__restrict__ v, const double *__restrict__ w)
+{
+    const int l = threadIdx.x & 63;
+    double a[kDotThreads / 64];
+#pragma unroll
+    for (int k = 0; k < kDotThreads / 64; ++k) {
+        a[k] = 0.0;
+        for (int e = l + 64 * k; e < n; e += kDotThreads) a[k] += v[e] * w[e];
+    }
+#pragma unroll
+    for (int s = kDotThreads / 128; s > 0; s >>= 1)
+#pragma unroll
+        for (int k = 0; k < s; ++k) a[k] += a[k + s];
+    double r = a[0];
+    for (int s = 32; s > 0; s >>= 1) r += __shfl_down(r, s);
+    return r;
+}
+
+__device__ void small_tail(int n, double *__restrict__ Vb, GState *__restrict__ st, double *__restrict__ H,
+                           double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ g, SmallLds &L)
+{
+    const int tid = threadIdx.x, wv = tid >> 6, j = st->j;
+    double *wg = Vb + (size_t)(j + 1) * n;
+    for (int e = tid; e < n; e += kDotThreads) L.w[e] = wg[e];
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+        double *h = pass ? L.h2 : L.h1;
+        for (int i = wv; i <= j; i += kDotThreads / 64) {
+            const double v = wave_dot(n, Vb + (size_t)i * n, L.w);
+            if ((tid & 63) == 0) h[i] = v;
+        }
+        __syncthreads();
+        for (int e = tid; e < n; e += kDotThreads) {
+            double acc = 0.0;
+#pragma unroll 8
+            for (int i = 0; i <= j; ++i) acc += h[i] * Vb[(size_t)i * n + e];
+            L.w[e] -= acc;
+        }
+        __syncthreads();
+    }
+    if (wv == 0) {
+        const double nrm2 = wave_dot(n, L.w, L.w);
+        if (tid == 0) {
+            st->nrm2 = nrm2;
+            givens_step(st, H, cs, sn, g, L.h1, L.h2);
+            L.inv = st->inv;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < n; e += kDotThreads) wg[e] = L.w[e] * L.inv;
+}
+
+__global__ __launch_bounds__(kDotThreads) void k_gsmall(int n, double *__restrict__ Vb, GState *__restrict__ st,
+                                                        double *__restrict__ H, double *__restrict__ cs,
+                                                        double *__restrict__ sn, double *__restrict__ g)
+{
+    __shared__ SmallLds L;
+    if (st->done) return;   // uniform: read before thread 0 may set it (barriers between)
+    small_tail(n, Vb, st, H, cs, sn, g, L);
+}
+
 void kr_graph_iteration_tail(hipStream_t s, int n, int m, double *Vb, GState *st, double *H, double *cs, double *sn,
                              double *g, double *h1, double *h2)
 {
+    if (n <= kSmallKrylov) {
+        hipLaunchKernelGGL(k_gsmall, dim3(1), dim3(kDotThreads), 0, s, n, Vb, st, H, cs, sn, g);
+        return;
+    }
     hipLaunchKernelGGL(k_gdots, dim3(m + 1), dim3(kDotThreads), 0, s, n, Vb, st, h1);
     hipLaunchKernelGGL(k_gupdate, g1(n), dim3(kKB), 0, s, n, Vb, st, h1);
     hipLaunchKernelGGL(k_gdots, dim3(m + 1), dim3(kDotThreads), 0, s, n, Vb, st, h2);
@@ -295,8 +377,22 @@ __global__ void k_bgnormalize(int R, const KrylovReq *__restrict__ rq, const int
 
 int kr_batch_blocks(int n) { return (n + kKB - 1) / kKB; }
 
-void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot)
+__global__ __launch_bounds__(kDotThreads) void k_bgsmall(const KrylovReq *__restrict__ rq)
 {
+    __shared__ SmallLds L;
+    const KrylovReq &q = rq[blockIdx.x];
+    if (q.st->done) return;
+    small_tail(q.n, q.Vb, q.st, q.H, q.cs, q.sn, q.g, L);
+}
+
+// nmax: the largest n of the solves
+void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot, int nmax)
+{
+    if (nmax <= kSmallKrylov) {
+        hipLaunchKernelGGL(k_bgsmall, dim3(R), dim3(kDotThreads), 0, s, rq);
+        HIPCHECK(hipGetLastError());
+        return;
+    }
     const dim3 gd((unsigned)std::max(1, std::min(ndot, 1024)));
     hipLaunchKernelGGL(k_bgdots, gd, dim3(kDotThreads), 0, s, R, rq, 0);
     hipLaunchKernelGGL(k_bgupdate, dim3(nblocks), dim3(kKB), 0, s, R, rq, boff, 0);

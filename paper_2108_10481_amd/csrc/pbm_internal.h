@@ -463,7 +463,8 @@ void calderon_left(DevMesh &d, const double *in, double *out, const DevCtl &ctl)
 int kr_batch_blocks(int n);
 // boff: prefix of kr_batch_blocks(n_r) over the R solves (device); ndot: an
 // upper bound of the dot-product items (sum of the capacities + 1)
-void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot);
+void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot,
+                             int nmax);
 // batched source weights, far-field finish (regular and symmetric splits) and
 // gather of R solves; boff_* prefixes of the blocks each solve takes
 int tail_blocks_source(const TailReq &q);

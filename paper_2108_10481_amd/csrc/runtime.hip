@@ -1217,6 +1217,8 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
     const KrylovReq *dk = (const KrylovReq *)(base + bt);
     const int *dsrc = (const int *)(base + bt + bk), *dfin = dsrc + (L + 1), *dgat = dfin + (L + 1),
               *dkry = dgat + (L + 1);
+    int nmax = 0;
+    for (int r : live) nmax = std::max(nmax, n[r]);
     for (int r : live) ds[r]->ctl = DevCtl{&G[r]->st->j, &G[r]->st->done, (size_t)n[r]};
     HIPCHECK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     try {
@@ -1226,7 +1228,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
         launch_batch_gather(s, L, dt, dgat, bgat[L]);
         for (int r : live)   // apply_after_far's mass-preconditioner step, per request
             if (mass_mode(*ds[r])) mass_precond(*ds[r], 1, ds[r]->mtmp, ds[r]->kry.basis + n[r], ds[r]->ctl);
-        kr_batch_iteration_tail(s, L, dk, dkry, bkry[L], ndot);
+        kr_batch_iteration_tail(s, L, dk, dkry, bkry[L], ndot, nmax);
         HIPCHECK(hipGetLastError());
     } catch (...) {
         hipGraph_t dead = nullptr;
