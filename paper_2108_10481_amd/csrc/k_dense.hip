@@ -842,11 +842,19 @@ static void build_tiles(const HostMesh &hm, DevMesh &d, Dense &D, const std::vec
             for (int c = 0; c < D.ncolor; ++c) {
                 const int32_t *cl = tcol_list.data() + D.color_ptr[c];
                 const int n = D.color_ptr[c + 1] - D.color_ptr[c];
+                // asm_group targets per block share the tile's data.  A launch of fewer than
+                // 1024 targets and tiles does not fill the 512 resident blocks with
+                // them: one target per block (10580 triangles: 220 pairs in 55 blocks 26
+                // us, in 204 blocks 11 us; 1712 pairs in 428 blocks 42 us, in 571 46 us)
+                long long total = 0;
+                for (int i = D.tcolor_ptr[kc]; i < D.tcolor_ptr[kc + 1]; ++i)
+                    total += std::lower_bound(cl, cl + n, (lst[i] + 1) * TL) - cl;
+                const int grp = total < 1024 ? 1 : D.asm_group;
                 for (int i = D.tcolor_ptr[kc]; i < D.tcolor_ptr[kc + 1]; ++i) {
                     const int k = lst[i];
                     const int nk = (int)(std::lower_bound(cl, cl + n, (k + 1) * TL) - cl);
-                    for (int g = 0; g < nk; g += D.asm_group)
-                        blocks.push_back(make_int4(k, D.color_ptr[c] + g, D.color_ptr[c] + std::min(g + D.asm_group, nk), 0));
+                    for (int g = 0; g < nk; g += grp)
+                        blocks.push_back(make_int4(k, D.color_ptr[c] + g, D.color_ptr[c] + std::min(g + grp, nk), 0));
                 }
                 D.sym_ptr.push_back(blocks.size());
             }
