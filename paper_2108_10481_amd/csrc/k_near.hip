@@ -135,15 +135,16 @@ __device__ inline int ss_order(int t, int s, const int *tv, const int *sv, int *
 // each, which are then uniform across the wavefront: a point and its nine weights
 // come through scalar loads and feed the vector unit as scalar operands, and the
 // 36 sums need no reduction across lanes, only over the wavefronts (LDS).
-// out[36 p + 9 op + 3 a + b], op = V_L, K_L, V_Y, K_Y; a, b local vertex ids of t
-// and s in stored order; p = idx[item].  SMALL: every kappa log2(e) r of a near
+// out[36 p + 4 (3 a + b) + op], op = V_L, K_L, V_Y, K_Y (the four values that one
+// vertex pair's row needs lie together); a, b local vertex ids of t and s in stored
+// order; p = idx[item].  SMALL: every kappa log2(e) r of a near
 // pair is at most kExpSmall, 8 instead of 15 instructions for its exponential.
 // Identical triangles lie in one plane: d.n = 0, K = 0, only V is summed.
 // Bound: the FP64 vector rate, 75 instructions per point and pair (68 SMALL; 39
 // and 32 for identical triangles); with a group of lanes per pair (points, weights
 // and basis formed by every lane, 36 butterfly reductions) it was about 130.
 // Refresh of a 24500-triangle matrix-free handle (all of the near field): 1.67 ->
-// 0.81 ms.
+// 0.81 ms (0.71 with k_near_slots as it is below).
 template <int CASE, bool SMALL, int WAVES>
 __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__restrict__ idx,
                                          const int32_t *__restrict__ pair_t, const int32_t *__restrict__ pair_s,
@@ -247,11 +248,12 @@ __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__
         for (int k = 0; k < 3; ++k)
 #pragma unroll
             for (int l = 0; l < 3; ++l) {
-                double *ol = o + 3 * pt[k] + ps[l];
-                ol[0] = aL[0][3 * k + l] * scale;
-                ol[9] = CASE == 3 ? 0.0 : aL[NK - 1][3 * k + l] * scale;
-                ol[18] = aY[0][3 * k + l] * scale;
-                ol[27] = CASE == 3 ? 0.0 : aY[NK - 1][3 * k + l] * scale;
+                double4 v;
+                v.x = aL[0][3 * k + l] * scale;
+                v.y = CASE == 3 ? 0.0 : aL[NK - 1][3 * k + l] * scale;
+                v.z = aY[0][3 * k + l] * scale;
+                v.w = CASE == 3 ? 0.0 : aY[NK - 1][3 * k + l] * scale;
+                *(double4 *)(o + 4 * (3 * pt[k] + ps[l])) = v;
             }
     }
 }
@@ -364,49 +366,79 @@ __global__ void k_pair_sums(int64_t npair, const double *__restrict__ blk, doubl
     if (p >= npair) return;
     const double *B = blk + p * 36;
     double SL = 0.0, SY = 0.0;
-    for (int a = 0; a < 9; ++a) { SL += B[a]; SY += B[18 + a]; }
+    for (int a = 0; a < 9; ++a) { SL += B[4 * a]; SY += B[4 * a + 2]; }
     sums[2 * p] = SL;
     sums[2 * p + 1] = SY;
 }
 
-__global__ void k_near_slots(int64_t nnz, NearCoef cf, const int32_t *__restrict__ slot_ptr,
-                             const uint32_t *__restrict__ slot_code, const int32_t *__restrict__ pair_t,
-                             const int32_t *__restrict__ pair_s, const int32_t *__restrict__ pair_rev,
-                             const double *__restrict__ geo, const double *__restrict__ blk,
-                             const double *__restrict__ sums, double *__restrict__ N, double *__restrict__ Mval)
+// The values of one nonzero (i, j): its contributions in slot order.  Bound: the
+// caches, a chain of loads (code, pair, block) per contribution at scattered
+// pairs.  The four values of a contribution lie together (with one 3 x 3 block per
+// operator each was in a cache line of its own), and kSlotBatch contributions are
+// loaded before the first is added, in their order.  24500 triangles, direct: one
+// by one 167 us, in batches 116, with the values together 66; 10580, Juffer: 128,
+// 103, 73 us.
+constexpr int kSlotBatch = 4;
+template <int FAMILY>
+__global__ __launch_bounds__(256) void k_near_slots(int64_t nnz, NearCoef cf, const int32_t *__restrict__ slot_ptr,
+                                                    const uint32_t *__restrict__ slot_code,
+                                                    const int32_t *__restrict__ pair_t, const int32_t *__restrict__ pair_s,
+                                                    const int32_t *__restrict__ pair_rev, const double *__restrict__ geo,
+                                                    const double *__restrict__ blk, const double *__restrict__ sums,
+                                                    double *__restrict__ N, double *__restrict__ Mval)
 {
     const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (slot >= nnz) return;
+    const FormCoef &f = cf.f;
     double n11 = 0.0, n12 = 0.0, n21 = 0.0, n22 = 0.0, mass = 0.0;
-    for (int c = slot_ptr[slot]; c < slot_ptr[slot + 1]; ++c) {
-        const uint32_t code = slot_code[c];
-        const int p = (int)(code >> 4), k = (code >> 2) & 3, l = code & 3;
-        const int t = pair_t[p], s = pair_s[p];
-        const double *B = blk + (size_t)p * 36;
-        const double *gt = geo + (size_t)t * kGeo;
-        const double vL = B[3 * k + l], kL = B[9 + 3 * k + l];
-        const double vY = B[18 + 3 * k + l], kY = B[27 + 3 * k + l];
-        const double mss = (s == t) ? gt[21] / 12.0 * (k == l ? 2.0 : 1.0) : 0.0;
-        mass += mss;
-        const FormCoef &f = cf.f;
-        // row 1: K and V (Dirichlet trace equations)
-        n11 += f.mass[0][0] * mss + f.aL[0][0] * kL + f.aY[0][0] * kY;
-        n12 += f.mass[0][1] * mss + f.aL[0][1] * vL + f.aY[0][1] * vY;
-        if (f.family == 0) {
-            n21 += f.mass[1][0] * mss + f.aL[1][0] * kL + f.aY[1][0] * kY;
-            n22 += f.mass[1][1] * mss + f.aL[1][1] * vL + f.aY[1][1] * vY;
-        } else {                                  // row 2: D and T (Neumann trace equations)
-            const double *gs = geo + (size_t)s * kGeo;
-            const double *R = blk + (size_t)pair_rev[p] * 36;
-            const double nn = gt[18] * gs[18] + gt[19] * gs[19] + gt[20] * gs[20];
-            const double cc = gt[22 + 3 * k] * gs[22 + 3 * l] + gt[23 + 3 * k] * gs[23 + 3 * l] +
-                              gt[24 + 3 * k] * gs[24 + 3 * l];
-            // D: curl_k . curl_l V + kappa^2 (n_t . n_s) V, by parts; T = K^T
-            const double dL = cc * sums[2 * (size_t)p];
-            const double dY = cc * sums[2 * (size_t)p + 1] + cf.kappa * cf.kappa * nn * vY;
-            const double tL = R[9 + 3 * l + k], tY = R[27 + 3 * l + k];
-            n21 += f.mass[1][0] * mss + f.aL[1][0] * dL + f.aY[1][0] * dY;
-            n22 += f.mass[1][1] * mss + f.aL[1][1] * tL + f.aY[1][1] * tY;
+    const int c1 = slot_ptr[slot + 1];
+    for (int c0 = slot_ptr[slot]; c0 < c1; c0 += kSlotBatch) {
+        uint32_t code[kSlotBatch];
+        int t[kSlotBatch], s[kSlotBatch], rev[kSlotBatch];
+        double4 q[kSlotBatch];   // V_L, K_L, V_Y, K_Y
+        double dL[kSlotBatch], dY[kSlotBatch], tL[kSlotBatch], tY[kSlotBatch];
+#pragma unroll
+        for (int u = 0; u < kSlotBatch; ++u) code[u] = slot_code[min(c0 + u, c1 - 1)];   // the last again past the end
+#pragma unroll
+        for (int u = 0; u < kSlotBatch; ++u) {
+            const int p = (int)(code[u] >> 4), kl = 3 * (int)((code[u] >> 2) & 3) + (int)(code[u] & 3);
+            t[u] = pair_t[p];
+            s[u] = pair_s[p];
+            if (FAMILY != 0) rev[u] = pair_rev[p];
+            q[u] = *(const double4 *)(blk + (size_t)p * 36 + 4 * kl);
+        }
+        if (FAMILY != 0) {   // row 2: D and T (Neumann trace equations)
+#pragma unroll
+            for (int u = 0; u < kSlotBatch; ++u) {
+                const int p = (int)(code[u] >> 4), k = (code[u] >> 2) & 3, l = code[u] & 3;
+                const double *gt = geo + (size_t)t[u] * kGeo, *gs = geo + (size_t)s[u] * kGeo;
+                const double *R = blk + (size_t)rev[u] * 36 + 4 * (3 * l + k);
+                const double nn = gt[18] * gs[18] + gt[19] * gs[19] + gt[20] * gs[20];
+                const double cc = gt[22 + 3 * k] * gs[22 + 3 * l] + gt[23 + 3 * k] * gs[23 + 3 * l] +
+                                  gt[24 + 3 * k] * gs[24 + 3 * l];
+                // D: curl_k . curl_l V + kappa^2 (n_t . n_s) V, by parts; T = K^T
+                dL[u] = cc * sums[2 * (size_t)p];
+                dY[u] = cc * sums[2 * (size_t)p + 1] + cf.kappa * cf.kappa * nn * q[u].z;
+                tL[u] = R[1];
+                tY[u] = R[3];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kSlotBatch; ++u) {
+            if (c0 + u >= c1) break;
+            const int k = (code[u] >> 2) & 3, l = code[u] & 3;
+            const double mss = (s[u] == t[u]) ? geo[(size_t)t[u] * kGeo + 21] / 12.0 * (k == l ? 2.0 : 1.0) : 0.0;
+            mass += mss;
+            // row 1: K and V (Dirichlet trace equations)
+            n11 += f.mass[0][0] * mss + f.aL[0][0] * q[u].y + f.aY[0][0] * q[u].w;
+            n12 += f.mass[0][1] * mss + f.aL[0][1] * q[u].x + f.aY[0][1] * q[u].z;
+            if (FAMILY == 0) {
+                n21 += f.mass[1][0] * mss + f.aL[1][0] * q[u].y + f.aY[1][0] * q[u].w;
+                n22 += f.mass[1][1] * mss + f.aL[1][1] * q[u].x + f.aY[1][1] * q[u].z;
+            } else {
+                n21 += f.mass[1][0] * mss + f.aL[1][0] * dL[u] + f.aY[1][0] * dY[u];
+                n22 += f.mass[1][1] * mss + f.aL[1][1] * tL[u] + f.aY[1][1] * tY[u];
+            }
         }
     }
     N[slot] = n11;
@@ -532,8 +564,13 @@ void launch_near_values(DevMesh &d, const FormCoef &f, const double *blk, const 
     cf.kappa = d.prm.kappa;
     cf.f = f;
     const int64_t nnz = d.nnz();
-    hipLaunchKernelGGL(k_near_slots, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, d.stream, nnz, cf,
-                       d.slot_ptr, d.slot_code, d.pair_t, d.pair_s, d.pair_rev, d.geo, blk, sums, N, Mval);
+    const dim3 g((unsigned)((nnz + 255) / 256)), b(256);
+    if (f.family == 0)
+        hipLaunchKernelGGL(k_near_slots<0>, g, b, 0, d.stream, nnz, cf, d.slot_ptr, d.slot_code, d.pair_t, d.pair_s,
+                           d.pair_rev, d.geo, blk, sums, N, Mval);
+    else
+        hipLaunchKernelGGL(k_near_slots<1>, g, b, 0, d.stream, nnz, cf, d.slot_ptr, d.slot_code, d.pair_t, d.pair_s,
+                           d.pair_rev, d.geo, blk, sums, N, Mval);
     HIPCHECK(hipGetLastError());
 }
 

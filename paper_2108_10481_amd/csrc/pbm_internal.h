@@ -258,7 +258,7 @@ struct DevMesh {
     int32_t *slot_ptr = nullptr;
     uint32_t *slot_code = nullptr;
     double *pair_sums = nullptr;   // npair x 2: sum of the 3 x 3 V_L and V_Y entries
-    double *pairblk = nullptr;     // npair x 36
+    double *pairblk = nullptr;     // npair x 9 x 4 (ss_pairs)
     double *N = nullptr;           // 4 x nnz near blocks (N11, N12, N21, N22), mass included
     double *pinv = nullptr;        // V x 4
     // mass preconditioners: M over the near CSR slots, 1 / M_ii, Chebyshev

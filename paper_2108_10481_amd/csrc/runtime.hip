@@ -1803,6 +1803,11 @@ pb_status pb_mesh_near_blocks(pb_mesh_handle *h, int32_t n, const int32_t *t, co
     launch_pair_blocks_subset(d, n, dt, ds, di, count, o);
     HIPCHECK(hipMemcpyAsync(out, o, sizeof(double) * 36 * n, hipMemcpyDeviceToHost, d.stream));
     HIPCHECK(hipStreamSynchronize(d.stream));
+    for (int k = 0; k < n; ++k) {   // operator by operator, 3 x 3 each
+        double *b = out + 36 * (size_t)k, v[36];
+        for (int e = 0; e < 36; ++e) v[9 * (e & 3) + (e >> 2)] = b[e];
+        std::copy(v, v + 36, b);
+    }
     return PB_OK;
     PB_CATCH
 }
