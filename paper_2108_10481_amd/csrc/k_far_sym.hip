@@ -357,12 +357,12 @@ __global__ __launch_bounds__(64) void k_sym_tiles(int T, const double *__restric
 }
 
 // Row tile I against nk column tiles by one block: tile_of(k) the k-th, src_slot(k,
-// sj, cl) where its triangle sj (column cl) takes its 16 sums (null: nowhere;
-// added to what is there if `add`), row_slot(t) where triangle t of I takes its
+// sj, cl) where its triangle sj (column cl) takes its 16 sums (null: nowhere),
+// row_slot(t) where triangle t of I takes its
 template <int FORM, bool K0, typename IP, typename DP, typename RP, typename TileOf, typename SrcSlot, typename RowSlot>
 __device__ __forceinline__ void sym_row(const SymCoef<float> &cf, IP __restrict__ tri, DP __restrict__ stat,
                                         DP __restrict__ tiles, RP __restrict__ dyn, int T, int I, int nk, TileOf tile_of,
-                                        SrcSlot src_slot, bool add, RowSlot row_slot, SymLds &L)
+                                        SrcSlot src_slot, RowSlot row_slot, SymLds &L)
 {
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int g = lane >> 4, li = lane & 15;
@@ -430,7 +430,7 @@ __device__ __forceinline__ void sym_row(const SymCoef<float> &cf, IP __restrict_
             float *o = sj < T ? src_slot(k, sj, cl) : nullptr;
             if (o) {
                 f32x4 *so = (f32x4 *)o + m;
-                f32x4 v = add ? *so : zero;
+                f32x4 v = zero;
 #pragma unroll
                 for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][m];
                 *so = v;
@@ -458,21 +458,156 @@ __device__ __forceinline__ void sym_row(const SymCoef<float> &cf, IP __restrict_
     }
 }
 
-// Item (a, b) of one mesh by one block; part holds the 2 nr slots
+// Item (a, b) of one mesh by one block; part holds the 2 nr slots.  sym_row's work
+// written out: through the shared functions the compiler issues the staging loads
+// later, 8% of a product of 1620 triangles (direct 103 us against 93, second kind
+// 122 against 114; 1% either way at 20480).
 template <int FORM, bool K0, typename IP, typename DP, typename RP>
 __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict__ tri, DP __restrict__ stat,
                                          DP __restrict__ tiles, RP __restrict__ dyn, int T, int rt, int nr, int a, int b,
                                          float *__restrict__ part, SymLds &L)
 {
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int g = lane >> 4, li = lane & 15;
     const int ntile = (T + 63) / 64;
     const int I0 = a * rt, I1 = min(ntile, I0 + rt);
     const int J0 = b * rt, J1 = min(ntile, J0 + rt);
+    SymRows &R = L.r[w];
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int I = I0; I < I1; ++I) {
-        const int first = a == b ? I : J0;
-        // the item's earlier target tiles came before
-        sym_row<FORM, K0>(cf, tri, stat, tiles, dyn, T, I, J1 - first, [&](int k) { return first + k; },
-                          [&](int k, int sj, int cl) { return part + ((size_t)(nr + a) * T + sj) * 16; }, I != I0,
-                          [&](int tr) { return part + ((size_t)b * T + tr) * 16; }, L);
+        const int t = 64 * I + 16 * w + li;      // the lane's target triangle as an operand row
+        const int tc = min(t, T - 1);
+        const auto ts = stat + (size_t)tc * kStat;
+        const auto td = dyn + (size_t)tc * kDyn;
+        f32x4 a1[6], a2[6], W[3];
+#pragma unroll
+        for (int p = 0; p < 6; ++p) a1[p] = a2[p] = zero;
+        W[0] = W[1] = W[2] = zero;
+        for (int J = a == b ? I : J0; J < J1; ++J) {
+            const double cx = tiles[kTileRec * (size_t)J], cy = tiles[kTileRec * (size_t)J + 1], cz = tiles[kTileRec * (size_t)J + 2];
+            const double c[3] = {cx, cy, cz};
+            const double s = cf.s;
+            // columns: wavefronts 0..2 two points each, wavefront 3 the rest
+            {
+                const int sj = min(64 * J + lane, T - 1);
+                const bool in = 64 * J + lane < T;   // past the end: the last triangle with zero weights
+                const auto ss = stat + (size_t)sj * kStat;
+                const auto sd = dyn + (size_t)sj * kDyn;
+                if (w < 3) {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const int q = 2 * w + k;
+                        const double yx = (ss[3 * q] - cx) * s, yy = (ss[3 * q + 1] - cy) * s, yz = (ss[3 * q + 2] - cz) * s;
+                        L.c.bq[q][lane] = f32x4{(float)(-2.0 * yx), (float)(-2.0 * yy), (float)(-2.0 * yz),
+                                                (float)(yx * yx + yy * yy + yz * yz)};
+                        const float b1 = in ? sd[q] : 0.0f, b2 = in ? sd[6 + q] : 0.0f;
+                        // FORM 0: the weights of R3, 1/r, E, e/r; else those of K, V, T and D's normal part
+                        L.c.w[q][lane] = FORM == 0 ? f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b1, cf.cD * b2}
+                                                   : f32x4{cf.cK * b1, cf.cV * b2, cf.cT * b2, cf.kD * b1};
+                    }
+                } else {
+                    const double nx = ss[18], ny = ss[19], nz = ss[20];
+                    const double os = (ss[21] - (cx * nx + cy * ny + cz * nz)) * s;
+                    L.c.bn[lane] = f32x4{(float)nx, (float)ny, (float)nz, (float)-os};
+                    if (FORM >= 1) L.c.curl[lane] = in ? f32x4{sd[12], sd[13], sd[14], 0.0f} : zero;
+                    L.c.id[0][lane] = in ? tri[3 * sj] : -1;
+                    L.c.id[1][lane] = in ? tri[3 * sj + 1] : -1;
+                    L.c.id[2][lane] = in ? tri[3 * sj + 2] : -1;
+                }
+            }
+            // rows of this wavefront
+            float A[6], A2;
+#pragma unroll
+            for (int p = 0; p < 6; ++p) {
+                const double cg = g == 0 ? c[0] : g == 1 ? c[1] : c[2];
+                const float xs = (float)((ts[3 * p + (g < 3 ? g : 2)] - cg) * s);
+                A[p] = g < 3 ? xs : 1.0f;
+                if (g < 3) R.x[p][g][li] = xs;
+            }
+            A2 = g < 3 ? 0.5f * (float)ts[18 + (g < 3 ? g : 2)] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int p = g + 4 * k;
+                if (p < 6) {
+                    const double x = (ts[3 * p] - cx) * s, y = (ts[3 * p + 1] - cy) * s, z = (ts[3 * p + 2] - cz) * s;
+                    R.x2[p][li] = (float)(x * x + y * y + z * z);
+                } else if (p == 6) {
+                    R.o[li] = (float)((ts[21] - (cx * ts[18] + cy * ts[19] + cz * ts[20])) * s);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) R.d[4 * g + k][li] = t < T ? td[4 * g + k] : 0.0f;
+            __syncthreads();
+            // well separated: |X| |Y| stays of the order of r^2
+            const double dx = tiles[kTileRec * (size_t)I] - cx, dy = tiles[kTileRec * (size_t)I + 1] - cy, dz = tiles[kTileRec * (size_t)I + 2] - cz;
+            const double reach = kSymApart * (tiles[kTileRec * (size_t)I + 3] + tiles[kTileRec * (size_t)J + 3]);
+            const bool near = dx * dx + dy * dy + dz * dz < reach * reach;
+            if (!near) {
+                const bool live[4] = {true, true, true, true};
+                for (int cb = 0; cb < 4; ++cb) {
+                    f32x4 src;
+                    sym_block<FORM, K0, false>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
+                    L.out[w][16 * cb + li][g] = src;
+                }
+            } else {
+                int tv[4][3];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int tr = 64 * I + 16 * w + 4 * g + v, trc = min(tr, T - 1);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) tv[v][k] = tr < T ? tri[3 * trc + k] : -1;
+                }
+                for (int cb = 0; cb < 4; ++cb) {
+                    f32x4 src = zero;
+                    if (I != J || cb >= w) {   // uniform: below the diagonal every pair has been met
+                        const int j0 = L.c.id[0][16 * cb + li], j1 = L.c.id[1][16 * cb + li], j2 = L.c.id[2][16 * cb + li];
+                        bool live[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            bool m = (j0 >= 0) & (tv[v][0] >= 0);
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) m = m & (tv[v][k] != j0) & (tv[v][k] != j1) & (tv[v][k] != j2);
+                            if (I == J) m = m & (16 * w + 4 * g + v < 16 * cb + li);
+                            live[v] = m;
+                        }
+                        sym_block<FORM, K0, true>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
+                    }
+                    L.out[w][16 * cb + li][g] = src;
+                }
+            }
+            __syncthreads();
+            // the four wavefronts' source-side sums, in order, onto the slot (the item's
+            // earlier target tiles came before)
+            {
+                const int cl = tid >> 2, k = tid & 3, sj = 64 * J + cl;
+                if (sj < T) {
+                    f32x4 *so = (f32x4 *)(part + ((size_t)(nr + a) * T + sj) * 16) + k;
+                    f32x4 v = I == I0 ? zero : *so;
+#pragma unroll
+                    for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][k];
+                    *so = v;
+                }
+            }
+        }
+        // target-side sums over the 16 columns of each row of lanes
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float o[16];
+#pragma unroll
+            for (int p = 0; p < 6; ++p) {
+                o[p] = row_sum(a1[p][v]);
+                o[6 + p] = row_sum(a2[p][v]);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) o[12 + k] = FORM == 0 ? 0.0f : row_sum(W[k][v]);
+            o[15] = 0.0f;
+            const int tr = 64 * I + 16 * w + 4 * g + v;
+            if (li == 0 && tr < T) {
+                f32x4 *fo = (f32x4 *)(part + ((size_t)b * T + tr) * 16);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) fo[k] = f32x4{o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
+            }
+        }
     }
 }
 
@@ -546,7 +681,7 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_sym_list(int T, SymCoef<f
                           const int slot = entries[it.y + k].y;
                           return slot < 0 ? nullptr : slots + ((size_t)slot * kSymTile + cl) * 16;
                       },
-                      false, [&](int tr) { return slots + ((size_t)it.w * kSymTile + tr - kSymTile * it.x) * 16; }, lds);
+                      [&](int tr) { return slots + ((size_t)it.w * kSymTile + tr - kSymTile * it.x) * 16; }, lds);
 }
 
 // kFinishLanes lanes per triangle over its nr + 1 slots, then the test
