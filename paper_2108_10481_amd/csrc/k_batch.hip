@@ -467,16 +467,27 @@ static void apply_accurate(DevMesh &d, int nb, const double *X, double *Y)
 {
     const int V = d.hm.V, n = 2 * V;
     Dense *D = d.dense;
-    if (nb < 2 || !D->A32 || d.prof.on(0) || !D->Y16 || !split_space(d)) {
+    if (nb < 2 || !D->A32 || !D->Y16 || !split_space(d)) {
         for (int s = 0; s < nb; ++s) apply_operator(d, X + (size_t)s * n, Y + (size_t)s * n, PB_APPLY_PRECOND, nullptr);
         return;
     }
     const int ntile = (n + 16 * kHiRows - 1) / (16 * kHiRows), KS = parts_for(d, ntile);
+    Profiler &pf = d.prof;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (pf.on(0)) {
+        HIPCHECK(hipEventCreate(&e0));
+        HIPCHECK(hipEventCreate(&e1));
+        HIPCHECK(hipEventRecord(e0, d.stream));
+    }
     hipLaunchKernelGGL(k_pad_hi, dim3((unsigned)((16 * D->ld + 255) / 256)), dim3(256), 0, d.stream, V, n, nb, D->Vp,
                        D->ld, D->vperm, X, D->X64);
     hipLaunchKernelGGL(k_gemm32, dim3((ntile * KS + 3) / 4), dim3(256), 0, d.stream, n, D->ld, KS, D->A32, D->X64, D->P64);
     hipLaunchKernelGGL(k_join_parts, dim3((unsigned)((16 * (size_t)n + 255) / 256)), dim3(256), 0, d.stream, n, nb, KS,
                        D->P64, D->Y16);
+    if (pf.on(0)) {
+        HIPCHECK(hipEventRecord(e1, d.stream));
+        pf.record(0, e0, e1, (double)n * n * 4.0 + kMaxBatch * (double)n * (8.0 + 8.0));
+    }
     gather_all(d, nb, X, Y);
     HIPCHECK(hipGetLastError());
 }
