@@ -53,17 +53,16 @@ PEAK_TFLOPS = {"f32": 157.3, "f64": 78.6}   # MI355X published vector peaks
 ASM_FLOPS_PER_PP = {0: 25.83, 1: 29.25}
 # VALU issue: a SIMD issues one wave64 VALU instruction per 4 cycles, so the
 # device's issue capacity is 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane
-# instructions per second.  The rocprofv3 counters show the far-field kernels'
-# transcendentals (v_rsq_f32, v_exp_f32) overlapping the other VALU work there
-# (SQ_ACTIVE_INST_VALU, which counts each of them as two quad-cycles, exceeds
-# the kernel's SIMD cycles), so the issue fraction charges the executed
-# non-transcendental instructions and the transcendentals are reported beside
-# it against the measured v_exp_f32 rate.  Executed non-transcendental VALU
+# instructions per second.  The issue fraction charges the executed
+# non-transcendental instructions; the transcendentals (v_rsq_f32, v_exp_f32:
+# two quad-cycles each) are reported beside it against the measured v_exp_f32
+# rate.  With both, SQ_ACTIVE_INST_VALU covers 91-93% of the far-field
+# kernels' SIMD cycles.  Executed non-transcendental VALU
 # lane instructions per ordered kernel pair, from SQ_INSTS_VALU -
 # SQ_INSTS_VALU_TRANS_F32 (profiles/k_far_star81920_trace_and_counters.md,
 # profiles/sphere20480_fp32_assembled_trace_and_traffic.md):
 ISSUE_PEAK = 256 * 4 * 16 * 2.4e9
-FAR_VALU_PER_PAIR = {0: 11.79, 1: 16.70}   # k_far_sym<FORM>, one transcendental per pair
+FAR_VALU_PER_PAIR = {0: 8.13, 1: 10.95}   # k_far_sym<FORM>, one transcendental per pair
 FAR_TRANS_PER_PAIR = 1.0
 ASM_VALU_PER_PP = {0: 22.50, 1: 25.76}     # far-field assembly, one transcendental per pair
 ASM_TRANS_PER_PP = 1.0
@@ -578,9 +577,8 @@ def batch(argv=None):
     solved once; in the fused solve the far fields of all requests still
     iterating run in one persistent launch per kernel form and GMRES
     iteration.  The fused solve's handles evaluate every unordered triangle
-    pair once (far_symmetric 1), which a batch of small meshes can fill the
-    device with; the one-after-another baseline uses the single-solve default
-    (per ordered pair below 3584 triangles).  The fused results are bitwise
+    pair once (far_symmetric 1), as the one-after-another baseline's do by
+    default.  The fused results are bitwise
     those of single solves on the same handles, which the run checks; the
     fused launches are timed with HIP events.  The first fused call plans
     the far-field work lists and captures the batch graph, which later calls
@@ -601,8 +599,8 @@ def batch(argv=None):
                                                                          far_symmetric=sym))
                     for m, _, f in reqs]
         # the fused solve's handles evaluate every unordered triangle pair once
-        # (far_symmetric 1: the batch fills the device whatever the mesh sizes);
-        # the one-after-another baseline uses the single-solve default (0)
+        # (far_symmetric 1); the one-after-another baseline uses the single-solve
+        # default (0)
         hs = handles(1)
         ha = handles(0)
         sets = [(c.xyz, c.q) for _, c, _ in reqs]
@@ -715,7 +713,7 @@ def large(argv=None):
                                            "evals_per_s": round(w / (ms * 1e-3), 1) if ms > 0 else None},
                       "roofline": {"bound": "alu", "achieved": round(tf, 3), "peak": PEAK_TFLOPS["f32"],
                                    "unit": "TFLOP/s", "frac": round(tf / PEAK_TFLOPS["f32"], 4), "traffic": None,
-                                   "kernel": "treecode product (k_tree_charges, k_tree_proxies, k_tree_eval)"}}
+                                   "kernel": "treecode product (k_tree_charges, k_tree_m2m, k_tree_rows, k_tree_far, k_sym_list)"}}
         print(f"large: {fname} done", file=sys.stderr, flush=True)
     if not a.no_direct:
         with pbm.MeshHandle(mesh.xyz, mesh.tri, pbm.pb_default_options(formulation=pbm.PB_JUFFER,

@@ -1,6 +1,5 @@
 """GPU: the far field that evaluates every unordered triangle pair once, at the
-edges of its tiles (64 triangles in groups of 16 in FP32, 32 in groups of 8
-and 16 in FP64): less than one group, one tile and a remainder, many tiles with
+edges of its tiles (64 triangles, in FP32 in groups of 16): less than one group, one tile and a remainder, many tiles with
 a ragged last one and separated tile pairs.  The reference is the FP64 oracle's
 dense system.
 
