@@ -56,13 +56,13 @@ ASM_FLOPS_PER_PP = {0: 25.83, 1: 29.25}
 # instructions per second.  The issue fraction charges the executed
 # non-transcendental instructions; the transcendentals (v_rsq_f32, v_exp_f32:
 # two quad-cycles each) are reported beside it against the measured v_exp_f32
-# rate.  With both, SQ_ACTIVE_INST_VALU covers 91-93% of the far-field
+# rate.  With both, SQ_ACTIVE_INST_VALU covers 91-94% of the far-field
 # kernels' SIMD cycles.  Executed non-transcendental VALU
 # lane instructions per ordered kernel pair, from SQ_INSTS_VALU -
 # SQ_INSTS_VALU_TRANS_F32 (profiles/k_far_star81920_trace_and_counters.md,
 # profiles/sphere20480_fp32_assembled_trace_and_traffic.md):
 ISSUE_PEAK = 256 * 4 * 16 * 2.4e9
-FAR_VALU_PER_PAIR = {0: 8.13, 1: 10.95}   # k_far_sym<FORM>, one transcendental per pair
+FAR_VALU_PER_PAIR = {0: 8.13, 1: 10.96}   # k_far_sym<FORM>, one transcendental per pair
 FAR_TRANS_PER_PAIR = 1.0
 ASM_VALU_PER_PP = {0: 22.50, 1: 25.76}     # far-field assembly, one transcendental per pair
 ASM_TRANS_PER_PP = 1.0

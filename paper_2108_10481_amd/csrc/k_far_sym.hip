@@ -458,18 +458,20 @@ __device__ __forceinline__ void sym_row(const SymCoef<float> &cf, IP __restrict_
     }
 }
 
-// Item (a, b) of one mesh by one block; part holds the 2 nr slots.  sym_row's work
+// Item (a, b, z) of one mesh by one block: part z of nz takes the column groups
+// 4 z / nz .. 4 (z + 1) / nz of every tile (PARTS; else nz = 1); part holds the 2 nr nz slots.  sym_row's work
 // written out: through the shared functions the compiler issues the staging loads
 // later, 8% of a product of 1620 triangles (direct 103 us against 93, second kind
 // 122 against 114; 1% either way at 20480).
-template <int FORM, bool K0, typename IP, typename DP, typename RP>
+template <int FORM, bool K0, bool PARTS, typename IP, typename DP, typename RP>
 __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict__ tri, DP __restrict__ stat,
-                                         DP __restrict__ tiles, RP __restrict__ dyn, int T, int rt, int nr, int a, int b,
+                                         DP __restrict__ tiles, RP __restrict__ dyn, int T, int rt, int nr, int nz, int a, int b, int z,
                                          float *__restrict__ part, SymLds &L)
 {
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int g = lane >> 4, li = lane & 15;
     const int ntile = (T + 63) / 64;
+    const int cb0 = PARTS ? 4 * z / nz : 0, cb1 = PARTS ? 4 * (z + 1) / nz : 4;
     const int I0 = a * rt, I1 = min(ntile, I0 + rt);
     const int J0 = b * rt, J1 = min(ntile, J0 + rt);
     SymRows &R = L.r[w];
@@ -544,7 +546,7 @@ __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict
             const bool near = dx * dx + dy * dy + dz * dz < reach * reach;
             if (!near) {
                 const bool live[4] = {true, true, true, true};
-                for (int cb = 0; cb < 4; ++cb) {
+                for (int cb = cb0; cb < cb1; ++cb) {
                     f32x4 src;
                     sym_block<FORM, K0, false>(cf, L.c, R, 16 * cb, lane, A, A2, live, a1, a2, W, src);
                     L.out[w][16 * cb + li][g] = src;
@@ -557,7 +559,7 @@ __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict
 #pragma unroll
                     for (int k = 0; k < 3; ++k) tv[v][k] = tr < T ? tri[3 * trc + k] : -1;
                 }
-                for (int cb = 0; cb < 4; ++cb) {
+                for (int cb = cb0; cb < cb1; ++cb) {
                     f32x4 src = zero;
                     if (I != J || cb >= w) {   // uniform: below the diagonal every pair has been met
                         const int j0 = L.c.id[0][16 * cb + li], j1 = L.c.id[1][16 * cb + li], j2 = L.c.id[2][16 * cb + li];
@@ -581,10 +583,11 @@ __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict
             {
                 const int cl = tid >> 2, k = tid & 3, sj = 64 * J + cl;
                 if (sj < T) {
-                    f32x4 *so = (f32x4 *)(part + ((size_t)(nr + a) * T + sj) * 16) + k;
+                    f32x4 *so = (f32x4 *)(part + ((size_t)((PARTS ? (nz + z) * nr : nr) + a) * T + sj) * 16) + k;
                     f32x4 v = I == I0 ? zero : *so;
+                    if (!PARTS || (cl >> 4 >= cb0 && cl >> 4 < cb1))   // the other parts' columns: zero
 #pragma unroll
-                    for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][k];
+                        for (int u = 0; u < kSymWaves; ++u) v += L.out[u][cl][k];
                     *so = v;
                 }
             }
@@ -603,7 +606,7 @@ __device__ __forceinline__ void sym_item(const SymCoef<float> &cf, IP __restrict
             o[15] = 0.0f;
             const int tr = 64 * I + 16 * w + 4 * g + v;
             if (li == 0 && tr < T) {
-                f32x4 *fo = (f32x4 *)(part + ((size_t)b * T + tr) * 16);
+                f32x4 *fo = (f32x4 *)(part + ((size_t)((PARTS ? z * nr : 0) + b) * T + tr) * 16);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) fo[k] = f32x4{o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]};
             }
@@ -623,7 +626,7 @@ __device__ __forceinline__ int sym_next_item(int *__restrict__ next, SymLds &L)
 // One mesh: each block takes items (heaviest first) from a device counter
 // until the list is done.
 template <int FORM, bool K0>
-__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, int nr, SymCoef<float> cf,
+__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, int nr, int nz, SymCoef<float> cf,
                                                               const int32_t *__restrict__ tri,
                                                               const double *__restrict__ stat,
                                                               const double *__restrict__ tiles,
@@ -638,7 +641,30 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym(int T, int rt, in
         const int i = sym_next_item(next, lds);
         if (i >= nitems) return;
         const int4 it = items[i];
-        sym_item<FORM, K0>(cf, tri, stat, tiles, dyn, T, rt, nr, it.y, it.z, part, lds);
+        sym_item<FORM, K0, false>(cf, tri, stat, tiles, dyn, T, rt, nr, 1, it.y, it.z, 0, part, lds);
+    }
+}
+
+// ... with items in parts (meshes of few items).  A kernel of its own: the part's
+// bounds as variables cost the direct form of k_far_sym registers (70.2 against 69.2
+// ms at 81920 triangles).
+template <int FORM, bool K0>
+__global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym_parts(int T, int rt, int nr, int nz, SymCoef<float> cf,
+                                                              const int32_t *__restrict__ tri,
+                                                              const double *__restrict__ stat,
+                                                              const double *__restrict__ tiles,
+                                                              const float *__restrict__ dyn,
+                                                              const int4 *__restrict__ items, int nitems,
+                                                              int *__restrict__ next, float *__restrict__ part,
+                                                              DevCtl ctl)
+{
+    __shared__ SymLds lds;
+    if (ctl_skip(ctl)) return;   // uniform: every wavefront leaves
+    for (;;) {
+        const int i = sym_next_item(next, lds);
+        if (i >= nitems) return;
+        const int4 it = items[i];
+        sym_item<FORM, K0, true>(cf, tri, stat, tiles, dyn, T, rt, nr, nz, it.y, it.z, it.w, part, lds);
     }
 }
 
@@ -656,7 +682,8 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_far_sym_batch(const FarRe
         const int4 it = items[i];
         const FarReq<float> &rq = reqs[it.x];
         if (rq.skip && *rq.skip) continue;
-        sym_item<FORM, K0>(rq.sc, rq.tri, rq.stat64, rq.tiles, rq.dyn, rq.T, rq.rt, rq.nr, it.y, it.z, rq.part, lds);
+        sym_item<FORM, K0, true>(rq.sc, rq.tri, rq.stat64, rq.tiles, rq.dyn, rq.T, rq.rt, rq.nr, rq.nz, it.y, it.z, it.w, rq.part,
+                             lds);
     }
 }
 
@@ -704,8 +731,8 @@ __global__ void k_sym_set(int *p, int v) { *p = v; }
 
 // The symmetric split applies to FP32 matrix-free meshes of every size.
 // Automatic (mode 0) is yes: measured per product (direct / second kind, launches
-// included), 320 triangles 77 / 76 us against 94 / 101 us per ordered pair, 1620
-// 95 / 116 against 133 / 166, 3380 216 against 328 (direct); mode 1 always, mode -1
+// included), 320 triangles 51 us (second kind) against 101 us per ordered pair, 1620
+// 89 / 111 against 133 / 166, 3380 216 against 328 (direct); mode 1 always, mode -1
 // never.
 bool sym_eligible(int T, double kappa, int mode)
 {
@@ -715,7 +742,10 @@ bool sym_eligible(int T, double kappa, int mode)
 }
 
 // Ranges of rt tiles: at most 320 ranges (51000 items) in FP32, kSym64Ranges in
-// FP64, whose slots are twice as large.  In FP64 an item (64 steps of 36 point
+// FP64, whose slots are twice as large.  In FP32 an item's four column groups are
+// dealt to nz parts while there are fewer than 400 (per product in one part / now:
+// 320 triangles second kind 75 / 51 us, 720 76 / 65, 1280 direct 74 / 69, 1620 94 /
+// 89; up to 512 parts: 1280 76).  In FP64 an item (64 steps of 36 point
 // pairs per lane, 16 for each wavefront) is cut into nz parts where the items
 // are few for the 512 resident blocks: into two below 2048 items, further below
 // 600 (measured per product, 1620 triangles / 351 items: 2 parts 138 us, 8 172 us,
@@ -728,8 +758,10 @@ void sym_plan(int T, bool fp32, int request, int &rt, int &nr, int &nz, std::vec
     rt = std::max(1, (ntile + most - 1) / most);
     nr = (ntile + rt - 1) / rt;
     nz = 1;
-    if (!fp32) {
-        const int n = nr * (nr + 1) / 2;
+    const int n = nr * (nr + 1) / 2;
+    if (fp32) {
+        while (nz < 4 && n * nz < 400) nz *= 2;
+    } else {
         while (nz < 16 && n * nz < (nz == 1 ? 2048 : 600)) nz *= 2;
     }
     std::vector<std::pair<int, int4>> w;
@@ -807,10 +839,14 @@ void launch_far_sym(DevMesh &d)
     const bool k0 = !(d.prm.kappa > 0.0);
     const int nb = d.sym_blocks[sym_form_index(form)];
 #define SYM_RUN(KF)                                                                                             \
-    hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, cf, d.tri,  \
+    hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, d.sym_nz, cf, d.tri,  \
                        d.stat64, d.sym_tiles, d.dyn32, d.sym_items, d.sym_nitems, d.sym_next, (float *)d.part,  \
                        d.ctl);
-    SYM_PICK(k_far_sym, form, k0, SYM_RUN)
+    if (d.sym_nz > 1) {
+        SYM_PICK(k_far_sym_parts, form, k0, SYM_RUN)
+    } else {
+        SYM_PICK(k_far_sym, form, k0, SYM_RUN)
+    }
     HIPCHECK(hipGetLastError());
 }
 

@@ -569,8 +569,10 @@ size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64)
     double part = (double)S * t * 16 * 8;
     if (o->precision == PB_FP32 && o->operator_mode != PB_TREECODE && o->regular_order != 1 &&
         sym_eligible(T, o->kappa, o->far_symmetric)) {
-        const double ntile = std::ceil(t / 64.0), rt = std::ceil(ntile / 320.0);
-        part = std::max(part, 2.0 * std::ceil(ntile / rt) * t * 16 * 4);   // the symmetric far field's slots
+        int rt, nr, nz;
+        std::vector<int4> items;
+        sym_plan(T, true, 0, rt, nr, nz, items);
+        part = std::max(part, 2.0 * nr * nz * t * 16 * 4);   // the symmetric far field's slots
     }
     if (sym64 && o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE && o->regular_order != 1) {
         int rt, nr, nz;

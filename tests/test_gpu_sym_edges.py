@@ -42,3 +42,20 @@ def test_product_at_tile_edges(cases, name, form, kappa):
         assert np.array_equal(y, again)
         assert np.linalg.norm(y - ref) < tol * np.linalg.norm(ref), (precision, sym)
         assert np.abs(y - ref).max() < 10 * tol * np.abs(ref).max(), (precision, sym)
+
+
+@pytest.mark.parametrize("freq", [5, 8, 9, 10])   # 500, 1280, 1620, 2000 triangles: 4, 2, 2 parts, whole items
+@pytest.mark.parametrize("form", [pbm.PB_DIRECT_EXT_PERM, pbm.PB_JUFFER])
+def test_parts_of_items(freq, form):
+    """FP32 items cut into parts by column groups, against the FP64 product per
+    ordered pair (PB_AUTO stays on it); the tolerance is the one above."""
+    m = inputs.star_surface(4, freq, 5.0)[0]
+    x = np.random.default_rng(31).standard_normal(2 * m.n_vertices)
+    out = []
+    for precision, mode in ((pbm.PB_FP64, pbm.PB_AUTO), (pbm.PB_FP32, pbm.PB_MATRIX_FREE)):
+        opt = pbm.pb_default_options(formulation=form, precision=precision, operator_mode=mode)
+        with pbm.MeshHandle(m.xyz, m.tri, opt) as h:
+            out.append(pbm.pb_mesh_apply(h, x))
+    ref, y = out
+    assert np.linalg.norm(y - ref) < 2e-6 * np.linalg.norm(ref)
+    assert np.abs(y - ref).max() < 2e-5 * np.abs(ref).max()
