@@ -70,7 +70,7 @@ struct FarCoef {
 // by sym_coef
 template <typename R>
 struct SymCoef {
-    R s;                   // coordinate scale (kappa log2 e; 1 for kappa = 0)
+    R s;                   // coordinate scale (kappa log2 e; 1 unscreened)
     R kap;                 // kappa / s
     R cK, cV, cT, cD;      // factors of the four sums (FORM 0: kL, vL, kY, vY)
     R kD;                  // kappa^2 times the Yukawa coefficient of D
@@ -301,8 +301,8 @@ inline int far_coef(const DevMesh &d, FarCoef<R> &cf)
 // scaled by s = kappa log2(e) (kappa > 0): with x' = s x, 1/r = s / r', the
 // normal-derivative factors (d.n)/r^3 = s^2 (d'.n)/r'^3 and exp(-kappa r) =
 // exp2(-r'), so the K- and T-type coefficients take s^2, the V- and D-type ones
-// s, and kappa becomes kappa / s.  For kappa = 0, s = 1 (coordinates and
-// coefficients as they are, kappa 0).  Returns the kernel FORM: 0 (direct), 1
+// s, and kappa becomes kappa / s.  Unscreened (far_k0), s = 1: coordinates and
+// coefficients as they are.  Returns the kernel FORM: 0 (direct), 1
 // (every operator has a Laplace term: its coefficient is taken out), 3 (none
 // has), 4 (some have: a combined field with one zero constant).
 template <typename R>
@@ -310,7 +310,7 @@ inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
 {
     FarCoef<double> c;
     int form = far_coef(d, c);
-    const double s = d.prm.kappa > 0.0 ? d.prm.kappa * 1.4426950408889634 : 1.0, s2 = s * s;
+    const double s = d.far_k0 ? 1.0 : d.prm.kappa * 1.4426950408889634, s2 = s * s;
     sc = SymCoef<R>{};
     sc.s = (R)s;
     sc.kap = (R)(d.prm.kappa / s);
@@ -338,7 +338,7 @@ inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
     return form;
 }
 
-// CALL with the kernel of a form (0, 1, 3, 4) and screening (k0: kappa = 0)
+// CALL with the kernel of a form (0, 1, 3, 4) and screening (k0: none)
 #define SYM_PICK(KERNEL, form, k0, CALL)                                                       \
     if (k0) {                                                                                  \
         if (form == 0) CALL((KERNEL<0, true>))                                                 \

@@ -517,7 +517,7 @@ static void batch_plan(const std::vector<DevMesh *> &ds, const std::vector<int> 
     for (int f = 0; f < 4; ++f) fb.nitems[f] = 0;
     std::vector<FarReq<R>> reqs(ds.size());
     std::vector<std::vector<std::pair<int, int4>>> q(4);   // (cost, item) per form
-    // symmetric items per form 0, 1, 3, 4 (kappa > 0), then per form with kappa = 0
+    // symmetric items per form 0, 1, 3, 4 (screened), then per form without screening
     std::vector<std::vector<std::pair<int, int4>>> sq(2 * kSymForms);
     for (int r : live) {
         DevMesh &d = *ds[r];
@@ -541,7 +541,7 @@ static void batch_plan(const std::vector<DevMesh *> &ds, const std::vector<int> 
             std::vector<int4> its;
             sym_plan(T, sizeof(R) == 4, r, rq.rt, rq.nr, rq.nz, its);
             const int rt = rq.rt;
-            const int sf = sym_form_index(sform) + (d.prm.kappa > 0.0 ? 0 : kSymForms);
+            const int sf = sym_form_index(sform) + (d.far_k0 ? kSymForms : 0);
             const int ntile = (T + kSymTile - 1) / kSymTile;
             for (const int4 &e : its) {   // weighed by its tile pairs in units of a sixteenth
                 const int na = std::min(ntile, (e.y + 1) * rt) - e.y * rt;

@@ -26,7 +26,7 @@
 // Coordinates (points and the plane offsets) are used scaled by s = kappa
 // log2(e), with the coefficients of sym_coef: then exp(-kappa r) = exp2(-r')
 // with r' = r2' / sqrt(r2') and no multiply for the argument.  Unscreened
-// meshes (kappa = 0, K0) keep their coordinates and skip the exponential:
+// meshes (far_k0: K0) keep their coordinates and skip the exponential:
 // e = 1, so the Yukawa kernels are the Laplace ones.
 //
 // Bound: VALU issue.  A point pair of the direct form costs 6 instructions for
@@ -836,7 +836,7 @@ void launch_far_sym(DevMesh &d)
 {
     SymCoef<float> cf;
     const int form = sym_coef(d, cf);
-    const bool k0 = !(d.prm.kappa > 0.0);
+    const bool k0 = d.far_k0;
     const int nb = d.sym_blocks[sym_form_index(form)];
 #define SYM_RUN(KF)                                                                                             \
     hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, d.sym_nz, cf, d.tri,  \
@@ -854,7 +854,7 @@ void launch_sym_list(DevMesh &d, const int4 *items, int nitems, const int2 *entr
 {
     SymCoef<float> cf;
     const int form = sym_coef(d, cf);
-    const bool k0 = !(d.prm.kappa > 0.0);
+    const bool k0 = d.far_k0;
 #define SYM_RUN_LIST(KF)                                                                                           \
     hipLaunchKernelGGL(KF, dim3(nitems), dim3(64 * kSymWaves), 0, d.stream, d.hm.T, cf, d.tri, d.stat64, tiles, d.dyn32, \
                        items, entries, slots, d.ctl);

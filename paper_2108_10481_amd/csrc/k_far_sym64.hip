@@ -420,7 +420,7 @@ void launch_far_sym64(DevMesh &d)
 {
     SymCoef<double> cf;
     const int form = sym_coef(d, cf);
-    const bool k0 = !(d.prm.kappa > 0.0);
+    const bool k0 = d.far_k0;
     const int nb = d.sym_blocks[sym_form_index(form)];
 #define SYM_RUN(KF)                                                                                              \
     hipLaunchKernelGGL(KF, dim3(nb), dim3(64 * kS64Waves), 0, d.stream, d.hm.T, d.sym_rt, d.sym_nr, d.sym_nz, cf, d.tri,   \

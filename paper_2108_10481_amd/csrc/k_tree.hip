@@ -43,8 +43,9 @@
 // other meets it inside a farther cluster) drops the other side's sums.  Every
 // piece and every side of a pair writes its own slot of 64 x 16 sums; a tile's
 // slots are consecutive and k_tree_finish adds them in FP64.
-// FP64, larger theta (squared distances would cancel), and handles whose memory
-// budget does not hold the slots keep leaves and batches of 64 triangles and one
+// FP64, larger theta (squared distances would cancel), a kappa outside the scaled
+// coordinates' range (far_scale) and handles whose memory budget does not hold the
+// slots keep leaves and batches of 64 triangles and one
 // lane per target (k_tree_eval).
 #include <algorithm>
 #include <cmath>
@@ -453,7 +454,7 @@ bool tree_ordered(const pb_options &o)
 
 Tree *tree_create(DevMesh &d)
 {
-    Tree *t = tree_ordered(d.opt) ? tree_plan(d, true) : nullptr;
+    Tree *t = tree_ordered(d.opt) && d.far_scaled ? tree_plan(d, true) : nullptr;
     return t ? t : tree_plan(d, false);
 }
 
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(256) void k_tree_proxies(int deg, int np, const int
 
 // coefficients of k_tree_far, for coordinates scaled by s
 struct TreeCoef {
-    double s;         // kappa log2(e), 1 for kappa = 0
+    double s;         // kappa log2(e), 1 unscreened
     float kap;        // kappa / s
     float tL, tY;     // of d.n_t qV R3 and E
     float dL, dY;     // of the curl sums
@@ -1047,7 +1048,7 @@ static void tree_launch_tiled(DevMesh &d)
     Tree &tr = *d.tree;
     FarCoef<double> c;
     const int form = far_coef(d, c);
-    const bool k0 = !(d.prm.kappa > 0.0);
+    const bool k0 = d.far_k0;
     TreeCoef tc;
     tc.s = k0 ? 1.0 : d.prm.kappa * 1.4426950408889634;
     tc.kap = (float)(d.prm.kappa / tc.s);

@@ -282,6 +282,8 @@ struct DevMesh {
     GraphGmres *gg[2] = {nullptr, nullptr};   // per operator level
     double t_setup = 0.0;
     double max_edge = 0.0;         // longest triangle edge
+    bool far_k0 = false;           // the far field leaves the screening out (far_scale)
+    bool far_scaled = true;        // kappa is in the range of the kernels on scaled coordinates
     bool want_dense = false;
     // charges workspace
     double *qbuf = nullptr;        // 7 x qcap: SoA x, y, z, q then AoS xyz
@@ -346,7 +348,7 @@ struct FarBatch {
     size_t req_cap = 0, item_cap = 0;
     int first[4] = {0, 0, 0, 0}, nitems[4] = {0, 0, 0, 0}, nblocks[4] = {0, 0, 0, 0};
     // symmetric FP32 items {request, a, b} of the requests with a symmetric split:
-    // queues for forms 0, 1, 3, 4 (kappa > 0), then the same for kappa = 0
+    // queues for forms 0, 1, 3, 4 (screened), then the same without screening
     void *sym_items = nullptr;
     size_t sym_cap = 0;
     int sym_first[8] = {}, sym_n[8] = {}, sym_nblocks[8] = {};

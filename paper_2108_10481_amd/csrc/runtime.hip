@@ -408,6 +408,37 @@ static void setup_and_wait(DevMesh &d)
 
 size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64);
 
+// Longest edge, and what kappa allows the far field.  The symmetric kernels and the
+// tiled treecode work on coordinates scaled by kappa log2(e) (sym_coef).  extent
+// bounds every scaled distance.  FP32: below 2^-26 exp(-kappa r) rounds to 1, so the
+// unscreened variant, unscaled, is exact to rounding; scaled distances of triangles
+// whose edges are below 2^-32 would take r^-3 and its sums out of the range of
+// FP32.  Both precisions: the FP64 exponential and FP32's r^-3 end at 2^30.  What
+// is out of range runs per ordered pair, or by the general treecode, on the
+// coordinates as they are.
+static void far_scale(DevMesh &d)
+{
+    const HostMesh &hm = d.hm;
+    double lo[3] = {hm.xyz[0], hm.xyz[1], hm.xyz[2]}, hi[3] = {lo[0], lo[1], lo[2]}, extent = 0.0, e2min = 0.0, e2max = 0.0;
+    for (size_t i = 0; i < hm.xyz.size(); ++i) {
+        lo[i % 3] = std::min(lo[i % 3], hm.xyz[i]);
+        hi[i % 3] = std::max(hi[i % 3], hm.xyz[i]);
+    }
+    for (int c = 0; c < 3; ++c) extent += hi[c] - lo[c];
+    for (size_t i = 0; i < hm.tri.size(); ++i) {
+        const double *p = &hm.xyz[3 * (size_t)hm.tri[i]], *q = &hm.xyz[3 * (size_t)hm.tri[i % 3 == 2 ? i - 2 : i + 1]];
+        const double dx = p[0] - q[0], dy = p[1] - q[1], dz = p[2] - q[2], e2 = dx * dx + dy * dy + dz * dz;
+        e2min = i == 0 ? e2 : std::min(e2min, e2);
+        e2max = std::max(e2max, e2);
+    }
+    d.max_edge = std::sqrt(e2max);
+    const double kl = d.prm.kappa * 1.4426950408889634;
+    const bool fp32 = d.prm.precision == PB_FP32;
+    d.far_k0 = !(d.prm.kappa > 0.0) || (fp32 && extent * kl < std::ldexp(1.0, -26));
+    d.far_scaled = d.far_k0 || (extent * kl < std::ldexp(1.0, 30) &&
+                                (!fp32 || std::sqrt(e2min) * kl > std::ldexp(1.0, -32)));
+}
+
 static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCache *cache = nullptr)
 {
     check_options(opt);
@@ -427,18 +458,12 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     HIPCHECK(hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking));
     const HostMesh &hm = d->hm;
     const int V = hm.V, T = hm.T;
+    far_scale(*d);
     d->S = opt->source_chunks > 0 ? std::min(opt->source_chunks, T) : choose_chunks(T);
     if (opt->operator_mode == PB_TREECODE) {
         d->tree = tree_create(*d);
         if (tree_splits(*d->tree) > 0) d->S = tree_splits(*d->tree);
     }
-
-    for (size_t i = 0; i < hm.tri.size(); ++i) {
-        const double *p = &hm.xyz[3 * (size_t)hm.tri[i]], *q = &hm.xyz[3 * (size_t)hm.tri[i % 3 == 2 ? i - 2 : i + 1]];
-        const double dx = p[0] - q[0], dy = p[1] - q[1], dz = p[2] - q[2];
-        d->max_edge = std::max(d->max_edge, dx * dx + dy * dy + dz * dz);
-    }
-    d->max_edge = std::sqrt(d->max_edge);
 
     d->xyz = upload(*d, hm.xyz);
     d->tri = upload(*d, hm.tri);
@@ -501,17 +526,8 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     // known to stay matrix-free); under a memory budget the automatic choice
     // takes it where the handle's expected footprint with its slots fits
     bool sym = (fp32 || (opt->precision == PB_FP64 && opt->operator_mode == PB_MATRIX_FREE)) &&
-               opt->operator_mode != PB_TREECODE && d->far_rule == 0 && sym_eligible(T, opt->kappa, fp32 ? opt->far_symmetric : 0);
-    if (sym && !fp32) {
-        // the FP64 kernel's exponential takes scaled distances below 2^30
-        double lo[3] = {hm.xyz[0], hm.xyz[1], hm.xyz[2]}, hi[3] = {lo[0], lo[1], lo[2]}, span = 0.0;
-        for (size_t i = 0; i < hm.xyz.size(); ++i) {
-            lo[i % 3] = std::min(lo[i % 3], hm.xyz[i]);
-            hi[i % 3] = std::max(hi[i % 3], hm.xyz[i]);
-        }
-        for (int c = 0; c < 3; ++c) span += hi[c] - lo[c];
-        sym = span * opt->kappa * 1.4426950408889634 < 1073741824.0;
-    }
+               opt->operator_mode != PB_TREECODE && d->far_rule == 0 && d->far_scaled &&
+               sym_eligible(T, opt->kappa, fp32 ? opt->far_symmetric : 0);
     if (sym && opt->memory_budget && (!fp32 || (opt->far_symmetric == 0 && T < 3584)) &&
         estimate_device_bytes(V, T, opt, true) > opt->memory_budget)
         sym = false;
@@ -522,8 +538,8 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
         d->sym_items = upload(*d, items);
         d->sym_nitems = (int)items.size();
         d->sym_next = (int *)d->alloc(sizeof(int));
-        const bool k0 = !(opt->kappa > 0.0);
-        for (int f = 0; f < kSymForms; ++f) d->sym_blocks[f] = sym_blocks(fp32, d->sym_nitems, kSymFormOf[f], k0);
+        for (int f = 0; f < kSymForms; ++f)
+            d->sym_blocks[f] = sym_blocks(fp32, d->sym_nitems, kSymFormOf[f], d->far_k0);
         d->sym_tiles = (double *)d->alloc(sizeof(double) * kTileRec * ((size_t)(T + kSymTile - 1) / kSymTile));
         part_bytes = std::max(part_bytes,
                               (fp32 ? sizeof(float) : sizeof(double)) * 16 * 2 * (size_t)d->sym_nr * d->sym_nz * T);
@@ -1170,6 +1186,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
         key_append(key, q);
         key_append(key, d.fm);   // the far-field coefficients follow from fm and kappa
         key_append(key, d.prm.kappa);
+        key_append(key, d.far_k0);
         key_append(key, sym);
         key_append(key, d.stat32);
         key_append(key, d.stat64);

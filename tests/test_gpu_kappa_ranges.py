@@ -1,0 +1,82 @@
+"""Screening constants far outside the physical range, where coordinates scaled by
+kappa, their cubes and exponents leave the range of a number format.  A tiny
+positive kappa is no screening to rounding, a huge one leaves the Laplace
+kernels alone; neither may give infinities or NaN.
+
+FP32 far fields are held to the FP64 assembled far field (unscaled coordinates,
+the library's exponential) with the repository's bound for FP32 far fields, 2e-5;
+the treecode adds its own error, below 1e-6 at degree 7 and theta 0.5.  What is
+below FP32's range (Yukawa kernels alone at a huge kappa: 1e-125) is zero there."""
+import numpy as np
+import pytest
+
+import inputs
+
+pytestmark = pytest.mark.gpu
+
+pbm = pytest.importorskip("paper_2108_10481_amd")
+
+TINY = float(np.finfo(np.float32).tiny)
+FORMS = [(pbm.PB_DIRECT_INT, 1.0, 1.0), (pbm.PB_JUFFER, 1.0, 1.0), (pbm.PB_MULLER_EXT, 1.0, 1.0),
+         (pbm.PB_CFIE_EXT, 0.0, 1.0), (pbm.PB_CFIE_EXT, 0.0, 0.0)]   # the last two: some, no Laplace terms
+
+
+def _opts(form, kappa, **kw):
+    return pbm.pb_default_options(formulation=form[0], cfie_alpha=form[1], cfie_beta=form[2], kappa=kappa, **kw)
+
+
+def _far(m, x, opt):
+    with pbm.MeshHandle(m.xyz, m.tri, opt) as h:
+        return pbm.pb_mesh_apply(h, x, pbm.PB_APPLY_FAR_ONLY), h.info()
+
+
+@pytest.fixture(scope="module")
+def star6():
+    return inputs.star_surface(4, 6, 5.0)[0]       # 720 triangles
+
+
+@pytest.fixture(scope="module")
+def star14():
+    return inputs.star_surface(4, 14, 5.0)[0]      # 3920
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("kappa", [1e-300, 1e-20, 1e-14, 1e-13, 1e-12, 1e-10, 1e-9, 1e-6, 1e3, 1e8, 1e12])
+def test_fp32_far_field(star6, star14, form, kappa):
+    for m, modes in ((star6, (dict(), dict(far_symmetric=1), dict(far_symmetric=-1))),
+                     (star14, (dict(), dict(operator_mode=pbm.PB_TREECODE, tree_degree=7, tree_theta=0.5)))):
+        x = np.random.default_rng(41).standard_normal(2 * m.n_vertices)
+        ref, _ = _far(m, x, _opts(form, kappa, operator_mode=pbm.PB_ASSEMBLED))
+        for kw in modes:
+            y, _ = _far(m, x, _opts(form, kappa, precision=pbm.PB_FP32, **kw))
+            assert np.isfinite(y).all(), (m.n_triangles, kw)
+            assert np.linalg.norm(y - ref) <= 2.1e-5 * np.linalg.norm(ref) + TINY, (m.n_triangles, kw)
+
+
+@pytest.mark.parametrize("form", FORMS[:2])
+def test_fp32_graded_edges(form):
+    """Short edges on a large surface: the screening is not below rounding across
+    it, and distances of the short edges' size have cubes out of range."""
+    m = inputs.bipyramid(510, 4.0, 4.0)
+    x = np.random.default_rng(43).standard_normal(2 * m.n_vertices)
+    ref, _ = _far(m, x, _opts(form, 1e-9, operator_mode=pbm.PB_ASSEMBLED))
+    for sym in (0, 1):
+        y, info = _far(m, x, _opts(form, 1e-9, precision=pbm.PB_FP32, far_symmetric=sym))
+        assert info["far_symmetric"] == 0
+        assert np.linalg.norm(y - ref) <= 2.1e-5 * np.linalg.norm(ref)
+
+
+def test_batch_with_negligible_screening():
+    """Requests without screening to rounding beside screened ones, twice the same
+    meshes: bitwise their single solves."""
+    reqs = []
+    for k, kappa in enumerate((1e-14, 0.125, 1e-14, 1e6)):
+        m, shape = inputs.star_surface(7 + k // 2, 5 + k // 2, 5.0)
+        c = inputs.charges_in_star(30 + k, 5, shape)
+        reqs.append((pbm.MeshHandle(m.xyz, m.tri, pbm.pb_default_options(kappa=kappa, precision=pbm.PB_FP32)), (c.xyz, c.q)))
+    hs, sets = [r[0] for r in reqs], [r[1] for r in reqs]
+    single = [pbm.pb_mesh_solve(h, *s) for h, s in zip(hs, sets)]
+    for _ in range(2):
+        for a, b in zip(single, pbm.pb_solve_batch(hs, sets)):
+            assert a["status"] == pbm.PB_OK and np.isfinite(a["dG"])
+            assert a["dG"] == b["dG"] and a["iterations"] == b["iterations"] and np.array_equal(a["phi"], b["phi"])
