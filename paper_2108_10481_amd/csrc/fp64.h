@@ -6,7 +6,7 @@
 
 namespace pbm {
 
-// 2^-r for r >= 0: r = n + f', |f'| <= 1/2, by adding 1.5 2^52 (the low word of
+// 2^-r for 0 <= r < 2^30: r = n + f', |f'| <= 1/2, by adding 1.5 2^52 (the low word of
 // the sum is then -n); 2^f as its degree-11 interpolation at the Chebyshev
 // points of [-1/2, 1/2], relative error 2e-17 (coefficients from that
 // interpolation in 50 digits).  15 instructions, 78 cycles per wavefront

@@ -137,15 +137,16 @@ __device__ inline int ss_order(int t, int s, const int *tv, const int *sv, int *
 // 36 sums need no reduction across lanes, only over the wavefronts (LDS).
 // out[36 p + 4 (3 a + b) + op], op = V_L, K_L, V_Y, K_Y (the four values that one
 // vertex pair's row needs lie together); a, b local vertex ids of t and s in stored
-// order; p = idx[item].  SMALL: every kappa log2(e) r of a near
-// pair is at most kExpSmall, 8 instead of 15 instructions for its exponential.
+// order; p = idx[item].  RANGE 0: every kappa log2(e) r of a near pair is at most
+// kExpSmall, 8 instead of 15 instructions for its exponential; 2: some may pass
+// 2^30, past which exp2neg_n's exponent wraps, and are cut off at 2000 (2^-2000 = 0).
 // Identical triangles lie in one plane: d.n = 0, K = 0, only V is summed.
-// Bound: the FP64 vector rate, 75 instructions per point and pair (68 SMALL; 39
+// Bound: the FP64 vector rate, 75 instructions per point and pair (68 in RANGE 0; 39
 // and 32 for identical triangles); with a group of lanes per pair (points, weights
 // and basis formed by every lane, 36 butterfly reductions) it was about 130.
 // Refresh of a 24500-triangle matrix-free handle (all of the near field): 1.67 ->
 // 0.81 ms (0.71 with k_near_slots as it is below).
-template <int CASE, bool SMALL, int WAVES>
+template <int CASE, int RANGE, int WAVES>
 __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__restrict__ idx,
                                          const int32_t *__restrict__ pair_t, const int32_t *__restrict__ pair_s,
                                          const int32_t *__restrict__ tri, const double *__restrict__ xyz,
@@ -199,7 +200,8 @@ __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__
         double ri[1], ek[1];
         rsqrt3_n<1>(r2, ri);
         ek[0] = kl * r2[0] * ri[0];
-        if (SMALL) exp2small_n<1>(ek);
+        if (RANGE == 2) ek[0] = fmin(ek[0], 2000.0);
+        if (RANGE == 0) exp2small_n<1>(ek);
         else exp2neg_n<1>(ek);
         const double gL = ri[0], gY = ek[0] * ri[0];
         double fL = 0.0, fY = 0.0;
@@ -261,7 +263,7 @@ __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__
 // All pairs in one launch, blocks of 64 pairs of one case: identical, edge, then
 // vertex pairs (fewest, with the most points, first)
 struct SSRange { int first, count, blocks, npts; const double *pts; };
-template <bool SMALL, int WAVES>
+template <int RANGE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_near_ss(SSRange r3, SSRange r2, SSRange r1, const int32_t *__restrict__ idx,
                                                         const int32_t *__restrict__ pair_t,
                                                         const int32_t *__restrict__ pair_s,
@@ -272,18 +274,18 @@ __global__ __launch_bounds__(64 * WAVES) void k_near_ss(SSRange r3, SSRange r2, 
     __shared__ double red[WAVES - 1][18][64];
     int b = blockIdx.x;
     if (b < r3.blocks) {
-        ss_pairs<3, SMALL, WAVES>(64 * b, r3.count, idx + r3.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r3.pts,
+        ss_pairs<3, RANGE, WAVES>(64 * b, r3.count, idx + r3.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r3.pts,
                                   r3.npts, out, red);
         return;
     }
     b -= r3.blocks;
     if (b < r2.blocks) {
-        ss_pairs<2, SMALL, WAVES>(64 * b, r2.count, idx + r2.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r2.pts,
+        ss_pairs<2, RANGE, WAVES>(64 * b, r2.count, idx + r2.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r2.pts,
                                   r2.npts, out, red);
         return;
     }
     b -= r2.blocks;
-    ss_pairs<1, SMALL, WAVES>(64 * b, r1.count, idx + r1.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r1.pts, r1.npts,
+    ss_pairs<1, RANGE, WAVES>(64 * b, r1.count, idx + r1.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r1.pts, r1.npts,
                               out, red);
 }
 
@@ -321,17 +323,20 @@ static void launch_ss(DevMesh &d, const int count[4], const int32_t *idx, const 
     }
     const double kl = d.prm.kappa * 1.4426950408889634;
     // a near pair's points are at most two longest edges apart
-    const bool small = 2.0 * d.max_edge * kl <= kExpSmall;
-#define SS_RUN(SM, W)                                                                                               \
-    hipLaunchKernelGGL((k_near_ss<SM, W>), dim3(blocks), dim3(64 * W), 0, d.stream, r[3], r[2], r[1], idx, pt, ps, \
+    const double reach = 2.0 * d.max_edge * kl;
+    const int range = reach <= kExpSmall ? 0 : reach < 1073741824.0 ? 1 : 2;
+#define SS_RUN(E, W)                                                                                                \
+    hipLaunchKernelGGL((k_near_ss<E, W>), dim3(blocks), dim3(64 * W), 0, d.stream, r[3], r[2], r[1], idx, pt, ps, \
                        d.tri, d.xyz, d.geo, kl, d.prm.kappa, out)
     // eight wavefronts share a block's pairs while four would leave compute units idle
     if (blocks < 256) {
-        if (small) SS_RUN(true, 8);
-        else SS_RUN(false, 8);
+        if (range == 0) SS_RUN(0, 8);
+        else if (range == 1) SS_RUN(1, 8);
+        else SS_RUN(2, 8);
     } else {
-        if (small) SS_RUN(true, 4);
-        else SS_RUN(false, 4);
+        if (range == 0) SS_RUN(0, 4);
+        else if (range == 1) SS_RUN(1, 4);
+        else SS_RUN(2, 4);
     }
 #undef SS_RUN
     HIPCHECK(hipGetLastError());

@@ -80,3 +80,36 @@ def test_batch_with_negligible_screening():
         for a, b in zip(single, pbm.pb_solve_batch(hs, sets)):
             assert a["status"] == pbm.PB_OK and np.isfinite(a["dG"])
             assert a["dG"] == b["dG"] and a["iterations"] == b["iterations"] and np.array_equal(a["phi"], b["phi"])
+
+
+@pytest.mark.parametrize("kappa", [2e8, 1e9, 3e9, 4.5e9, 1e10, 1e12])
+def test_near_blocks_at_huge_kappa(star6, kappa):
+    """Sauter-Schwab blocks past the exponent range of the near field's exponential:
+    at 4 Gauss points r is above 1e-6 edge lengths at every point, so exp(-kappa r)
+    is below exp(-100) of the Laplace kernel's value, K_Y's by a further kappa r;
+    the Laplace blocks do not see kappa."""
+    t = np.repeat(np.arange(6, dtype=np.int32), star6.n_triangles)
+    s = np.tile(np.arange(star6.n_triangles, dtype=np.int32), 6)
+    share = (star6.tri[t][:, :, None] == star6.tri[s][:, None, :]).any(axis=(1, 2))
+    t, s = t[share], s[share]
+    with pbm.MeshHandle(star6.xyz, star6.tri, pbm.pb_default_options(kappa=kappa)) as h:
+        b = pbm.pb_mesh_near_blocks(h, t, s)
+    with pbm.MeshHandle(star6.xyz, star6.tri, pbm.pb_default_options(kappa=0.125)) as h:
+        ref = pbm.pb_mesh_near_blocks(h, t, s)
+    assert np.isfinite(b).all()
+    assert np.abs(b[:, 2:]).max() <= 1e-30 * np.abs(ref[:, :2]).max()
+    assert np.abs(b[:, :2] - ref[:, :2]).max() <= 1e-14 * np.abs(ref[:, :2]).max()
+
+
+@pytest.mark.parametrize("precision", [pbm.PB_FP64, pbm.PB_FP32])
+def test_solve_at_huge_kappa(star6, precision):
+    """The solution no longer depends on kappa once every exponential has
+    underflowed: kappa 1e12 against 1e8, to the solver's tolerance."""
+    c = inputs.charges_ball(51, 5, 1.0)
+    out = []
+    for kappa in (1e8, 1e12):
+        with pbm.MeshHandle(star6.xyz, star6.tri, pbm.pb_default_options(kappa=kappa, precision=precision, tol=1e-7)) as h:
+            out.append(pbm.pb_mesh_solve(h, c.xyz, c.q))
+    a, b = out
+    assert a["status"] == b["status"] == pbm.PB_OK
+    assert abs(a["dG"] - b["dG"]) <= 1e-5 * abs(a["dG"])
