@@ -2,6 +2,8 @@
 // (k_tree.hip) products: coefficients, math helpers, one source triangle's
 // regular-rule sums against a target triangle.
 #pragma once
+#include <cmath>
+
 #include "pbm_internal.h"
 
 namespace pbm {
@@ -303,8 +305,9 @@ inline int far_coef(const DevMesh &d, FarCoef<R> &cf)
 // exp2(-r'), so the K- and T-type coefficients take s^2, the V- and D-type ones
 // s, and kappa becomes kappa / s.  Unscreened (far_k0), s = 1: coordinates and
 // coefficients as they are.  Returns the kernel FORM: 0 (direct), 1
-// (every operator has a Laplace term: its coefficient is taken out), 3 (none
-// has), 4 (some have: a combined field with one zero constant).
+// (every operator has a Laplace term, not tiny beside its Yukawa one: its
+// coefficient is taken out), 3 (none has), 4 (else: a combined field with a zero or
+// tiny constant).
 template <typename R>
 inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
 {
@@ -320,7 +323,11 @@ inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
         sc.cT = (R)(c.kY * s2); sc.cD = (R)(c.vY * s);
         return 0;
     }
-    if (form == 1 && !(c.cKL != 0.0 && c.cVL != 0.0 && c.cTL != 0.0 && c.cDL != 0.0)) form = 4;
+    // the ratio of FORM 1 stays far inside FP32's range (constants of the combined
+    // field may be tiny): 2^40 leaves the sums of r^-3 and of its multiple apart
+    auto factors = [](double L, double Y) { return L != 0.0 && std::fabs(Y) <= 1099511627776.0 * std::fabs(L); };
+    if (form == 1 && !(factors(c.cKL, c.cKY) && factors(c.cVL, c.cVY) && factors(c.cTL, c.cTY) && factors(c.cDL, c.cDY)))
+        form = 4;
     if (form == 1) {
         sc.cK = (R)(c.cKL * s2); sc.cV = (R)(c.cVL * s);
         sc.cT = (R)(c.cTL * s2); sc.cD = (R)(c.cDL * s);

@@ -113,3 +113,16 @@ def test_solve_at_huge_kappa(star6, precision):
     a, b = out
     assert a["status"] == b["status"] == pbm.PB_OK
     assert abs(a["dG"] - b["dG"]) <= 1e-5 * abs(a["dG"])
+
+
+@pytest.mark.parametrize("alpha,beta", [(1e-42, 1.0), (1.0, 1e-42), (1e-30, 1e-30), (1e-11, 1e-13), (1e-42, 0.0)])
+@pytest.mark.parametrize("mode", [pbm.PB_MATRIX_FREE, pbm.PB_TREECODE])
+def test_fp32_tiny_combined_field_constants(star14, alpha, beta, mode):
+    """Combined fields whose Laplace terms are tiny beside the Yukawa ones, over the
+    range of FP32 as a ratio, against the FP64 matrix-free far field; bounds as above."""
+    x = np.random.default_rng(47).standard_normal(2 * star14.n_vertices)
+    form = (pbm.PB_CFIE_EXT, alpha, beta)
+    ref, _ = _far(star14, x, _opts(form, 0.125))
+    y, _ = _far(star14, x, _opts(form, 0.125, precision=pbm.PB_FP32, operator_mode=mode, tree_degree=7, tree_theta=0.5))
+    assert np.isfinite(y).all()
+    assert np.linalg.norm(y - ref) <= 2.1e-5 * np.linalg.norm(ref)
