@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void k_reaction(int T, int npts, int C, int ch
     const int c = id % C, k = (id / C) * 64 + ((int)threadIdx.x & 63);
     if ((id / C) * 64 >= npts) return;
     const int kc = min(k, npts - 1);
-    const double x = pts[3 * kc], y = pts[3 * kc + 1], z = pts[3 * kc + 2];
+    const double x = point_cut(pts[3 * kc]), y = point_cut(pts[3 * kc + 1]), z = point_cut(pts[3 * kc + 2]);
     const int s0 = c * chunk, s1 = min(T, s0 + chunk);
     using CD = const __attribute__((address_space(4))) double *;
     double acc = 0.0;

@@ -64,6 +64,15 @@ struct HostMesh {
     std::vector<int32_t> slot_ptr;    // nnz + 1
     std::vector<uint32_t> slot_code;  // p << 4 | k << 2 | l per contribution, in row visiting order
 };
+// Coordinates of charges and evaluation points past 5e153 are moved there: their
+// squared distances would be infinite, which rsqrt3_n turns into NaN, and what they
+// contribute is 0 to any rounding.  Infinities and NaN stay.
+__host__ __device__ inline double point_cut(double v)
+{
+    const double m = v < 0.0 ? -v : v;
+    return m > 5e153 && m <= 1.7976931348623157e308 ? (v < 0.0 ? -5e153 : 5e153) : v;
+}
+
 constexpr int kSymTile = 64;   // triangles per tile of the symmetric far field and the tiled treecode
 
 // tile > 0: order the triangles by a balanced k-d tree over tiles of that many

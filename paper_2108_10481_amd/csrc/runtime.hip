@@ -1424,7 +1424,7 @@ void charges_to_device(DevMesh &d, const pb_charges *c)
     std::vector<double> h(7 * (size_t)nq);
     for (int i = 0; i < nq; ++i) {
         for (int c3 = 0; c3 < 3; ++c3) {
-            h[(size_t)c3 * nq + i] = c->xyz[3 * i + c3];
+            h[(size_t)c3 * nq + i] = point_cut(c->xyz[3 * i + c3]);
             h[(size_t)4 * nq + 3 * i + c3] = c->xyz[3 * i + c3];
         }
         h[(size_t)3 * nq + i] = c->q[i];
