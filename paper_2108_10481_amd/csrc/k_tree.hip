@@ -44,8 +44,8 @@
 // piece and every side of a pair writes its own slot of 64 x 16 sums; a tile's
 // slots are consecutive and k_tree_finish adds them in FP64.
 // FP64, larger theta (squared distances would cancel), a kappa outside the scaled
-// coordinates' range (far_scale) and handles whose memory budget does not hold the
-// slots keep leaves and batches of 64 triangles and one
+// coordinates' range (far_scale) and handles with no room for the slots (slots_fit)
+// keep leaves and batches of 64 triangles and one
 // lane per target (k_tree_eval).
 #include <algorithm>
 #include <cmath>
@@ -220,12 +220,18 @@ void plan_tiles(const HostMesh &hm, Tree &tr, const std::vector<std::vector<int3
     std::stable_sort(pl.near_items.begin(), pl.near_items.end(), longer);
 }
 
-// What an admission estimate charges for a treecode handle's partial sums
-// (estimate_device_bytes): slots past it are taken only without a budget.
-double charged_sums(const DevMesh &d)
+// Whether the tiled path's slots are taken.  Listed direct pairs grow like T^2 as
+// theta goes to 0 and each has its slot, while the general path's sums are bounded:
+// up to what an admission estimate charges for those (estimate_device_bytes)
+// always; without a budget up to four times that and half of the free memory
+// (theta 0.2 at 450000 triangles: 2.1 times, 416 ms per product against 744).
+bool slots_fit(const DevMesh &d, size_t bytes)
 {
-    const double t = d.hm.T;
-    return 128.0 * t * (d.S + std::min(64.0, 4.0 * std::ceil(65536.0 / std::ceil(t / 64.0))));
+    const double t = d.hm.T, charged = 128.0 * t * (d.S + std::min(64.0, 4.0 * std::ceil(65536.0 / std::ceil(t / 64.0))));
+    if ((double)bytes <= charged) return true;
+    size_t free_bytes = 0, total = 0;
+    if (d.opt.memory_budget || (double)bytes > 4.0 * charged) return false;
+    return hipMemGetInfo(&free_bytes, &total) == hipSuccess && bytes <= free_bytes / 2;
 }
 
 }  // namespace
@@ -317,7 +323,7 @@ static Tree *tree_plan(DevMesh &d, bool tiled)
     TilePlan tp;
     if (tiled) {
         plan_tiles(hm, *tr, far_of_tile, near_of_tile, tp);
-        if (d.opt.memory_budget && (double)tree_slot_bytes(*tr) > charged_sums(d)) return nullptr;
+        if (!slots_fit(d, tree_slot_bytes(*tr))) return nullptr;
     }
     // Pieces of about equal work over the whole mesh (a batch's list is cut
     // into a number of pieces proportional to its work; about 64 per SIMD in

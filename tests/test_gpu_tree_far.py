@@ -46,3 +46,34 @@ def test_tiled_treecode_matches_direct(mesh, degree, theta, form, kappa):
     print("%.2e %.2e" % (np.linalg.norm(d64) / scale, np.linalg.norm(d32) / scale))
     assert np.linalg.norm(d32) < 2 * np.linalg.norm(d64) + tol * scale
     assert np.abs(d32).max() < 2 * np.abs(d64).max() + 10 * tol * top
+
+
+def test_memory_stays_bounded_at_small_theta():
+    """Nearly every pair of tiles direct: the handle stays within its estimate (a slot
+    per pair would take 20 GB)."""
+    m = inputs.star_surface(4, 100, 28.0)[0]      # 200000 triangles
+    opt = pbm.pb_default_options(precision=pbm.PB_FP32, operator_mode=pbm.PB_TREECODE, tree_degree=2, tree_theta=0.01)
+    with pbm.MeshHandle(m.xyz, m.tri, opt) as h:
+        assert h.info()["device_bytes"] <= pbm.pb_estimate_device_bytes(m.xyz, m.tri, opt)
+
+
+@pytest.mark.parametrize("form", [pbm.PB_DIRECT_EXT_PERM, pbm.PB_JUFFER])
+@pytest.mark.parametrize("theta,degree", [(0.01, 2), (0.25, 7)])
+def test_general_path_on_the_tile_order(form, theta, degree):
+    """Under a memory budget that leaves the tiles' slots out, the general path runs
+    on the triangles' k-d order; tolerance as above."""
+    m = inputs.star_surface(4, 32, 9.0)[0]        # 20480 triangles, 320 tiles
+    x = np.random.default_rng(31).standard_normal(2 * m.n_vertices)
+    tree = dict(operator_mode=pbm.PB_TREECODE, tree_degree=degree, tree_theta=theta, source_chunks=1)
+    out = []
+    for kw in (dict(), dict(tree), dict(tree, precision=pbm.PB_FP32), dict(tree, precision=pbm.PB_FP32)):
+        opt = pbm.pb_default_options(formulation=form, **kw)
+        if len(out) == 3:
+            opt.memory_budget = pbm.pb_estimate_device_bytes(m.xyz, m.tri, opt)
+        with pbm.MeshHandle(m.xyz, m.tri, opt) as h:
+            out.append(pbm.pb_mesh_apply(h, x))
+    ref, y64, tiled, general = out
+    assert not np.array_equal(tiled, general)
+    scale, err64 = np.linalg.norm(ref), np.linalg.norm(y64 - ref)
+    for y in (tiled, general):
+        assert np.linalg.norm(y - ref) < 2 * err64 + (2e-7 + 2e-6) * scale
