@@ -299,7 +299,7 @@ struct DevMesh {
     int qcap = 0;
     double *fpts = nullptr;        // 2 x T x 6 (RHS point values)
     double *red = nullptr;         // reduction scratch
-    int redcap = 0;
+    size_t redcap = 0;
     Dense *dense = nullptr;
     const int32_t *dense_vpos = nullptr;   // vertex -> row of the dense far field
     Tree *tree = nullptr;                  // treecode plan (PB_TREECODE)
@@ -327,6 +327,7 @@ struct DevMesh {
     double *dync64 = nullptr;   // the same weights in FP64 (far_rule 2, FP64 precision)
     int64_t nnz() const { return (int64_t)hm.col.size(); }
     void *alloc(size_t n);
+    void give_back(void *p, size_t n);
     ~DevMesh();
 };
 

@@ -155,6 +155,17 @@ void *DevMesh::alloc(size_t n)
     return p;
 }
 
+// frees one allocation of n bytes early, in stream order (a block of a server's
+// cache stays until the handle goes)
+void DevMesh::give_back(void *p, size_t n)
+{
+    auto it = std::find(allocs.begin(), allocs.end(), p);
+    if (it == allocs.end()) return;
+    HIPCHECK(hipFreeAsync(p, stream));
+    allocs.erase(it);
+    bytes -= std::max<size_t>(n, 256);
+}
+
 DevMesh::~DevMesh()
 {
     if (stream) (void)hipStreamSynchronize(stream);
@@ -1432,11 +1443,17 @@ void charges_to_device(DevMesh &d, const pb_charges *c)
     HIPCHECK(hipMemcpyAsync(d.qbuf, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, d.stream));
 }
 
+// Scratch for sums over sources: the far field's partial sums (at least 16 doubles
+// per triangle and source chunk) where they hold it, else a buffer that grows
 static double *reduction_buffer(DevMesh &d, size_t need)
 {
-    if (need > (size_t)d.redcap) {
+    if (need <= 16 * (size_t)d.S * d.hm.T) return (double *)d.part;
+    if (need > d.redcap) {
+        if (d.red) d.give_back(d.red, sizeof(double) * d.redcap);
+        d.red = nullptr;
+        d.redcap = 0;
         d.red = (double *)d.alloc(sizeof(double) * need);
-        d.redcap = (int)need;
+        d.redcap = need;
     }
     return d.red;
 }
