@@ -538,8 +538,11 @@ static void batch_plan(const std::vector<DevMesh *> &ds, const std::vector<int> 
             const int sform = sym_coef(d, rq.sc);
             rq.stat64 = d.stat64;
             rq.tiles = d.sym_tiles;
+            rq.rt = d.sym_rt;
+            rq.nr = d.sym_nr;
+            rq.nz = d.sym_nz;
             std::vector<int4> its;
-            sym_plan(T, sizeof(R) == 4, r, rq.rt, rq.nr, rq.nz, its);
+            sym_items(T, SymSplit{d.sym_rt, d.sym_nr, d.sym_nz}, r, its);
             const int rt = rq.rt;
             const int sf = sym_form_index(sform) + (d.far_k0 ? kSymForms : 0);
             const int ntile = (T + kSymTile - 1) / kSymTile;

@@ -749,28 +749,37 @@ bool sym_eligible(int T, double kappa, int mode)
 // pairs per lane, 16 for each wavefront) is cut into nz parts where the items
 // are few for the 512 resident blocks: into two below 2048 items, further below
 // 600 (measured per product, 1620 triangles / 351 items: 2 parts 138 us, 8 172 us,
-// 16 226 us; 3380 triangles / 1431 items: 1 part 444 us, 2 416 us).  Items {request, a, b, part}; larger ones come
-// first, among equal ones those near the diagonal, whose tiles touch and take
-// longer, so that the list ends with the lightest.
-void sym_plan(int T, bool fp32, int request, int &rt, int &nr, int &nz, std::vector<int4> &items)
+// 16 226 us; 3380 triangles / 1431 items: 1 part 444 us, 2 416 us).  parts
+// false: items stay whole (no room for the parts' slots under a memory budget).
+SymSplit sym_split(int T, bool fp32, bool parts)
 {
     const int most = fp32 ? 320 : kSym64Ranges, ntile = (T + kSymTile - 1) / kSymTile;
-    rt = std::max(1, (ntile + most - 1) / most);
-    nr = (ntile + rt - 1) / rt;
-    nz = 1;
-    const int n = nr * (nr + 1) / 2;
+    SymSplit s;
+    s.rt = std::max(1, (ntile + most - 1) / most);
+    s.nr = (ntile + s.rt - 1) / s.rt;
+    const int n = s.nr * (s.nr + 1) / 2;
+    if (!parts) return s;
     if (fp32) {
-        while (nz < 4 && n * nz < 400) nz *= 2;
+        while (s.nz < 4 && n * s.nz < 400) s.nz *= 2;
     } else {
-        while (nz < 16 && n * nz < (nz == 1 ? 2048 : 600)) nz *= 2;
+        while (s.nz < 16 && n * s.nz < (s.nz == 1 ? 2048 : 600)) s.nz *= 2;
     }
+    return s;
+}
+
+// Items {request, a, b, part}; larger ones come first, among equal ones those near
+// the diagonal, whose tiles touch and take longer, so that the list ends with the
+// lightest.
+void sym_items(int T, const SymSplit &s, int request, std::vector<int4> &items)
+{
+    const int ntile = (T + kSymTile - 1) / kSymTile, rt = s.rt;
     std::vector<std::pair<int, int4>> w;
-    for (int k = 0; k < nr; ++k)
-        for (int a = 0; a + k < nr; ++a) {
+    for (int k = 0; k < s.nr; ++k)
+        for (int a = 0; a + k < s.nr; ++a) {
             const int b = a + k;
             const int na = std::min(ntile, (a + 1) * rt) - a * rt, nb = std::min(ntile, (b + 1) * rt) - b * rt;
             const int pairs = a == b ? na * (na + 1) / 2 : na * nb;
-            for (int z = 0; z < nz; ++z) w.push_back({pairs, make_int4(request, a, b, z)});
+            for (int z = 0; z < s.nz; ++z) w.push_back({pairs, make_int4(request, a, b, z)});
         }
     std::stable_sort(w.begin(), w.end(), [](const std::pair<int, int4> &x, const std::pair<int, int4> &y) {
         return x.first > y.first;

@@ -386,7 +386,12 @@ void ss_group(const std::vector<int32_t> &tri, int n, const int32_t *t, const in
 int choose_chunks(int T);
 // symmetric far field (k_far_sym.hip)
 bool sym_eligible(int T, double kappa, int mode);
-void sym_plan(int T, bool fp32, int request, int &rt, int &nr, int &nz, std::vector<int4> &items);
+struct SymSplit {
+    int rt = 1, nr = 1, nz = 1;   // tiles per range, ranges, parts of an item
+    size_t slots() const { return 2 * (size_t)nr * nz; }   // of 16 values per triangle
+};
+SymSplit sym_split(int T, bool fp32, bool parts);
+void sym_items(int T, const SymSplit &s, int request, std::vector<int4> &items);
 int resident_blocks(const void *kernel, int threads, int nitems);
 int sym_blocks(bool fp32, int nitems, int form, bool k0);
 void launch_sym_reset(hipStream_t s, int *next);

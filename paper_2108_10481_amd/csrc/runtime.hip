@@ -417,7 +417,7 @@ static void setup_and_wait(DevMesh &d)
     HIPCHECK(hipStreamSynchronize(d.stream));
 }
 
-size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64);
+size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots);
 
 // Longest edge, and what kappa allows the far field.  The symmetric kernels and the
 // tiled treecode work on coordinates scaled by kappa log2(e) (sym_coef).  extent
@@ -544,16 +544,19 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
         sym = false;
     if (sym) {
         // 2 nr nz slots of 16 values per triangle
+        const SymSplit sp = sym_split(T, fp32, true);
         std::vector<int4> items;
-        sym_plan(T, fp32, 0, d->sym_rt, d->sym_nr, d->sym_nz, items);
+        sym_items(T, sp, 0, items);
+        d->sym_rt = sp.rt;
+        d->sym_nr = sp.nr;
+        d->sym_nz = sp.nz;
         d->sym_items = upload(*d, items);
         d->sym_nitems = (int)items.size();
         d->sym_next = (int *)d->alloc(sizeof(int));
         for (int f = 0; f < kSymForms; ++f)
             d->sym_blocks[f] = sym_blocks(fp32, d->sym_nitems, kSymFormOf[f], d->far_k0);
         d->sym_tiles = (double *)d->alloc(sizeof(double) * kTileRec * ((size_t)(T + kSymTile - 1) / kSymTile));
-        part_bytes = std::max(part_bytes,
-                              (fp32 ? sizeof(float) : sizeof(double)) * 16 * 2 * (size_t)d->sym_nr * d->sym_nz * T);
+        part_bytes = std::max(part_bytes, (fp32 ? sizeof(float) : sizeof(double)) * 16 * sp.slots() * T);
     }
     d->part = d->alloc(part_bytes);
     d->triout = (double *)d->alloc(sizeof(double) * 6 * T);
@@ -584,8 +587,8 @@ DevMesh *create_mesh_checked(const pb_mesh *mesh, const pb_options *opt, BlockCa
 // near blocks (about 14 T pairs and 20 V nonzeros per block on molecular
 // surfaces, with margin), work vectors, the Arnoldi basis, and the dense far
 // field in assembled modes.
-// sym64: a matrix-free FP64 handle takes the symmetric split's slots
-size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64)
+// slots: a matrix-free FP64 handle takes the symmetric split's slots
+size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots)
 {
     const double v = V, t = T, n = 2.0 * V;
     // a buffer of kCacheMin bytes or more may come from a server's block cache,
@@ -594,19 +597,11 @@ size_t estimate_device_bytes(int V, int T, const pb_options *o, bool sym64)
     const int S = o->source_chunks > 0 ? std::min(o->source_chunks, T) : choose_chunks(T);
     double b = t * (kGeo * 8 + kStat * 12 + kDyn * 12 + 6 * 8 + 12 * 8 + 3 * 4 * 2);
     double part = (double)S * t * 16 * 8;
-    if (o->precision == PB_FP32 && o->operator_mode != PB_TREECODE && o->regular_order != 1 &&
-        sym_eligible(T, o->kappa, o->far_symmetric)) {
-        int rt, nr, nz;
-        std::vector<int4> items;
-        sym_plan(T, true, 0, rt, nr, nz, items);
-        part = std::max(part, 2.0 * nr * nz * t * 16 * 4);   // the symmetric far field's slots
-    }
-    if (sym64 && o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE && o->regular_order != 1) {
-        int rt, nr, nz;
-        std::vector<int4> items;
-        sym_plan(T, false, 0, rt, nr, nz, items);
-        part = std::max(part, 2.0 * nr * nz * t * 16 * 8);
-    }
+    const bool fp32 = o->precision == PB_FP32;
+    if (o->operator_mode != PB_TREECODE && o->regular_order != 1 &&
+        ((fp32 && sym_eligible(T, o->kappa, o->far_symmetric)) ||
+         (slots && o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE)))
+        part = std::max(part, (double)sym_split(T, fp32, true).slots() * t * 16 * (fp32 ? 4 : 8));
     b += buf(part);
     b += buf(16.0 * t * (36 * 8 + 3 * 4));
     b += 24.0 * v * (4 * 8 + 4) + v * (4 * 8 + 4 * 4);

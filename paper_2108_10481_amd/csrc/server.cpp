@@ -21,7 +21,7 @@
 
 namespace pbm {
 DevMesh *create_mesh_checked(const pb_mesh *mesh, const pb_options *opt, BlockCache *cache);
-size_t estimate_device_bytes(int V, int T, const pb_options *opt, bool sym64);
+size_t estimate_device_bytes(int V, int T, const pb_options *opt, bool slots);
 }  // namespace pbm
 
 using namespace pbm;
@@ -221,7 +221,7 @@ pb_status pb_submit(pb_server *s, const pb_mesh *mesh, const pb_charges *charges
     r->q.assign(charges->q, charges->q + charges->n);
     r->opt = *opt;
     r->est = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt, true);
-    // an FP64 handle that its symmetric split's slots would keep out runs per ordered pair
+    // a handle that its symmetric split's slots would keep out does with fewer or none
     if (r->est > s->budget) r->est = estimate_device_bytes(mesh->n_vertices, mesh->n_triangles, opt, false);
     if (r->est > s->budget) fail(PB_E_NOMEM, "request footprint exceeds the server's device-memory budget");
     // the handle may not outgrow its admission footprint
