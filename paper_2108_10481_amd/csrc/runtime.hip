@@ -419,6 +419,13 @@ static void setup_and_wait(DevMesh &d)
 
 size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots);
 
+// the symmetric split is a choice that a handle without room for its slots leaves
+// out: in FP64, and on small FP32 meshes by the automatic choice
+static bool sym_optional(const pb_options *o, int T)
+{
+    return o->precision == PB_FP64 || (o->far_symmetric == 0 && T < 3584);
+}
+
 // Longest edge, and what kappa allows the far field.  The symmetric kernels and the
 // tiled treecode work on coordinates scaled by kappa log2(e) (sym_coef).  extent
 // bounds every scaled distance.  FP32: below 2^-26 exp(-kappa r) rounds to 1, so the
@@ -539,12 +546,11 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     bool sym = (fp32 || (opt->precision == PB_FP64 && opt->operator_mode == PB_MATRIX_FREE)) &&
                opt->operator_mode != PB_TREECODE && d->far_rule == 0 && d->far_scaled &&
                sym_eligible(T, opt->kappa, fp32 ? opt->far_symmetric : 0);
-    if (sym && opt->memory_budget && (!fp32 || (opt->far_symmetric == 0 && T < 3584)) &&
-        estimate_device_bytes(V, T, opt, true) > opt->memory_budget)
-        sym = false;
+    const bool room = !sym || !opt->memory_budget || estimate_device_bytes(V, T, opt, true) <= opt->memory_budget;
+    if (!room && sym_optional(opt, T)) sym = false;
     if (sym) {
         // 2 nr nz slots of 16 values per triangle
-        const SymSplit sp = sym_split(T, fp32, true);
+        const SymSplit sp = sym_split(T, fp32, room);
         std::vector<int4> items;
         sym_items(T, sp, 0, items);
         d->sym_rt = sp.rt;
@@ -587,7 +593,8 @@ DevMesh *create_mesh_checked(const pb_mesh *mesh, const pb_options *opt, BlockCa
 // near blocks (about 14 T pairs and 20 V nonzeros per block on molecular
 // surfaces, with margin), work vectors, the Arnoldi basis, and the dense far
 // field in assembled modes.
-// slots: a matrix-free FP64 handle takes the symmetric split's slots
+// slots: the symmetric split's partial sums as they are without a budget, else only
+// what the handle cannot fall back from
 size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots)
 {
     const double v = V, t = T, n = 2.0 * V;
@@ -600,8 +607,9 @@ size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots)
     const bool fp32 = o->precision == PB_FP32;
     if (o->operator_mode != PB_TREECODE && o->regular_order != 1 &&
         ((fp32 && sym_eligible(T, o->kappa, o->far_symmetric)) ||
-         (slots && o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE)))
-        part = std::max(part, (double)sym_split(T, fp32, true).slots() * t * 16 * (fp32 ? 4 : 8));
+         (o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE)) &&
+        (slots || !sym_optional(o, T)))
+        part = std::max(part, (double)sym_split(T, fp32, slots).slots() * t * 16 * (fp32 ? 4 : 8));
     b += buf(part);
     b += buf(16.0 * t * (36 * 8 + 3 * 4));
     b += 24.0 * v * (4 * 8 + 4) + v * (4 * 8 + 4 * 4);

@@ -37,3 +37,36 @@ def test_potentials_of_growing_point_sets(npts, budget):
                 top = n
         held = h.info()["device_bytes"] - before
     assert held <= sum(grown) + 8 * (2 ** 18 + max(npts))
+
+
+@pytest.mark.parametrize("freq", [6, 13])         # 720 and 3380 triangles
+@pytest.mark.parametrize("kw", [dict(), dict(precision=pbm.PB_FP32), dict(precision=pbm.PB_FP32, far_symmetric=1)])
+def test_products_without_room_for_the_split(freq, kw):
+    """A budget without room for the symmetric split's slots: per ordered pair (with
+    far_symmetric 1: whole items), against the product without a budget; FP64 1e-12,
+    FP32 2e-6 as elsewhere.  Alone and served the solve is bitwise the same."""
+    m, shape = inputs.star_surface(4, freq, 5.0)
+    c = inputs.charges_in_star(6, 5, shape)
+    x = np.random.default_rng(29).standard_normal(2 * m.n_vertices)
+    opt = pbm.pb_default_options(formulation=pbm.PB_JUFFER, **kw)
+    lean = dict(kw, far_symmetric=-1) if kw else dict(operator_mode=pbm.PB_AUTO)
+    budget = pbm.pb_estimate_device_bytes(m.xyz, m.tri, pbm.pb_default_options(formulation=pbm.PB_JUFFER, **lean))
+    with pbm.MeshHandle(m.xyz, m.tri, opt) as h:
+        ref = pbm.pb_mesh_apply(h, x)
+        full = h.info()
+    tight = pbm.pb_default_options(formulation=pbm.PB_JUFFER, memory_budget=budget, **kw)
+    with pbm.MeshHandle(m.xyz, m.tri, tight) as h:
+        y = pbm.pb_mesh_apply(h, x)
+        info = h.info()
+        alone = pbm.pb_mesh_solve(h, c.xyz, c.q)
+    assert info["device_bytes"] <= budget
+    if pbm.pb_estimate_device_bytes(m.xyz, m.tri, opt) > budget:
+        assert info["device_bytes"] < full["device_bytes"]
+        if kw.get("far_symmetric") != 1:
+            assert info["far_symmetric"] == 0
+    tol = 2e-6 if kw else 1e-12
+    assert np.linalg.norm(y - ref) <= tol * np.linalg.norm(ref)
+    with pbm.Server(hbm_budget=budget, max_slots=1) as s:
+        served = s.wait(s.submit(m.xyz, m.tri, c.xyz, c.q, opt))
+    assert served["status"] == pbm.PB_OK
+    assert served["dG"] == alone["dG"] and np.array_equal(served["phi"], alone["phi"])
