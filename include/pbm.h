@@ -152,7 +152,9 @@ typedef struct {
     double tol;               /* relative preconditioned residual (paper: 1e-5) */
     int32_t max_iter;         /* GMRES iterations (no restart), default 1000 */
     int32_t singular_order;   /* Gauss points per dimension, Sauter-Schwab (default 4) */
-    int32_t source_chunks;    /* far-field split of the source range; 0 = automatic */
+    int32_t source_chunks;    /* per-ordered-pair far field: split of the source range; 0 =
+                                 automatic.  With far_symmetric 0 a given split keeps FP64 and
+                                 small FP32 products per ordered pair (see far_symmetric) */
     int32_t inner_max_iter;   /* mixed modes: inner GMRES cap (default 200) */
     double inner_tol;         /* mixed modes: inner relative tolerance (default 1e-3) */
     size_t memory_budget;     /* bytes the handle may hold on the device; 0 = 90% of free */
@@ -174,14 +176,24 @@ typedef struct {
                                  triangle; 1: the one-point (centroid) rule, matrix-free in FP64
                                  or FP32 only, not with the Calderon preconditioners.  The source
                                  projections and Delta G always use the 6-point rule. */
-    int32_t far_symmetric;    /* FP32 matrix-free far field, screened or not (Numerical
+    int32_t far_symmetric;    /* matrix-free far field, screened or not (Numerical
                                  discretization; the kernels are symmetric in x, y): every
                                  unordered triangle pair evaluated once for both directions or
-                                 every ordered pair.  0 (default, automatic): once per unordered
-                                 pair (faster at every size); 1: once per unordered pair; -1: per
-                                 ordered pair.  Single and batched solves of a handle use the same
+                                 every ordered pair.  PB_FP32, and PB_FP64 with PB_MATRIX_FREE
+                                 (PB_AUTO and the one-point rule stay per ordered pair).
+                                 0 (default, automatic): once per unordered pair, which is faster
+                                 at every size but needs up to 24 KB of partial sums per triangle
+                                 in FP64, 40 KB in FP32: where a memory budget has no room for
+                                 them FP64 handles, and FP32 ones below 3584 triangles, run per
+                                 ordered pair, as they do where source_chunks is given; 1: once
+                                 per unordered pair (PB_FP64 under such a budget: per ordered
+                                 pair); -1: per ordered pair.  A kappa outside the kernels' range
+                                 (kappa times the extent from about 2^30 on; in FP32 also kappa
+                                 times the shortest edge below about 2^-32 where kappa times the
+                                 extent is not below 2^-26) runs per ordered pair whatever is
+                                 asked.  Single and batched solves of a handle use the same
                                  choice, so their results stay bitwise equal; the two choices
-                                 agree to FP32 rounding. */
+                                 agree to rounding. */
 } pb_options;
 
 typedef struct {
@@ -205,11 +217,13 @@ typedef struct {
     int32_t n_vertices, n_triangles;
     int64_t n_near_pairs;     /* ordered triangle pairs sharing >= 1 vertex */
     int64_t near_nnz;         /* nonzeros of each near-field vertex block */
-    int32_t source_chunks;    /* far-field source split in use */
+    int32_t source_chunks;    /* source split of products per ordered pair (not used by
+                                 products that evaluate every unordered pair once) */
     int32_t assembled;        /* 1 if the far field is held as a dense matrix */
     size_t device_bytes;
-    int32_t far_symmetric;    /* 1 if matrix-free products evaluate every unordered
-                                 triangle pair once (FP32, see pb_options.far_symmetric) */
+    int32_t far_symmetric;    /* 1 if matrix-free FP32 products evaluate every unordered
+                                 triangle pair once (see pb_options.far_symmetric); 0 for FP64
+                                 handles, whichever they do */
 } pb_mesh_info;
 
 /* Fill *opt with the paper's settings: eps 4/80, kappa 0.125, direct

@@ -729,18 +729,6 @@ __global__ void k_sym_set(int *p, int v) { *p = v; }
 
 // ------------------------------------------------------------------ host
 
-// The symmetric split applies to FP32 matrix-free meshes of every size.
-// Automatic (mode 0) is yes: measured per product (direct / second kind, launches
-// included), 320 triangles 51 us (second kind) against 101 us per ordered pair, 1620
-// 89 / 111 against 133 / 166, 3380 216 against 328 (direct); mode 1 always, mode -1
-// never.
-bool sym_eligible(int T, double kappa, int mode)
-{
-    (void)T;
-    (void)kappa;   // kappa = 0 takes the unscreened variant
-    return mode >= 0;
-}
-
 // Ranges of rt tiles: at most 320 ranges (51000 items) in FP32, kSym64Ranges in
 // FP64, whose slots are twice as large.  In FP32 an item's four column groups are
 // dealt to nz parts while there are fewer than 400 (per product in one part / now:

@@ -385,7 +385,6 @@ void ss_group(const std::vector<int32_t> &tri, int n, const int32_t *t, const in
               int count[4]);
 int choose_chunks(int T);
 // symmetric far field (k_far_sym.hip)
-bool sym_eligible(int T, double kappa, int mode);
 struct SymSplit {
     int rt = 1, nr = 1, nz = 1;   // tiles per range, ranges, parts of an item
     size_t slots() const { return 2 * (size_t)nr * nz; }   // of 16 values per triangle

@@ -419,6 +419,20 @@ static void setup_and_wait(DevMesh &d)
 
 size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots);
 
+// Whether the options ask for every unordered pair once.  FP32 of every size: measured
+// per product (direct / second kind, launches included), 320 triangles 51 us (second
+// kind) against 101 us per ordered pair, 1620 89 / 111 against 133 / 166, 3380 216
+// against 328 (direct); FP64 where the far field is known to stay matrix-free
+// (k_far_sym64.hip).  far_symmetric -1 is no.  A source split given without
+// far_symmetric 1 is one of the per-ordered-pair kernel and keeps it, except in
+// FP32 from 3584 triangles on.
+static bool sym_wanted(const pb_options *o, int T)
+{
+    if (o->operator_mode == PB_TREECODE || o->regular_order == 1 || o->far_symmetric < 0) return false;
+    if (o->precision != PB_FP32 && !(o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE)) return false;
+    return o->far_symmetric == 1 || o->source_chunks == 0 || (o->precision == PB_FP32 && T >= 3584);
+}
+
 // the symmetric split is a choice that a handle without room for its slots leaves
 // out: in FP64, and on small FP32 meshes by the automatic choice
 static bool sym_optional(const pb_options *o, int T)
@@ -540,12 +554,9 @@ static DevMesh *create_mesh(const pb_mesh *mesh, const pb_options *opt, BlockCac
     size_t part_bytes = sizeof(double) * 16 * (size_t)d->S * T;
     if (d->tree) part_bytes = std::max(part_bytes, tree_slot_bytes(*d->tree));
     const bool fp32 = opt->precision == PB_FP32;
-    // every unordered pair once, FP32 or FP64 (FP64 only when the far field is
-    // known to stay matrix-free); under a memory budget the automatic choice
-    // takes it where the handle's expected footprint with its slots fits
-    bool sym = (fp32 || (opt->precision == PB_FP64 && opt->operator_mode == PB_MATRIX_FREE)) &&
-               opt->operator_mode != PB_TREECODE && d->far_rule == 0 && d->far_scaled &&
-               sym_eligible(T, opt->kappa, fp32 ? opt->far_symmetric : 0);
+    // every unordered pair once; under a memory budget an optional split is taken
+    // where the handle's expected footprint with its slots fits
+    bool sym = sym_wanted(opt, T) && d->far_rule == 0 && d->far_scaled;
     const bool room = !sym || !opt->memory_budget || estimate_device_bytes(V, T, opt, true) <= opt->memory_budget;
     if (!room && sym_optional(opt, T)) sym = false;
     if (sym) {
@@ -605,10 +616,7 @@ size_t estimate_device_bytes(int V, int T, const pb_options *o, bool slots)
     double b = t * (kGeo * 8 + kStat * 12 + kDyn * 12 + 6 * 8 + 12 * 8 + 3 * 4 * 2);
     double part = (double)S * t * 16 * 8;
     const bool fp32 = o->precision == PB_FP32;
-    if (o->operator_mode != PB_TREECODE && o->regular_order != 1 &&
-        ((fp32 && sym_eligible(T, o->kappa, o->far_symmetric)) ||
-         (o->precision == PB_FP64 && o->operator_mode == PB_MATRIX_FREE)) &&
-        (slots || !sym_optional(o, T)))
+    if (sym_wanted(o, T) && (slots || !sym_optional(o, T)))
         part = std::max(part, (double)sym_split(T, fp32, slots).slots() * t * 16 * (fp32 ? 4 : 8));
     b += buf(part);
     b += buf(16.0 * t * (36 * 8 + 3 * 4));

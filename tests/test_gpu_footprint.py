@@ -70,3 +70,30 @@ def test_products_without_room_for_the_split(freq, kw):
         served = s.wait(s.submit(m.xyz, m.tri, c.xyz, c.q, opt))
     assert served["status"] == pbm.PB_OK
     assert served["dG"] == alone["dG"] and np.array_equal(served["phi"], alone["phi"])
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(precision=pbm.PB_FP32)])
+@pytest.mark.parametrize("form", [pbm.PB_DIRECT_INT, pbm.PB_JUFFER])
+def test_split_asked_for(form, kw):
+    """far_symmetric -1 is per ordered pair in FP64 too, and a given source split is
+    one of that kernel: bitwise the same with far_symmetric -1 beside it, in its own
+    summation order, with its own (smaller) workspace."""
+    m = inputs.star_surface(4, 9, 5.0)[0]         # 1620 triangles
+    x = np.random.default_rng(37).standard_normal(2 * m.n_vertices)
+
+    def run(**more):
+        with pbm.MeshHandle(m.xyz, m.tri, pbm.pb_default_options(formulation=form, **kw, **more)) as h:
+            return pbm.pb_mesh_apply(h, x), h.info()["device_bytes"]
+
+    auto, b0 = run()
+    ordered, b1 = run(far_symmetric=-1)
+    three, b2 = run(source_chunks=3)
+    both, b3 = run(source_chunks=3, far_symmetric=-1)
+    always, b4 = run(source_chunks=3, far_symmetric=1)
+    assert b2 == b3 and b3 < b1
+    if not kw:
+        assert b1 < b0
+    assert np.array_equal(three, both) and np.array_equal(auto, always)
+    assert not np.array_equal(auto, ordered) and not np.array_equal(three, ordered)
+    for y in (ordered, three):
+        assert np.linalg.norm(y - auto) <= (2e-6 if kw else 1e-12) * np.linalg.norm(auto)
