@@ -130,49 +130,117 @@ __device__ inline int ss_order(int t, int s, const int *tv, const int *sv, int *
     return ns;
 }
 
+// An ordered pair (t, s): vertex ids in quadrature order and x - y = A + u1 e1 + u2 e2
+// - v1 f1 - v2 f2 at the point (u, v)
+struct SSPair {
+    int p, t, s, pt[3], ps[3];
+    double A[3], e1[3], e2[3], f1[3], f2[3], ns[3];
+};
+struct SSData {
+    const int32_t *pair_t, *pair_s, *tri;
+    const double *xyz, *geo;
+    double kl, kappa;
+    double *out;
+};
+
+__device__ __forceinline__ void ss_load(const SSData &D, int p, SSPair &q)
+{
+    q.p = p;
+    q.t = D.pair_t[p];
+    q.s = D.pair_s[p];
+    int tv[3], sv[3];
+    for (int k = 0; k < 3; ++k) { tv[k] = D.tri[3 * q.t + k]; sv[k] = D.tri[3 * q.s + k]; }
+    (void)ss_order(q.t, q.s, tv, sv, q.pt, q.ps);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double P0 = D.xyz[3 * tv[q.pt[0]] + c], P1 = D.xyz[3 * tv[q.pt[1]] + c], P2 = D.xyz[3 * tv[q.pt[2]] + c];
+        const double Q0 = D.xyz[3 * sv[q.ps[0]] + c], Q1 = D.xyz[3 * sv[q.ps[1]] + c], Q2 = D.xyz[3 * sv[q.ps[2]] + c];
+        q.A[c] = P0 - Q0;
+        q.e1[c] = P1 - P0; q.e2[c] = P2 - P1;
+        q.f1[c] = Q1 - Q0; q.f2[c] = Q2 - Q1;
+        q.ns[c] = D.geo[(size_t)q.s * kGeo + 18 + c];
+    }
+}
+
+// One point's record cur (13 values) into the sums of V (aL[0], aY[0]) and K.  RANGE
+// 0: every kappa log2(e) r of a near pair is at most kExpSmall, 8 instead of 15
+// instructions for its exponential; 2: some may pass 2^30, past which exp2neg_n's
+// exponent wraps, and are cut off at 2000 (2^-2000 = 0).  Identical triangles (CASE
+// 3) lie in one plane: d.n = 0, K = 0, only V is summed.
+template <int CASE, int RANGE, int NK>
+__device__ __forceinline__ void ss_add(const SSPair &q, const double (&cur)[13], double kl, double kappa, double (&aL)[NK][9],
+                                       double (&aY)[NK][9])
+{
+    double d[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        d[c] = fma(cur[0], q.e1[c], fma(cur[1], q.e2[c], fma(-cur[2], q.f1[c], fma(-cur[3], q.f2[c], q.A[c]))));
+    const double r2[1] = {d[0] * d[0] + d[1] * d[1] + d[2] * d[2]};
+    double ri[1], ek[1];
+    rsqrt3_n<1>(r2, ri);
+    ek[0] = kl * r2[0] * ri[0];
+    if (RANGE == 2) ek[0] = fmin(ek[0], 2000.0);
+    if (RANGE == 0) exp2small_n<1>(ek);
+    else exp2neg_n<1>(ek);
+    const double gL = ri[0], gY = ek[0] * ri[0];
+    double fL = 0.0, fY = 0.0;
+    if (CASE != 3) {
+        const double dn = d[0] * q.ns[0] + d[1] * q.ns[1] + d[2] * q.ns[2];
+        const double ri2 = gL * gL, ri3 = gL * ri2;
+        fL = dn * ri3;
+        fY = dn * (ek[0] * fma(kappa, ri2, ri3));
+    }
+#pragma unroll
+    for (int v = 0; v < 9; ++v) {
+        aL[0][v] = fma(cur[4 + v], gL, aL[0][v]);
+        aY[0][v] = fma(cur[4 + v], gY, aY[0][v]);
+        if (CASE != 3) {
+            aL[NK - 1][v] = fma(cur[4 + v], fL, aL[NK - 1][v]);
+            aY[NK - 1][v] = fma(cur[4 + v], fY, aY[NK - 1][v]);
+        }
+    }
+}
+
+// out[36 p + 4 (3 a + b) + op], op = V_L, K_L, V_Y, K_Y (the four values that one
+// vertex pair's row needs lie together); a, b local vertex ids of t and s in stored
+// order
+template <int CASE, int NK>
+__device__ __forceinline__ void ss_store(const SSData &D, const SSPair &q, const double (&aL)[NK][9], const double (&aY)[NK][9])
+{
+    const double scale = D.geo[(size_t)q.t * kGeo + 21] * D.geo[(size_t)q.s * kGeo + 21] / kPi;   // (2|t|)(2|s|) / (4 pi)
+    double *o = D.out + (size_t)q.p * 36;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            double4 v;
+            v.x = aL[0][3 * k + l] * scale;
+            v.y = CASE == 3 ? 0.0 : aL[NK - 1][3 * k + l] * scale;
+            v.z = aY[0][3 * k + l] * scale;
+            v.w = CASE == 3 ? 0.0 : aY[NK - 1][3 * k + l] * scale;
+            *(double4 *)(o + 4 * (3 * q.pt[k] + q.ps[l])) = v;
+        }
+}
+
 // One lane per ordered pair (t, s): the WAVES wavefronts of a block hold the same
 // 64 pairs of one case (CASE shared vertices) and take a part of the rule's points
 // each, which are then uniform across the wavefront: a point and its nine weights
 // come through scalar loads and feed the vector unit as scalar operands, and the
 // 36 sums need no reduction across lanes, only over the wavefronts (LDS).
-// out[36 p + 4 (3 a + b) + op], op = V_L, K_L, V_Y, K_Y (the four values that one
-// vertex pair's row needs lie together); a, b local vertex ids of t and s in stored
-// order; p = idx[item].  RANGE 0: every kappa log2(e) r of a near pair is at most
-// kExpSmall, 8 instead of 15 instructions for its exponential; 2: some may pass
-// 2^30, past which exp2neg_n's exponent wraps, and are cut off at 2000 (2^-2000 = 0).
-// Identical triangles lie in one plane: d.n = 0, K = 0, only V is summed.
 // Bound: the FP64 vector rate, 75 instructions per point and pair (68 in RANGE 0; 39
 // and 32 for identical triangles); with a group of lanes per pair (points, weights
 // and basis formed by every lane, 36 butterfly reductions) it was about 130.
 // Refresh of a 24500-triangle matrix-free handle (all of the near field): 1.67 ->
 // 0.81 ms (0.71 with k_near_slots as it is below).
 template <int CASE, int RANGE, int WAVES>
-__device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__restrict__ idx,
-                                         const int32_t *__restrict__ pair_t, const int32_t *__restrict__ pair_s,
-                                         const int32_t *__restrict__ tri, const double *__restrict__ xyz,
-                                         const double *__restrict__ geo, double kl, double kappa,
-                                         const double *__restrict__ pts, int npts, double *__restrict__ out,
-                                         double (*__restrict__ red)[18][64])
+__device__ __forceinline__ void ss_pairs(const SSData &D, int first, int count, const int32_t *__restrict__ idx,
+                                         const double *__restrict__ pts, int npts, double (*__restrict__ red)[18][64])
 {
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int item = first + lane;
     const bool active = item < count;   // lanes past the end repeat the last pair and do not store
-    const int p = idx[active ? item : count - 1];
-    const int t = pair_t[p], s = pair_s[p];
-    int tv[3], sv[3];
-    for (int k = 0; k < 3; ++k) { tv[k] = tri[3 * t + k]; sv[k] = tri[3 * s + k]; }
-    int pt[3], ps[3];
-    (void)ss_order(t, s, tv, sv, pt, ps);
-    double A[3], e1[3], e2[3], f1[3], f2[3], ns[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double P0 = xyz[3 * tv[pt[0]] + c], P1 = xyz[3 * tv[pt[1]] + c], P2 = xyz[3 * tv[pt[2]] + c];
-        const double Q0 = xyz[3 * sv[ps[0]] + c], Q1 = xyz[3 * sv[ps[1]] + c], Q2 = xyz[3 * sv[ps[2]] + c];
-        A[c] = P0 - Q0;
-        e1[c] = P1 - P0; e2[c] = P2 - P1;
-        f1[c] = Q1 - Q0; f2[c] = Q2 - Q1;
-        ns[c] = geo[(size_t)s * kGeo + 18 + c];
-    }
+    SSPair q;
+    ss_load(D, idx[active ? item : count - 1], q);
     constexpr int NK = CASE == 3 ? 1 : 2;   // V alone, or V and K, per kernel
     double aL[NK][9], aY[NK][9];
 #pragma unroll
@@ -192,34 +260,7 @@ __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__
 #pragma unroll
         for (int k = 0; k < 13; ++k) nx[k] = nxt[k];
         rec = nxt;
-        double d[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            d[c] = fma(cur[0], e1[c], fma(cur[1], e2[c], fma(-cur[2], f1[c], fma(-cur[3], f2[c], A[c]))));
-        const double r2[1] = {d[0] * d[0] + d[1] * d[1] + d[2] * d[2]};
-        double ri[1], ek[1];
-        rsqrt3_n<1>(r2, ri);
-        ek[0] = kl * r2[0] * ri[0];
-        if (RANGE == 2) ek[0] = fmin(ek[0], 2000.0);
-        if (RANGE == 0) exp2small_n<1>(ek);
-        else exp2neg_n<1>(ek);
-        const double gL = ri[0], gY = ek[0] * ri[0];
-        double fL = 0.0, fY = 0.0;
-        if (CASE != 3) {
-            const double dn = d[0] * ns[0] + d[1] * ns[1] + d[2] * ns[2];
-            const double ri2 = gL * gL, ri3 = gL * ri2;
-            fL = dn * ri3;
-            fY = dn * (ek[0] * fma(kappa, ri2, ri3));
-        }
-#pragma unroll
-        for (int v = 0; v < 9; ++v) {
-            aL[0][v] = fma(cur[4 + v], gL, aL[0][v]);
-            aY[0][v] = fma(cur[4 + v], gY, aY[0][v]);
-            if (CASE != 3) {
-                aL[NK - 1][v] = fma(cur[4 + v], fL, aL[NK - 1][v]);
-                aY[NK - 1][v] = fma(cur[4 + v], fY, aY[NK - 1][v]);
-            }
-        }
+        ss_add<CASE, RANGE, NK>(q, cur, D.kl, D.kappa, aL, aY);
 #pragma unroll
         for (int k = 0; k < 13; ++k) cur[k] = nx[k];
     }
@@ -243,21 +284,7 @@ __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__
     };
     join(aL);
     join(aY);
-    if (w == 0 && active) {
-        const double scale = geo[(size_t)t * kGeo + 21] * geo[(size_t)s * kGeo + 21] / kPi;   // (2|t|)(2|s|) / (4 pi)
-        double *o = out + (size_t)p * 36;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int l = 0; l < 3; ++l) {
-                double4 v;
-                v.x = aL[0][3 * k + l] * scale;
-                v.y = CASE == 3 ? 0.0 : aL[NK - 1][3 * k + l] * scale;
-                v.z = aY[0][3 * k + l] * scale;
-                v.w = CASE == 3 ? 0.0 : aY[NK - 1][3 * k + l] * scale;
-                *(double4 *)(o + 4 * (3 * pt[k] + ps[l])) = v;
-            }
-    }
+    if (w == 0 && active) ss_store<CASE, NK>(D, q, aL, aY);
 }
 
 // All pairs in one launch, blocks of 64 pairs of one case: identical, edge, then
@@ -265,28 +292,93 @@ __device__ __forceinline__ void ss_pairs(int first, int count, const int32_t *__
 struct SSRange { int first, count, blocks, npts; const double *pts; };
 template <int RANGE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_near_ss(SSRange r3, SSRange r2, SSRange r1, const int32_t *__restrict__ idx,
-                                                        const int32_t *__restrict__ pair_t,
-                                                        const int32_t *__restrict__ pair_s,
-                                                        const int32_t *__restrict__ tri, const double *__restrict__ xyz,
-                                                        const double *__restrict__ geo, double kl, double kappa,
-                                                        double *__restrict__ out)
+                                                        SSData D)
 {
     __shared__ double red[WAVES - 1][18][64];
     int b = blockIdx.x;
     if (b < r3.blocks) {
-        ss_pairs<3, RANGE, WAVES>(64 * b, r3.count, idx + r3.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r3.pts,
-                                  r3.npts, out, red);
+        ss_pairs<3, RANGE, WAVES>(D, 64 * b, r3.count, idx + r3.first, r3.pts, r3.npts, red);
         return;
     }
     b -= r3.blocks;
     if (b < r2.blocks) {
-        ss_pairs<2, RANGE, WAVES>(64 * b, r2.count, idx + r2.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r2.pts,
-                                  r2.npts, out, red);
+        ss_pairs<2, RANGE, WAVES>(D, 64 * b, r2.count, idx + r2.first, r2.pts, r2.npts, red);
         return;
     }
     b -= r2.blocks;
-    ss_pairs<1, RANGE, WAVES>(64 * b, r1.count, idx + r1.first, pair_t, pair_s, tri, xyz, geo, kl, kappa, r1.pts, r1.npts,
-                              out, red);
+    ss_pairs<1, RANGE, WAVES>(D, 64 * b, r1.count, idx + r1.first, r1.pts, r1.npts, red);
+}
+
+// One wavefront per ordered pair, a lane per point, and a reduction over the lanes:
+// where the pairs are too few to give every SIMD blocks of 64, a pair's chain of
+// points is cut into 64.  The block's wavefronts have pairs of one case and share
+// the records of 64 points in LDS (read by each from the caches they took 2.5 times
+// the time of the arithmetic).
+constexpr int kSSWaves = 4;    // sk, si cover 13 (of 16) values of 64 points with 256 threads
+constexpr int kSSRow = 68;     // rows 8 banks apart
+template <int CASE, int RANGE>
+__device__ __forceinline__ void ss_pair_wave(const SSData &D, int first, int count, const int32_t *__restrict__ idx,
+                                             const double *__restrict__ pts, int npts, double (*__restrict__ L)[kSSRow])
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int item = first + __builtin_amdgcn_readfirstlane(tid >> 6);
+    SSPair q;
+    ss_load(D, idx[min(item, count - 1)], q);   // past the end: the last pair, not stored
+    constexpr int NK = CASE == 3 ? 1 : 2;
+    double aL[NK][9], aY[NK][9];
+#pragma unroll
+    for (int o = 0; o < NK; ++o)
+#pragma unroll
+        for (int v = 0; v < 9; ++v) aL[o][v] = aY[o][v] = 0.0;
+    const int si = tid >> 2, sk = 4 * (tid & 3);   // staging: a quarter of point si's record
+    for (int i0 = 0; i0 < npts; i0 += 64) {
+        const double2 *rec = (const double2 *)(pts + (size_t)min(i0 + si, npts - 1) * kSSRec + sk);
+        const double2 u = rec[0], v = rec[1];
+        __syncthreads();   // the previous points are read
+        L[sk][si] = u.x;
+        if (sk < 12) {
+            L[sk + 1][si] = u.y;
+            L[sk + 2][si] = v.x;
+            L[sk + 3][si] = v.y;
+        }
+        __syncthreads();
+        if (i0 + lane < npts) {
+            double cur[13];
+#pragma unroll
+            for (int k = 0; k < 13; ++k) cur[k] = L[k][lane];
+            ss_add<CASE, RANGE, NK>(q, cur, D.kl, D.kappa, aL, aY);
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < NK; ++o)
+#pragma unroll
+        for (int v = 0; v < 9; ++v)
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                aL[o][v] += __shfl_xor(aL[o][v], off);
+                aY[o][v] += __shfl_xor(aY[o][v], off);
+            }
+    if (lane == 0 && item < count) ss_store<CASE, NK>(D, q, aL, aY);
+}
+
+// blocks of kSSWaves pairs of one case
+template <int RANGE>
+__global__ __launch_bounds__(64 * kSSWaves) void k_near_ss_wave(SSRange r3, SSRange r2, SSRange r1,
+                                                                const int32_t *__restrict__ idx, SSData D)
+{
+    __shared__ double L[13][kSSRow];
+    int b = blockIdx.x;
+    if (b < r3.blocks) {
+        ss_pair_wave<3, RANGE>(D, kSSWaves * b, r3.count, idx + r3.first, r3.pts, r3.npts, L);
+        return;
+    }
+    b -= r3.blocks;
+    if (b < r2.blocks) {
+        ss_pair_wave<2, RANGE>(D, kSSWaves * b, r2.count, idx + r2.first, r2.pts, r2.npts, L);
+        return;
+    }
+    b -= r2.blocks;
+    ss_pair_wave<1, RANGE>(D, kSSWaves * b, r1.count, idx + r1.first, r1.pts, r1.npts, L);
 }
 
 // Pair indices 0..n-1 grouped by the number of shared vertices: identical,
@@ -325,20 +417,32 @@ static void launch_ss(DevMesh &d, const int count[4], const int32_t *idx, const 
     // a near pair's points are at most two longest edges apart
     const double reach = 2.0 * d.max_edge * kl;
     const int range = reach <= kExpSmall ? 0 : reach < 1073741824.0 ? 1 : 2;
-#define SS_RUN(E, W)                                                                                                \
-    hipLaunchKernelGGL((k_near_ss<E, W>), dim3(blocks), dim3(64 * W), 0, d.stream, r[3], r[2], r[1], idx, pt, ps, \
-                       d.tri, d.xyz, d.geo, kl, d.prm.kappa, out)
-    // eight wavefronts share a block's pairs while four would leave compute units idle
-    if (blocks < 256) {
-        if (range == 0) SS_RUN(0, 8);
-        else if (range == 1) SS_RUN(1, 8);
-        else SS_RUN(2, 8);
+    const SSData D{pt, ps, d.tri, d.xyz, d.geo, kl, d.prm.kappa, out};
+#define SS_PICK(KERNEL0, KERNEL1, KERNEL2, grid, threads)                                                                \
+    if (range == 0) hipLaunchKernelGGL((KERNEL0), dim3(grid), dim3(threads), 0, d.stream, r[3], r[2], r[1], idx, D);     \
+    else if (range == 1) hipLaunchKernelGGL((KERNEL1), dim3(grid), dim3(threads), 0, d.stream, r[3], r[2], r[1], idx, D); \
+    else hipLaunchKernelGGL((KERNEL2), dim3(grid), dim3(threads), 0, d.stream, r[3], r[2], r[1], idx, D)
+    // A wavefront per pair costs 4.5 ns a pair for its reduction and about 10 ps a pair
+    // and n^4 point; blocks of 64 pairs a chain of 0.29 us per n^4 until they fill the
+    // device.  The lines meet at 28000 n^4 / (437 + n^4) pairs; below 20000 a wavefront
+    // per pair was the faster one everywhere.  Refresh in us, wavefront / block, at
+    // 980, 4100, 9300 and 16580 pairs (80 .. 1280 triangles): n = 2 46 / 47, 68 / 53;
+    // 4 56 / 100, 83 / 108, 121 / 111; 6 101 / 326, 144 / 336, 245 / 350, 398 / 390;
+    // 8 272 / 1221, 302 / 1265, 565 / 1264, 945 / 1233 (with a group of lanes per pair
+    // n = 8 took 708, 715, 995, 1289).  Eight wavefronts share a block's pairs while
+    // four leave compute units idle: n = 6, 25940 pairs in 406 blocks 435 / 655 us,
+    // 50900 in 796 779 / 756; n = 3 82 / 79 in 406.
+    const double n4 = (double)order * order * order * order;
+    if (first < 20000.0 * n4 / (437.0 + n4)) {
+        blocks = 0;
+        for (int c = 3; c >= 1; --c) blocks += r[c].blocks = (count[c] + kSSWaves - 1) / kSSWaves;
+        SS_PICK(k_near_ss_wave<0>, k_near_ss_wave<1>, k_near_ss_wave<2>, blocks, 64 * kSSWaves);
+    } else if (blocks < (order >= 4 ? 512 : 256)) {
+        SS_PICK((k_near_ss<0, 8>), (k_near_ss<1, 8>), (k_near_ss<2, 8>), blocks, 512);
     } else {
-        if (range == 0) SS_RUN(0, 4);
-        else if (range == 1) SS_RUN(1, 4);
-        else SS_RUN(2, 4);
+        SS_PICK((k_near_ss<0, 4>), (k_near_ss<1, 4>), (k_near_ss<2, 4>), blocks, 256);
     }
-#undef SS_RUN
+#undef SS_PICK
     HIPCHECK(hipGetLastError());
 }
 
