@@ -210,11 +210,15 @@ __global__ void k_gnormalize(int n, double *__restrict__ Vb, const GState *__res
 // took 21 us and as many gaps, this one takes 8.7 us.  A wavefront takes a dot product by itself:
 // lane l stands for the threads l + 64 k, k < 16, of dot_block_sum, whose first
 // four levels (512 .. 64) are then sums inside the lane and the others shuffles, so
-// that every result is bitwise the one of the separate kernels.  Above the limit
-// one block's reads of the basis outweigh the launches: FP64 direct solves (19
-// iterations) with one block / with seven launches, 324 unknowns 1498 / 1623 us,
-// 724 2016 / 2110, 1284 2831 / 2825, 1624 3519 / 3441, 2004 4660 / 4384.
-constexpr int kSmallKrylov = 1024;
+// that every result is bitwise the one of the separate kernels.  One block reads the
+// basis, j n values, four times at one compute unit's rate, and each dot product's n
+// values by one wavefront.  An iteration's time in us, one block / seven launches (FP32,
+// products included): 324 unknowns j = 8 57.4 / 61.3, 80 73.1 / 76.5, 160 96.1 / 101.2,
+// 224 114.3 / 113.4; 504 40 66.2 / 67.9, 56 72.1 / 69.5, 112 90.9 / 87.2; 724 8 70.3 /
+// 73.3, 24 73.0 / 73.2, 40 80.6 / 76.0, 320 226 / 161.  The lines meet near j n^2 = 2^24;
+// 984 unknowns are no faster from the start (8: 84.8 / 83.9).
+constexpr int kSmallKrylov = 768;      // unknowns
+bool kr_one_block(int n, int j) { return n <= kSmallKrylov && (long long)j * n * n <= 1 << 24; }
 struct SmallLds {
     double w[kSmallKrylov], h1[kSmallKrylov], h2[kSmallKrylov], inv;
 };
@@ -282,9 +286,9 @@ __global__ __launch_bounds__(kDotThreads) void k_gsmall(int n, double *__restric
 }
 
 void kr_graph_iteration_tail(hipStream_t s, int n, int m, double *Vb, GState *st, double *H, double *cs, double *sn,
-                             double *g, double *h1, double *h2)
+                             double *g, double *h1, double *h2, bool one_block)
 {
-    if (n <= kSmallKrylov) {
+    if (one_block) {
         hipLaunchKernelGGL(k_gsmall, dim3(1), dim3(kDotThreads), 0, s, n, Vb, st, H, cs, sn, g);
         return;
     }
@@ -385,10 +389,10 @@ __global__ __launch_bounds__(kDotThreads) void k_bgsmall(const KrylovReq *__rest
     small_tail(q.n, q.Vb, q.st, q.H, q.cs, q.sn, q.g, L);
 }
 
-// nmax: the largest n of the solves
-void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot, int nmax)
+void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot,
+                             bool one_block)
 {
-    if (nmax <= kSmallKrylov) {
+    if (one_block) {
         hipLaunchKernelGGL(k_bgsmall, dim3(R), dim3(kDotThreads), 0, s, rq);
         HIPCHECK(hipGetLastError());
         return;

@@ -480,7 +480,7 @@ int kr_batch_blocks(int n);
 // boff: prefix of kr_batch_blocks(n_r) over the R solves (device); ndot: an
 // upper bound of the dot-product items (sum of the capacities + 1)
 void kr_batch_iteration_tail(hipStream_t s, int R, const KrylovReq *rq, const int *boff, int nblocks, int ndot,
-                             int nmax);
+                             bool one_block);
 // batched source weights, far-field finish (regular and symmetric splits) and
 // gather of R solves; boff_* prefixes of the blocks each solve takes
 int tail_blocks_source(const TailReq &q);
@@ -489,7 +489,10 @@ int tail_blocks_gather(const TailReq &q);
 void launch_batch_source_prep(hipStream_t s, int R, const TailReq *rq, const int *boff, int nblocks);
 void launch_batch_finish(hipStream_t s, bool fp32, int R, const TailReq *rq, const int *boff, int nblocks);
 void launch_batch_gather(hipStream_t s, int R, const TailReq *rq, const int *boff, int nblocks);
+// whether one block takes the Krylov steps of a solve of n unknowns (one_block below:
+// the largest of a batch) up to iteration j; bitwise the same either way
+bool kr_one_block(int n, int j);
 void kr_graph_iteration_tail(hipStream_t s, int n, int m, double *Vb, GState *st, double *H, double *cs, double *sn,
-                             double *g, double *h1, double *h2);
+                             double *g, double *h1, double *h2, bool one_block);
 
 }  // namespace pbm

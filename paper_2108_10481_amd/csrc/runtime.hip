@@ -860,12 +860,16 @@ struct GraphGmres {
     const double *basis = nullptr;
     GState *st = nullptr;
     double *H = nullptr, *cs = nullptr, *sn = nullptr, *g = nullptr, *h1 = nullptr, *h2 = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    // the iteration with the Krylov steps in separate kernels, and in one block
+    // (kr_one_block), each captured at its first use
+    hipGraph_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t exec[2] = {nullptr, nullptr};
     ~GraphGmres()
     {
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
+        for (int k = 0; k < 2; ++k) {
+            if (exec[k]) (void)hipGraphExecDestroy(exec[k]);
+            if (graph[k]) (void)hipGraphDestroy(graph[k]);
+        }
     }
 };
 
@@ -892,24 +896,26 @@ static GraphGmres *graph_state(DevMesh &d, int m)
 
 // the handle's Arnoldi step after its far field (as apply_operator without
 // far_product) and the device Givens step, for capture under d.ctl
-static void iteration_tail(DevMesh &d, GraphGmres &G, int use_far)
+static void iteration_tail(DevMesh &d, GraphGmres &G, int use_far, bool one_block)
 {
     double *Vb = d.kry.basis;
     apply_after_far(d, Vb, Vb + G.n, PB_APPLY_PRECOND, use_far);
-    kr_graph_iteration_tail(d.stream, G.n, G.m, Vb, G.st, G.H, G.cs, G.sn, G.g, G.h1, G.h2);
+    kr_graph_iteration_tail(d.stream, G.n, G.m, Vb, G.st, G.H, G.cs, G.sn, G.g, G.h1, G.h2, one_block);
 }
 
-static void capture_into(DevMesh &d, GraphGmres &G)
+static void capture_into(DevMesh &d, GraphGmres &G, bool one_block)
 {
     const int n = G.n;
-    // one eager product first: settles autotuned launch shapes outside the capture
-    apply_operator(d, d.kry.basis, d.ztmp, PB_APPLY_PRECOND, nullptr);
-    HIPCHECK(hipStreamSynchronize(d.stream));
+    if (!G.exec[0] && !G.exec[1]) {
+        // one eager product first: settles autotuned launch shapes outside the capture
+        apply_operator(d, d.kry.basis, d.ztmp, PB_APPLY_PRECOND, nullptr);
+        HIPCHECK(hipStreamSynchronize(d.stream));
+    }
     double *Vb = d.kry.basis;
     d.ctl = DevCtl{&G.st->j, &G.st->done, (size_t)n};
     HIPCHECK(hipStreamBeginCapture(d.stream, hipStreamCaptureModeThreadLocal));
     try {
-        iteration_tail(d, G, far_product(d, Vb, 0));
+        iteration_tail(d, G, far_product(d, Vb, 0), one_block);
         HIPCHECK(hipGetLastError());
     } catch (...) {
         hipGraph_t dead = nullptr;
@@ -919,8 +925,11 @@ static void capture_into(DevMesh &d, GraphGmres &G)
         throw;
     }
     d.ctl = DevCtl();
-    HIPCHECK(hipStreamEndCapture(d.stream, &G.graph));
-    HIPCHECK(hipGraphInstantiate(&G.exec, G.graph, nullptr, nullptr, 0));
+    hipGraph_t &graph = G.graph[one_block];
+    if (graph) (void)hipGraphDestroy(graph);   // left by an instantiation that failed
+    graph = nullptr;
+    HIPCHECK(hipStreamEndCapture(d.stream, &graph));
+    HIPCHECK(hipGraphInstantiate(&G.exec[one_block], graph, nullptr, nullptr, 0));
 }
 
 void destroy_graphs(DevMesh &d)
@@ -975,7 +984,6 @@ static int gmres_graph(DevMesh &d, const double *pb, double *x, double tol, int 
     }
     kr_scale_copy(s, n, pb, 1.0 / beta, d.kry.basis);
     if (!G) G = graph_state(d, m);
-    if (!G->exec) capture_into(d, *G);
     GState h0{};
     h0.j = 0;
     h0.done = 0;
@@ -988,7 +996,9 @@ static int gmres_graph(DevMesh &d, const double *pb, double *x, double tol, int 
     HIPCHECK(hipMemcpyAsync(G->g, g0.data(), sizeof(double) * (m + 1), hipMemcpyHostToDevice, s));
     GState hs{};
     for (;;) {
-        for (int r = 0; r < kReplay; ++r) HIPCHECK(hipGraphLaunch(G->exec, s));
+        const bool one = kr_one_block(n, hs.j + kReplay);
+        if (!G->exec[one]) capture_into(d, *G, one);
+        for (int r = 0; r < kReplay; ++r) HIPCHECK(hipGraphLaunch(G->exec[one], s));
         HIPCHECK(hipMemcpyAsync(&hs, G->st, sizeof(GState), hipMemcpyDeviceToHost, s));
         HIPCHECK(hipStreamSynchronize(s));
         if (hs.done || hs.j >= m) break;
@@ -1154,7 +1164,7 @@ static void key_append(std::vector<char> &k, const T &v)
 // cache or captured now; caller holds g_lockstep_mu.
 static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std::vector<int> &live,
                                      const std::vector<GraphGmres *> &G, const std::vector<int> &n,
-                                     const std::vector<int> &m, bool fp32, hipStream_t s)
+                                     const std::vector<int> &m, bool fp32, bool one_block, hipStream_t s)
 {
     const int L = (int)live.size();
     std::vector<TailReq> tq(L);
@@ -1163,6 +1173,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
     int ndot = 0;
     std::vector<char> key;
     key_append(key, fp32);
+    key_append(key, one_block);
     for (int k = 0; k < L; ++k) {
         const int r = live[k];
         DevMesh &d = *ds[r];
@@ -1258,8 +1269,6 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
     const KrylovReq *dk = (const KrylovReq *)(base + bt);
     const int *dsrc = (const int *)(base + bt + bk), *dfin = dsrc + (L + 1), *dgat = dfin + (L + 1),
               *dkry = dgat + (L + 1);
-    int nmax = 0;
-    for (int r : live) nmax = std::max(nmax, n[r]);
     for (int r : live) ds[r]->ctl = DevCtl{&G[r]->st->j, &G[r]->st->done, (size_t)n[r]};
     HIPCHECK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     try {
@@ -1269,7 +1278,7 @@ static LockstepGraph &lockstep_graph(const std::vector<DevMesh *> &ds, const std
         launch_batch_gather(s, L, dt, dgat, bgat[L]);
         for (int r : live)   // apply_after_far's mass-preconditioner step, per request
             if (mass_mode(*ds[r])) mass_precond(*ds[r], 1, ds[r]->mtmp, ds[r]->kry.basis + n[r], ds[r]->ctl);
-        kr_batch_iteration_tail(s, L, dk, dkry, bkry[L], ndot, nmax);
+        kr_batch_iteration_tail(s, L, dk, dkry, bkry[L], ndot, one_block);
         HIPCHECK(hipGetLastError());
     } catch (...) {
         hipGraph_t dead = nullptr;
@@ -1344,7 +1353,12 @@ static void gmres_batch_graph(const std::vector<DevMesh *> &ds, hipStream_t s, b
     {
         std::lock_guard<std::mutex> lk(g_lockstep_mu);
         while (!running.empty()) {
-            LockstepGraph &lg = lockstep_graph(ds, running, G, n, m, fp32, s);
+            int nmax = 0, j = 0;   // every running solve is at the same iteration
+            for (int r : running) {
+                nmax = std::max(nmax, n[r]);
+                j = std::max(j, hs[r].j);
+            }
+            LockstepGraph &lg = lockstep_graph(ds, running, G, n, m, fp32, kr_one_block(nmax, j + kReplay), s);
             for (int k = 0; k < kReplay; ++k) HIPCHECK(hipGraphLaunch(lg.exec, s));
             for (int r : running)
                 HIPCHECK(hipMemcpyAsync(&hs[r], G[r]->st, sizeof(GState), hipMemcpyDeviceToHost, s));

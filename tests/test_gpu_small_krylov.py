@@ -43,3 +43,29 @@ def test_small_iterations_match_eager(sizes, precision):
         _same(e, s)
         _same(s, a)
         _same(s, b)
+
+
+@pytest.mark.parametrize("precision", [pbm.PB_FP64, pbm.PB_FP32])
+@pytest.mark.parametrize("sizes", [(70,), (600,), (724,), (768,), (770,), (724, 70), (768, 770)])
+def test_long_solves_change_kernels(sizes, precision):
+    """Solves that run on past the iterations one block serves: the separate kernels
+    take over between two checks, bitwise as eager launches throughout, also in a
+    second solve and in batches."""
+    meshes = [inputs.bipyramid(n // 2 - 2, 4.0, 4.0) for n in sizes]
+    sets = [inputs.charges_ball(80 + k, 5, 1.0) for k in range(len(sizes))]
+    sets = [(c.xyz, c.q) for c in sets]
+
+    def handles(**kw):
+        opt = pbm.pb_default_options(precision=precision, tol=1e-300, max_iter=57, preconditioner=pbm.PB_PREC_NONE, **kw)
+        return [pbm.MeshHandle(m.xyz, m.tri, opt) for m in meshes]
+
+    eager = [pbm.pb_mesh_solve(h, *c) for h, c in zip(handles(use_graph=0), sets)]
+    hs = handles()
+    single = [pbm.pb_mesh_solve(h, *c) for h, c in zip(hs, sets)]
+    again = [pbm.pb_mesh_solve(h, *c) for h, c in zip(hs, sets)]
+    batch = pbm.pb_solve_batch(hs, sets)
+    for e, s, a, b in zip(eager, single, again, batch):
+        assert e["iterations"] == 57
+        _same(e, s)
+        _same(s, a)
+        _same(s, b)
