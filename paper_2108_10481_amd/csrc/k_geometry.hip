@@ -316,14 +316,26 @@ int reaction_chunks(int T, int npts)
     return std::max(1, std::min({4096 / waves, T / 8, most}));
 }
 
-// part: npts x reaction_chunks partial sums; out: npts potentials
+// k_reaction_finish's sum of the C partial sums of one point, in its order (lane by
+// lane, then the butterfly's pairs), on the host
+double reaction_host_sum(int C, const double *part)
+{
+    double s[64] = {};
+    for (int c = 0; c < C; ++c) s[c % 64] += part[c];
+    for (int off = 32; off > 0; off >>= 1)
+        for (int l = 0; l < off; ++l) s[l] += s[l + off];
+    return s[0] * kInv4Pi;
+}
+
+// part: npts x reaction_chunks partial sums; out: npts potentials (null: the partial
+// sums are left to the caller)
 void launch_reaction(DevMesh &d, int npts, const double *pts, double *part, double *out)
 {
     const int T = d.hm.T, C = reaction_chunks(T, npts), chunk = (T + C - 1) / C;
     const long long waves = (long long)((npts + 63) / 64) * C;
     hipLaunchKernelGGL(k_reaction, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, d.stream, T, npts, C, chunk, pts,
                        d.stat64, d.dyn64, part);
-    hipLaunchKernelGGL(k_reaction_finish, dim3((npts + 3) / 4), dim3(256), 0, d.stream, npts, C, part, out);
+    if (out) hipLaunchKernelGGL(k_reaction_finish, dim3((npts + 3) / 4), dim3(256), 0, d.stream, npts, C, part, out);
     HIPCHECK(hipGetLastError());
 }
 

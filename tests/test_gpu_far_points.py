@@ -36,3 +36,21 @@ def test_distant_points(far):
     assert np.abs(v[[1, 4]]).max() < 1e-140
     assert np.abs(v[near] - ref).max() <= 1e-14 * np.abs(ref).max()
     assert np.abs(b - bref).max() <= 1e-14 * np.abs(bref).max()
+
+
+@pytest.mark.parametrize("freq", [1, 2, 4, 9])
+@pytest.mark.parametrize("npts", [1, 2, 7, 50, 63, 65])
+def test_small_potentials_sum_alike(freq, npts):
+    """Few partial sums are added on the host, more on the device, and always on the
+    device without allocation: bitwise the same."""
+    m = inputs.icosphere(freq, 2.0)
+    tr = np.random.default_rng(67).standard_normal(2 * m.n_vertices)
+    pts = inputs.charges_ball(68, npts, 1.0).xyz
+    with pbm.MeshHandle(m.xyz, m.tri, pbm.pb_default_options()) as h:
+        v = pbm.pb_mesh_reaction_potential(h, tr[:m.n_vertices], tr[m.n_vertices:], pts)
+        t, p = torch.from_numpy(tr).cuda(), torch.from_numpy(pts).cuda()
+        out = torch.zeros(npts, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        pbm.pb_mesh_reaction_potential_noalloc(h, t.data_ptr(), npts, p.data_ptr(), out.data_ptr())
+        pbm.pb_mesh_synchronize(h)
+    assert np.array_equal(out.cpu().numpy(), v)
