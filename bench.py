@@ -309,7 +309,8 @@ def main():
         "dtype": dtype, "data": "synthetic",
         "config": {"workload": workload, "precision": a.precision,
                    "operator_mode": "assembled" if assembled else "matrix-free",
-                   "source_chunks": info[forms[0]]["source_chunks"],
+                   # the per-ordered-pair kernel's; products that evaluate every unordered pair once have none
+                   "source_chunks": (None if info[forms[0]]["far_symmetric"] else info[forms[0]]["source_chunks"]),
                    "far_symmetric": a.far_symmetric,
                    "preconditioner": {"direct": "block-diagonal",
                                       "juffer": "scaled mass" if a.preconditioner == "scaled-mass"

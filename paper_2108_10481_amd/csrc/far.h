@@ -359,9 +359,12 @@ inline int sym_coef(const DevMesh &d, SymCoef<R> &sc)
         else CALL((KERNEL<4, false>))                                                          \
     }
 
-// Tiles I, J are apart when their centres are at least kSymApart times the sum
-// of their radii apart: then r >= (kSymApart - 1)(rad_I + rad_J) and the terms of
-// r^2 that cancel, 2 |X| |Y|, are a small multiple of r^2
+// Tiles I, J are apart when their centres are at least kSymApart times the sum of
+// their radii apart.  With coordinates relative to J's centre r^2 = |X|^2 - 2 X.Y +
+// |Y|^2 then loses at most (|X| + |Y|)^2 / r^2 roundings of 2^-24: at the limit, where
+// the two come closest, |X| = 1.5, |Y| = 1, r = 0.5 radii of equal tiles (25), 1.25, 1,
+// 0.25 radii of J for a much smaller I (81).  The subtracted form of global
+// coordinates loses the mesh's extent over r.
 constexpr double kSymApart = 1.25;
 
 void launch_sym_list(DevMesh &d, const int4 *items, int nitems, const int2 *entries, const double *tiles, float *slots);

@@ -18,10 +18,10 @@
 // normal components d.n_s = X.n_s - O_s and d.n_t = O_t - Y.n_t (O: a
 // triangle's plane offset; the points of a flat triangle lie in its plane).
 // The points enter relative to the centre of tile J, subtracted in FP64 and then
-// rounded: |Y| is at most the tile's radius, the terms that cancel against |X|^2
-// are small, and r^2 keeps the accuracy of the subtracted form as long as the
-// tiles are apart (kSymApart).  Tile pairs that are not apart take the
-// subtracted form (NEAR), and only they can hold pairs that share a vertex.
+// rounded, so their own rounding is that of a tile's size and not of the mesh's;
+// the terms that cancel cost at most 81 roundings of r^2 (kSymApart, far.h).  Tile
+// pairs that are not apart take the subtracted form (NEAR), and only they can hold
+// pairs that share a vertex.
 //
 // Coordinates (points and the plane offsets) are used scaled by s = kappa
 // log2(e), with the coefficients of sym_coef: then exp(-kappa r) = exp2(-r')
@@ -31,13 +31,15 @@
 //
 // Bound: VALU issue.  A point pair of the direct form costs 6 instructions for
 // the kernel values, two transcendentals and 8 fused multiply-adds into the sums
-// (16.0 executed with everything outside, by counters), the issue slots are 91%
+// (16.3 executed with everything outside, by counters), the issue slots are 91%
 // taken.  Measured per product, before (a lane per target triangle, the source
 // sums rotating through the wavefront, r^2 subtracted on the VALU) and now:
 // 81920 triangles direct 80.4 -> 69.5 ms, Juffer 108 -> 86 ms; 20480 triangles
 // Juffer 6.97 -> 5.98 ms; against the FP64 operator at 20480 triangles the error
 // went from 1.2e-8 / 5.5e-8 (direct / Juffer) to 0.6e-8 / 0.7e-8, the input
-// rounding of global coordinates being gone.  Three wavefronts per SIMD (168
+// rounding of global coordinates being gone; on spheres of 20480 triangles graded
+// towards a pole, edges 1 : 24, 1 : 240, 1 : 1900, the largest error of an entry went
+// from 2.5e-6, 8.2e-6, 4.0e-5 to 3.4e-7, 7.0e-7, 5.4e-6 (direct).  Three wavefronts per SIMD (168
 // registers, spilling) gained 3% on the direct form at 81920 triangles, lost 2%
 // at 20480 and 10% on Juffer.
 //
@@ -45,7 +47,8 @@
 // per target-side item (slot b, the source range) and one per source-side
 // item (slot nr + a, the target range): every slot is written by exactly one
 // item, so no atomics and a fixed summation order.  k_far_sym_finish adds a
-// triangle's nr + 1 slots in FP64 and projects them as k_far_finish does.
+// triangle's slots in FP64 (nr + 1 for each part of the items) and projects them as
+// k_far_finish does.
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -711,7 +714,7 @@ __global__ __launch_bounds__(64 * kSymWaves, 2) void k_sym_list(int T, SymCoef<f
                       [&](int tr) { return slots + ((size_t)it.w * kSymTile + tr - kSymTile * it.x) * 16; }, lds);
 }
 
-// kFinishLanes lanes per triangle over its nr + 1 slots, then the test
+// kFinishLanes lanes per triangle over its (nr + 1) nz slots, then the test
 // projection of k_far_finish (sym_finish_group, far.h)
 template <typename R>
 __global__ __launch_bounds__(256) void k_far_sym_finish(int T, int rt, int nr, int nz, int family, int swap,
