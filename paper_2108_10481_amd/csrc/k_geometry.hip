@@ -271,6 +271,36 @@ __device__ inline double block_sum(double v, double *sh)
     return r;
 }
 
+// The potential at few points of a small mesh: a block per point, its lanes over the
+// quadrature points, in one launch.  Bound: latency; the chunks of k_reaction are
+// chains of eight triangles behind scalar loads, and their sums a launch of their
+// own.  Potentials at 1 / 200 points, copies included, in us, by k_reaction and so:
+// 80 triangles 44 / 45 and 39 / 40, 320 46 / 46.5 and 42 / 44, 500 47 / 47.5 and 43.5 /
+// 45.5; a block per point at 720 45.7 / 46.6 against 46.5 / 47, at 1620 54 / 55 against
+// 49 / 50.
+constexpr int kPointTriangles = 768, kPointPoints = 512;
+__global__ __launch_bounds__(kRedBlock) void k_reaction_point(int T, const double *__restrict__ pts,
+                                                              const double *__restrict__ stat,
+                                                              const double *__restrict__ dyn, double *__restrict__ out)
+{
+    __shared__ double sh[kRedBlock];
+    const int k = blockIdx.x;
+    const double x = point_cut(pts[3 * k]), y = point_cut(pts[3 * k + 1]), z = point_cut(pts[3 * k + 2]);
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < 6 * T; i += kRedBlock) {
+        const int s = i / 6, q = i - 6 * s;
+        const double *st = stat + (size_t)s * kStat, *dy = dyn + (size_t)s * kDyn;
+        const double dx = x - st[3 * q], dyy = y - st[3 * q + 1], dz = z - st[3 * q + 2];
+        const double r2[1] = {dx * dx + dyy * dyy + dz * dz};
+        double ri[1];
+        rsqrt3_n<1>(r2, ri);
+        const double dn = dx * st[18] + dyy * st[19] + dz * st[20];
+        acc = fma(ri[0], dy[6 + q], fma(-dn * (ri[0] * (ri[0] * ri[0])), dy[q], acc));
+    }
+    const double tot = block_sum(acc, sh);
+    if (threadIdx.x == 0) out[k] = tot * kInv4Pi;
+}
+
 // Solid angle subtended by each triangle at point k (Van Oosterom-Strackee);
 // the sum is 4 pi for points inside a closed outward-oriented surface.
 __global__ __launch_bounds__(kRedBlock) void k_solid_angle(int T, int chunk, const double *__restrict__ pts,
@@ -311,31 +341,25 @@ static int red_chunks(int T) { return T < 4096 ? 1 : (T + 4095) / 4096; }
 // entry points sum alike)
 int reaction_chunks(int T, int npts)
 {
+    if (T <= kPointTriangles && npts <= kPointPoints) return 1;   // k_reaction_point
     const int waves = (npts + 63) / 64;
     const int most = std::max(1, (int)(kNoAllocScratchDoubles / (size_t)npts));
     return std::max(1, std::min({4096 / waves, T / 8, most}));
 }
 
-// k_reaction_finish's sum of the C partial sums of one point, in its order (lane by
-// lane, then the butterfly's pairs), on the host
-double reaction_host_sum(int C, const double *part)
-{
-    double s[64] = {};
-    for (int c = 0; c < C; ++c) s[c % 64] += part[c];
-    for (int off = 32; off > 0; off >>= 1)
-        for (int l = 0; l < off; ++l) s[l] += s[l + off];
-    return s[0] * kInv4Pi;
-}
-
-// part: npts x reaction_chunks partial sums; out: npts potentials (null: the partial
-// sums are left to the caller)
+// part: npts x reaction_chunks partial sums; out: npts potentials
 void launch_reaction(DevMesh &d, int npts, const double *pts, double *part, double *out)
 {
     const int T = d.hm.T, C = reaction_chunks(T, npts), chunk = (T + C - 1) / C;
+    if (T <= kPointTriangles && npts <= kPointPoints) {
+        hipLaunchKernelGGL(k_reaction_point, dim3(npts), dim3(kRedBlock), 0, d.stream, T, pts, d.stat64, d.dyn64, out);
+        HIPCHECK(hipGetLastError());
+        return;
+    }
     const long long waves = (long long)((npts + 63) / 64) * C;
     hipLaunchKernelGGL(k_reaction, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, d.stream, T, npts, C, chunk, pts,
                        d.stat64, d.dyn64, part);
-    if (out) hipLaunchKernelGGL(k_reaction_finish, dim3((npts + 3) / 4), dim3(256), 0, d.stream, npts, C, part, out);
+    hipLaunchKernelGGL(k_reaction_finish, dim3((npts + 3) / 4), dim3(256), 0, d.stream, npts, C, part, out);
     HIPCHECK(hipGetLastError());
 }
 

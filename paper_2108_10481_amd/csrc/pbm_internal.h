@@ -378,7 +378,6 @@ void launch_rhs(DevMesh &d, int nq, const double *qbuf, double *b);
 void formulation_rhs(DevMesh &d, int nq, const double *qbuf, double *b);
 int reaction_chunks(int T, int npts);
 void launch_reaction(DevMesh &d, int npts, const double *pts, double *part, double *out);
-double reaction_host_sum(int C, const double *part);
 void launch_inside_test(DevMesh &d, int nq, const double *qbuf, double *out);
 void launch_pair_blocks_subset(DevMesh &d, int n, const int32_t *t_sorted, const int32_t *s_sorted,
                                const int32_t *idx, const int count[4], double *out);

@@ -1510,17 +1510,6 @@ static void reaction_potential(DevMesh &d, const double *u, int npts, const doub
     launch_source_prep(d, u, false);
     double *part = reduction_buffer(d, (size_t)npts * (C + 1));
     double *out = part + (size_t)npts * C;
-    // few partial sums are added here instead of by one more launch (one point, 80
-    // triangles, copies included: 46 us with it, 44 without; 640 sums: 46 and 47)
-    constexpr size_t kHostSums = 512;
-    if ((size_t)npts * C <= kHostSums) {
-        double h[kHostSums];
-        launch_reaction(d, npts, pts_dev, part, nullptr);
-        HIPCHECK(hipMemcpyAsync(h, part, sizeof(double) * npts * C, hipMemcpyDeviceToHost, d.stream));
-        HIPCHECK(hipStreamSynchronize(d.stream));
-        for (int k = 0; k < npts; ++k) out_host[k] = reaction_host_sum((int)C, h + k * C);
-        return;
-    }
     launch_reaction(d, npts, pts_dev, part, out);
     HIPCHECK(hipMemcpyAsync(out_host, out, sizeof(double) * npts, hipMemcpyDeviceToHost, d.stream));
     HIPCHECK(hipStreamSynchronize(d.stream));
